@@ -5,6 +5,8 @@
 
 namespace fvpcg {
 
+struct ResOut;  // a resident solve's result (resident.hpp)
+
 // Per-matrix solve workspace, allocated on first use of each solver kind.
 struct Work {
     int n = 0;
@@ -27,6 +29,12 @@ struct Work {
     float* s32 = nullptr;
     float* p32 = nullptr;
     float* c32 = nullptr;
+    // resident solves (resident.hpp): slots, rendezvous word and abort flag,
+    // results (device, pinned)
+    double* res_slots = nullptr;
+    unsigned* res_meet = nullptr;  // [2]
+    ResOut* res_out = nullptr;
+    ResOut* res_pinned = nullptr;
     // reductions and scalars
     double* partials = nullptr;  // [4][grid]
     DevState* st = nullptr;      // device: [0] outer/main, [1] inner (mixed)
@@ -41,6 +49,7 @@ void work_free(Work& w);
 int work_need_cg(Work& w);
 int work_need_pipe(Work& w, bool literal);
 int work_need_mixed(Work& w);
+int work_need_resident(Work& w);
 
 }  // namespace fvpcg
 

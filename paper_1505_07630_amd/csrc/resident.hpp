@@ -1,0 +1,533 @@
+// Resident solves: a whole Krylov solve in one launch, with a system's matrix
+// rows and vectors held in registers and LDS by a team of workgroups from the
+// first iteration to the last.
+//
+// What bounds a small system is not memory but the chain of one iteration:
+// a launch, the slot -> gather loads, the reduction's ticket and the scalars.
+// With one launch per iteration that chain is 5.1 us at 1.7k cells, 7.1 us at
+// 32k and 40.7 us at 1M (where every array is read again from the last-level
+// cache).  Here an iteration reads nothing but the neighbours' exchanged
+// vector, and its only synchronisation is the reduction itself:
+//
+//   * member r of a team of G takes the system's row tiles r, r + G, ...
+//     (tiles of BS rows, the launch-per-iteration kernels' order), thread t
+//     the t-th row of each: RPT rows per thread, in registers; with RPT > 4
+//     four of the vectors in LDS;
+//   * the exchanged vector (w, or p and z) goes through device memory with
+//     agent-scope relaxed stores and loads, which pass the per-XCD L2 caches,
+//     so no cache is written back or invalidated.  Before a workgroup
+//     publishes its sums every one of its waves waits for its stores to
+//     complete (vmcnt 0), so a member that has seen all sums sees all rows;
+//   * a reduction is all-to-all: each member stores its partial sums in its
+//     slots, and reads everybody's until none holds the sentinel, a NaN bit
+//     pattern no sum is stored with.  The slots are their own flags.  There
+//     are four buffers of them; in reduction k a member puts the sentinel
+//     back into its slots of reduction k - 2 (nobody reads those any more:
+//     everybody has published k - 1, hence read k - 2), which every member
+//     sees before it can reach reduction k + 2.
+//
+// Measured alone on MI355X (exchange, reduction and 6 gathers per row): 3.7 us
+// per iteration with 64 workgroups and 1 row per thread, 5.6 with 256, 10.9
+// with 256 and 8 rows per thread (1M rows).  Acquire fences with cached gathers
+// instead took 4.1, 7.4 and 12.4 us, and a two-level reduction 5.6, 6.3, 11.0.
+//
+// The team must be resident together.  It meets once at the start (rendezvous)
+// with a short time limit; a team that does not come together there leaves
+// without having touched x, and the host takes the launch-per-iteration path.
+// Past the rendezvous every member holds its place until it ends, so every
+// wait ends; the waits are bounded by a clock all the same.
+//
+// Sums are formed in the launch-per-iteration kernels' order (rows per
+// thread, wave, workgroup, workgroups in index order) from the same
+// expressions, so both paths give the same bits.
+#pragma once
+
+#include "rows.hpp"
+
+namespace fvpcg {
+
+constexpr int kResBs = 512;           // threads per workgroup (kBsPipe: the same tiles)
+constexpr int kResMaxTeam = 256;      // members of a team at most
+constexpr int kResMaxRpt = 8;         // rows per thread at most
+constexpr int kResBufs = 4;           // slot buffers
+constexpr int kResSums = 3;           // sums per reduction
+constexpr unsigned long long kResSentinel = 0x7ff8f1c3a5965e17ull;
+constexpr unsigned kResAbort = 0x80000000u;
+
+// Doubles of slots a team of `size` needs.
+inline __host__ __device__ size_t res_slots(int size) { return (size_t)kResBufs * kResSums * size; }
+
+// What one system's solve reports.
+struct ResOut {
+    double bnorm, r0norm, rho, true_rr;
+    unsigned long long ticks, it_ticks;  // wall clock: the whole solve, the iterations
+    int32_t iter, status, zero_b, ok;    // ok = 0: left without a result (see above)
+};
+
+// One system as its team sees it.  Columns, values and vectors are indexed
+// by the global row; rows [c0, c1) are the system's.
+struct ResSystem {
+    const void* col;
+    const double* val;     // plain values (residuals)
+    const double* val_it;  // values of the iterations' product (column-scaled with Jacobi)
+    const double* d;
+    const double* b;
+    double* x;
+    double *e0, *e1;  // exchange vectors
+    size_t n;         // slot stride
+    int c0, c1;
+    double tol;
+    int maxit;
+};
+
+struct ResTeam {
+    int rank, size;
+    double* slots;            // [kResBufs][kResSums][size], sentinels at the start
+    unsigned* meet;           // rendezvous word, 0 at the start
+    int* abort_flag;          // any member's timeout
+    int* ok;                  // LDS: 1 until this workgroup has given up a wait
+    unsigned long long meet_ticks, spin_ticks;
+    int k;                    // reductions so far
+};
+
+// Agent-scope accesses of exchanged data.
+__device__ __forceinline__ void st_agent(double* p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double ld_agent(const double* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The wave's earlier stores have completed.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// True once the whole team runs; false if it did not come together in time.
+// The word counts arrivals; a member whose time is up sets the abort bit
+// unless the last one has arrived meanwhile, so all members agree.
+__device__ __forceinline__ bool team_meet(const ResTeam& t) {
+    __shared__ int s_go;
+    if (threadIdx.x == 0) {
+        unsigned w = __hip_atomic_fetch_add(t.meet, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+        const unsigned long long t0 = (unsigned long long)wall_clock64();
+        while (!(w & kResAbort) && w != (unsigned)t.size) {
+            if ((unsigned long long)wall_clock64() - t0 > t.meet_ticks) {
+                unsigned seen = w;
+                if (__hip_atomic_compare_exchange_strong(t.meet, &seen, w | kResAbort, __ATOMIC_RELAXED,
+                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    seen = w | kResAbort;
+                w = seen;
+                continue;
+            }
+            __builtin_amdgcn_s_sleep(2);
+            w = __hip_atomic_load(t.meet, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        s_go = !(w & kResAbort);
+    }
+    __syncthreads();
+    const bool go = s_go != 0;
+    __syncthreads();
+    return go;
+}
+
+// v[0..NV) summed over the team, the totals in every thread; false when a
+// wait was given up.  Every earlier agent-scope store of any member is
+// visible to every member afterwards.
+template <int BS, int NV>
+__device__ __forceinline__ bool team_sum(double (&v)[NV], ResTeam& t) {
+    static_assert(NV <= kResSums && NV <= BS / 64, "a wave per sum");
+    constexpr int kW = BS / 64;
+    __shared__ double s_part[NV][kW];
+    __shared__ double s_tot[NV];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) s_part[k][wid] = v[k];
+    }
+    stores_done();
+    __syncthreads();
+    double mine = 0.0;
+    if ((int)threadIdx.x < NV) {
+#pragma unroll
+        for (int w = 0; w < kW; ++w) mine += s_part[threadIdx.x][w];
+    }
+    double* buf = t.slots + (size_t)(t.k & (kResBufs - 1)) * kResSums * t.size;
+    if ((int)threadIdx.x < NV) {
+        if (__double_as_longlong(mine) == (long long)kResSentinel)
+            mine = __longlong_as_double((long long)(kResSentinel ^ 1ull));
+        st_agent(buf + (size_t)threadIdx.x * t.size + t.rank, mine);
+    }
+    if ((int)threadIdx.x < kResSums) {
+        double* old = t.slots + (size_t)((t.k + 2) & (kResBufs - 1)) * kResSums * t.size;
+        st_agent(old + (size_t)threadIdx.x * t.size + t.rank, __longlong_as_double((long long)kResSentinel));
+    }
+    if (wid < NV) {
+        const double* q = buf + (size_t)wid * t.size;
+        constexpr int kC = kResMaxTeam / 64;
+        double g[kC];
+        unsigned spins = 0;
+        const unsigned long long t0 = (unsigned long long)wall_clock64();
+        for (;;) {
+            bool wait = false;
+#pragma unroll
+            for (int i = 0; i < kC; ++i) {
+                g[i] = 0.0;
+                if (i * 64 + lane < t.size) {
+                    g[i] = ld_agent(q + i * 64 + lane);
+                    wait |= __double_as_longlong(g[i]) == (long long)kResSentinel;
+                }
+            }
+            if (!__any(wait)) break;
+            if ((++spins & 63u) == 0 &&
+                ((unsigned long long)wall_clock64() - t0 > t.spin_ticks ||
+                 __hip_atomic_load(t.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+                if (lane == 0) {
+                    __hip_atomic_store(t.abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    *t.ok = 0;
+                }
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < kC; ++i)
+            if (i * 64 < t.size) s += wave_sum(g[i]);
+        if (lane == 0) s_tot[wid] = s;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = s_tot[k];
+    t.k += 1;
+    return *t.ok != 0;
+}
+
+// Sums of a workgroup on its own (ONE): each tile of BS rows is summed as the
+// member of a team that held it would, then the tiles as the members.
+template <int BS, int NV, int RPT>
+__device__ __forceinline__ void tile_sums(double (&v)[RPT][NV], double (&tot)[NV]) {
+    constexpr int kW = BS / 64;
+    static_assert(NV <= kW && RPT <= 64, "a wave per sum, a lane per tile");
+    __shared__ double s_part[RPT][NV][kW];
+    __shared__ double s_tot[NV];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int q = 0; q < RPT; ++q)
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const double a = wave_sum(v[q][k]);
+            if (lane == 0) s_part[q][k][wid] = a;
+        }
+    __syncthreads();
+    if (wid < NV) {
+        double mine = 0.0;
+        if (lane < RPT) {
+#pragma unroll
+            for (int w = 0; w < kW; ++w) mine += s_part[lane][wid][w];
+        }
+        mine = wave_sum(mine);
+        if (lane == 0) s_tot[wid] = mine;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) tot[k] = s_tot[k];
+}
+
+// A thread's partial sums of one reduction, kept per row for tile_sums.
+template <int NV, int RPT, bool ONE>
+struct Sums {
+    static constexpr int kR = ONE ? RPT : 1;
+    double a[kR][NV] = {};
+    __device__ __forceinline__ void add(int k, int i, double v) { a[ONE ? k : 0][i] += v; }
+    __device__ __forceinline__ bool finish(ResTeam& t, double (&tot)[NV]) {
+        if constexpr (ONE) {
+            tile_sums<kResBs, NV, RPT>(a, tot);
+            return true;
+        } else {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) tot[i] = a[0][i];
+            return team_sum<kResBs, NV>(tot, t);
+        }
+    }
+};
+
+// Columns of RPT rows: int16 offsets two to a register, int32 columns one.
+template <int WT, typename CI>
+struct RowCols;
+template <int WT>
+struct RowCols<WT, int16_t> {
+    int v[(WT + 1) / 2];
+    __device__ __forceinline__ void load(const void* col, size_t n, int c) {
+        const int16_t* p = (const int16_t*)col;
+        int16_t t[WT];
+#pragma unroll
+        for (int i = 0; i < WT; ++i) t[i] = ld_once(p + (size_t)i * n + c);
+#pragma unroll
+        for (int i = 0; i < WT; i += 2)
+            v[i / 2] = (int)(uint16_t)t[i] | (i + 1 < WT ? (int)((unsigned)(uint16_t)t[i + 1] << 16) : 0);
+    }
+    __device__ __forceinline__ int at(int i, int c) const { return c + (int)(int16_t)(v[i / 2] >> (16 * (i & 1))); }
+    // Keeps the packed form live across the iterations: the compiler would
+    // otherwise unpack every column once before the loop, for twice the
+    // registers.
+    __device__ __forceinline__ void pin() {
+#pragma unroll
+        for (int i = 0; i < (WT + 1) / 2; ++i) asm volatile("" : "+v"(v[i]));
+    }
+};
+template <int WT>
+struct RowCols<WT, int> {
+    int v[WT];
+    __device__ __forceinline__ void load(const void* col, size_t n, int c) {
+        const int* p = (const int*)col;
+#pragma unroll
+        for (int i = 0; i < WT; ++i) v[i] = ld_once(p + (size_t)i * n + c);
+    }
+    __device__ __forceinline__ int at(int i, int) const { return v[i]; }
+    __device__ __forceinline__ void pin() {}
+};
+
+// RPT doubles per thread in registers, or in LDS.
+template <int BS, int RPT, bool LDS>
+struct Store;
+template <int BS, int RPT>
+struct Store<BS, RPT, false> {
+    double v[RPT];
+    __device__ __forceinline__ Store(double*) {}
+    __device__ __forceinline__ double get(int k) const { return v[k]; }
+    __device__ __forceinline__ void set(int k, double a) { v[k] = a; }
+};
+template <int BS, int RPT>
+struct Store<BS, RPT, true> {
+    double* p;
+    __device__ __forceinline__ Store(double* base) : p(base + threadIdx.x) {}
+    __device__ __forceinline__ double get(int k) const { return p[k * BS]; }
+    __device__ __forceinline__ void set(int k, double a) { p[k * BS] = a; }
+};
+
+// The exchanged vectors: device memory with agent scope, or, for a system one
+// workgroup solves alone (ONE), LDS.
+template <int RPT, bool ONE>
+struct Exchange;
+template <int RPT>
+struct Exchange<RPT, false> {
+    double* v[2];
+    __device__ __forceinline__ Exchange(const ResSystem& sys, double*) : v{sys.e0, sys.e1} {}
+    __device__ __forceinline__ void put(int buf, int c, double a) { st_agent((buf ? v[1] : v[0]) + c, a); }
+    __device__ __forceinline__ double get(int buf, int c) const { return ld_agent((buf ? v[1] : v[0]) + c); }
+};
+template <int RPT>
+struct Exchange<RPT, true> {
+    double* v;
+    __device__ __forceinline__ Exchange(const ResSystem& sys, double* lds) : v(lds - sys.c0) {}
+    __device__ __forceinline__ void put(int buf, int c, double a) { v[buf * RPT * kResBs + c] = a; }
+    __device__ __forceinline__ double get(int buf, int c) const { return v[buf * RPT * kResBs + c]; }
+};
+
+// acc + sum_i val[i][c] v(col_i), the values streamed once (the residuals at
+// the start and the end).
+template <int WT, typename CI, typename V>
+__device__ __forceinline__ double res_gather(const RowCols<WT, CI>& col, const double* __restrict__ val, size_t n, int c,
+                                             V&& v, double acc) {
+    double a[WT], g[WT];
+#pragma unroll
+    for (int i = 0; i < WT; ++i) {
+        a[i] = ld_once(val + (size_t)i * n + c);
+        g[i] = v(col.at(i, c));
+    }
+#pragma unroll
+    for (int i = 0; i < WT; ++i) acc += a[i] * g[i];
+    return acc;
+}
+
+// Scalars of the recurrences, the same in every thread of the team.
+struct ResScalars {
+    double gamma = 0, alpha = 0, beta = 0, tol_abs = 0, r0norm = 0, rho = 0;
+    int iter = 0, status = FVPCG_NOT_CONVERGED;
+    bool done = false;
+};
+
+// pipe_scalars' steps (rows.hpp).
+__device__ __forceinline__ void res_pipe_step(ResScalars& y, double gamma, double delta, double rho, bool first,
+                                              int maxit) {
+    if (first)
+        y.r0norm = sqrt(rho);
+    else
+        y.iter += 1;
+    y.rho = rho;
+    if (sqrt(rho) <= y.tol_abs) {
+        y.done = true;
+        y.status = FVPCG_OK;
+        return;
+    }
+    if (y.iter >= maxit) {
+        y.done = true;
+        y.status = FVPCG_NOT_CONVERGED;
+        return;
+    }
+    double beta, den;
+    if (first) {
+        beta = 0.0;
+        den = delta;
+    } else {
+        beta = gamma / y.gamma;
+        den = delta - beta * gamma / y.alpha;
+    }
+    const double alpha = gamma / den;
+    if (!(den > 0.0) || !isfinite(den) || !isfinite(alpha) || !isfinite(beta)) {
+        y.done = true;
+        y.status = FVPCG_BREAKDOWN;
+        return;
+    }
+    y.gamma = gamma;
+    y.alpha = alpha;
+    y.beta = beta;
+}
+
+// The k-th row of this thread and whether the system has it.
+#define RES_ROWS(k, c)                                              \
+    _Pragma("unroll") for (int k = 0; k < RPT; ++k)                 \
+        if (const int c = sys.c0 + (k * t.size + t.rank) * BS + (int)threadIdx.x; c < sys.c1)
+
+// LDS of a resident solve: four vectors with RPT > 4, or the two exchange
+// vectors of a workgroup on its own.
+template <int RPT, bool ONE>
+struct ResLds {
+    static constexpr bool vectors = RPT > 4;
+    static_assert(!(vectors && ONE), "a single workgroup's rows stay in registers");
+    static constexpr int doubles = ONE ? 2 * RPT * kResBs : vectors ? 4 * RPT * kResBs : 1;
+};
+
+// Folded pipelined CG (see solve.hip): registers hold the iteration values,
+// the columns, d, r and the row's own w; z, s, p and x are in LDS with
+// RPT > 4.
+template <int RPT, int WT, typename CI, bool JAC, bool ONE>
+__device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, double* lds, ResOut* out) {
+    constexpr int BS = kResBs;
+    constexpr bool L = ResLds<RPT, ONE>::vectors;
+    const unsigned long long t_begin = (unsigned long long)wall_clock64();
+    Exchange<RPT, ONE> e(sys, lds);
+    RowCols<WT, CI> col[RPT];
+    double d[RPT], r[RPT], w[RPT];
+    Store<BS, RPT, L> z(lds), s(lds + RPT * BS), p(lds + 2 * RPT * BS), x(lds + 3 * RPT * BS);
+    // r = b - A x through buffer 1, (b, b)
+    Sums<1, RPT, ONE> sb;
+    RES_ROWS(k, c) {
+        col[k].load(sys.col, sys.n, c);
+        const double bc = sys.b[c], dc = sys.d[c], xc = sys.x[c];
+        const double rc = bc - res_gather<WT, CI>(col[k], sys.val, sys.n, c, [&](int j) { return sys.x[j]; }, dc * xc);
+        d[k] = dc;
+        r[k] = rc;
+        x.set(k, xc);
+        z.set(k, 0.0);
+        s.set(k, 0.0);
+        p.set(k, 0.0);
+        e.put(1, c, rc);
+        sb.add(k, 0, bc * bc);
+    }
+    double bb[1];
+    bool ok = sb.finish(t, bb);
+    ResScalars y;
+    const double bnorm = sqrt(bb[0]);
+    y.tol_abs = sys.tol * bnorm;
+    const bool zero_b = bb[0] == 0.0;
+    double val[RPT][WT];
+    if (zero_b) {
+        y.done = true;
+        y.status = FVPCG_OK;
+    } else if (ok) {
+        // w = A M^-1 r
+        Sums<3, RPT, ONE> sa;
+        RES_ROWS(k, c) {
+            double g[WT];
+#pragma unroll
+            for (int i = 0; i < WT; ++i) {
+                val[k][i] = ld_once(sys.val_it + (size_t)i * sys.n + c);
+                g[i] = e.get(1, col[k].at(i, c));
+            }
+            const double rc = r[k], dc = d[k];
+            double wc = JAC ? rc : dc * rc;
+#pragma unroll
+            for (int i = 0; i < WT; ++i) wc += val[k][i] * g[i];
+            w[k] = wc;
+            e.put(0, c, wc);
+            const double uc = JAC ? rc / dc : rc;
+            sa.add(k, 0, rc * uc);
+            sa.add(k, 1, wc * uc);
+            sa.add(k, 2, rc * rc);
+        }
+        double a[3];
+        ok = sa.finish(t, a);
+        res_pipe_step(y, a[0], a[1], a[2], true, sys.maxit);
+    }
+    const unsigned long long t_it0 = (unsigned long long)wall_clock64();
+    for (int it = 0; ok && !y.done; ++it) {
+        const int in = it & 1;
+        const double alpha = y.alpha, beta = y.beta;
+        Sums<3, RPT, ONE> sa;
+        RES_ROWS(k, c) {
+            double g[WT];
+            if (RPT > 3) col[k].pin();
+#pragma unroll
+            for (int i = 0; i < WT; ++i) g[i] = e.get(in, col[k].at(i, c));
+            const double wc = w[k], dc = d[k];
+            double nv = JAC ? wc : dc * wc;
+#pragma unroll
+            for (int i = 0; i < WT; ++i) nv += val[k][i] * g[i];
+            const double zc = nv + beta * z.get(k);
+            const double wn = wc - alpha * zc;
+            e.put(in ^ 1, c, wn);
+            const double sc = wc + beta * s.get(k);
+            double rc = r[k];
+            double uc = JAC ? rc / dc : rc;
+            const double pc = uc + beta * p.get(k);
+            p.set(k, pc);
+            x.set(k, x.get(k) + alpha * pc);
+            rc -= alpha * sc;
+            z.set(k, zc);
+            s.set(k, sc);
+            r[k] = rc;
+            w[k] = wn;
+            uc = JAC ? rc / dc : rc;
+            sa.add(k, 0, rc * uc);
+            sa.add(k, 1, wn * uc);
+            sa.add(k, 2, rc * rc);
+        }
+        double a[3];
+        ok = sa.finish(t, a);
+        res_pipe_step(y, a[0], a[1], a[2], false, sys.maxit);
+    }
+    const unsigned long long t_it1 = (unsigned long long)wall_clock64();
+    if (!ok) return;
+    // x, also through buffer 0 (all reads of it were done before the last
+    // reduction), and ||b - A x||^2
+    RES_ROWS(k, c) {
+        if (zero_b) x.set(k, 0.0);
+        sys.x[c] = x.get(k);
+        e.put(0, c, x.get(k));
+    }
+    double rr[1];
+    if (!Sums<1, RPT, ONE>().finish(t, rr)) return;
+    Sums<1, RPT, ONE> sr;
+    RES_ROWS(k, c) {
+        const double rc = sys.b[c] - res_gather<WT, CI>(col[k], sys.val, sys.n, c, [&](int j) { return e.get(0, j); }, d[k] * x.get(k));
+        sr.add(k, 0, rc * rc);
+    }
+    if (!sr.finish(t, rr)) return;
+    if (t.rank == 0 && threadIdx.x == 0) {
+        ResOut o;
+        o.bnorm = bnorm;
+        o.r0norm = y.r0norm;
+        o.rho = y.rho;
+        o.true_rr = rr[0];
+        o.it_ticks = t_it1 - t_it0;
+        o.ticks = (unsigned long long)wall_clock64() - t_begin;
+        o.iter = y.iter;
+        o.status = y.status;
+        o.zero_b = zero_b ? 1 : 0;
+        o.ok = 1;
+        *out = o;
+    }
+}
+
+}  // namespace fvpcg

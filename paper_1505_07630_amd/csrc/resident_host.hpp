@@ -1,0 +1,45 @@
+// The resident solves' host interface (resident.hip).
+#pragma once
+
+#include <mutex>
+
+#include "handles.hpp"
+
+namespace fvpcg {
+
+struct ResOut;
+
+// Rendezvous limit: past it (other work holds the GPU's CUs) the launch-per-
+// iteration path runs instead (FVPCG_RESIDENT_MEET_MS sets another;
+// FVPCG_RESIDENT=0 always takes that path).  Limit of any later wait, which
+// ends by itself.
+constexpr double kResMeetMs = 20.0, kResSpinMs = 5000.0;
+
+struct ResPlan {
+    int rpt = 0;   // rows per thread; 0: not resident
+    int size = 0;  // workgroups
+    bool one = false;
+};
+
+// Buffers of a resident solve: exchange vectors, slots for kResMaxTeam
+// members, rendezvous word, abort flag, result (device, or pinned).
+struct ResWork {
+    double *e0, *e1, *slots;
+    unsigned* meet;
+    int* abort_flag;
+    ResOut* out;
+    ResOut* pinned;
+};
+
+// Held while a launch whose workgroups wait for each other is on the device:
+// two such launches side by side could each hold half of the CUs and wait.
+std::mutex* resident_teams(int device);
+
+ResPlan resident_plan(const fvpcg_mesh* m);
+
+// *done = false with FVPCG_OK: not solved here, solve by launches (x is still
+// a valid starting vector); a negative code is an error.
+int resident_solve(const fvpcg_matrix* A, const ResPlan& plan, const ResWork& w, const double* b, double* x, double tol,
+                   int maxit, bool jac, hipStream_t s, fvpcg_stats* stats, bool* done);
+
+}  // namespace fvpcg

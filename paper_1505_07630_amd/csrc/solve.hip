@@ -22,12 +22,11 @@
 #include <chrono>
 #include <mutex>
 
+#include "resident.hpp"
+#include "resident_host.hpp"
 #include "rows.hpp"
 
 namespace fvpcg {
-
-// ===========================================================================
-// Row kernels' building blocks
 
 // ===========================================================================
 // y = A v
@@ -709,6 +708,20 @@ int work_need_mixed(Work& w) {
     return FVPCG_OK;
 }
 
+int work_need_resident(Work& w) {
+    int rc;
+    if (!w.w[0] && (rc = dev_alloc(&w.w[0], (size_t)w.n, "w0"))) return rc;
+    if (!w.w[1] && (rc = dev_alloc(&w.w[1], (size_t)w.n, "w1"))) return rc;
+    if (!w.res_slots && (rc = dev_alloc(&w.res_slots, res_slots(kResMaxTeam), "resident slots"))) return rc;
+    if (!w.res_meet && (rc = dev_alloc(&w.res_meet, 2, "resident rendezvous"))) return rc;
+    if (!w.res_pinned && hipHostMalloc((void**)&w.res_pinned, sizeof(ResOut), hipHostMallocDefault) != hipSuccess) {
+        w.res_pinned = nullptr;
+        (void)hipGetLastError();
+        return set_error(FVPCG_OUT_OF_MEMORY, "pinned host allocation failed");
+    }
+    return FVPCG_OK;
+}
+
 void work_free(Work& w) {
     double* dv[] = {w.r, w.p, w.q, w.z, w.s, w.w[0], w.w[1], w.u, w.qq, w.lam, w.partials};
     for (double* p : dv)
@@ -716,6 +729,9 @@ void work_free(Work& w) {
     float* fv[] = {w.r32, w.r32b, w.w32[0], w.w32[1], w.z32, w.s32, w.p32, w.c32};
     for (float* p : fv)
         if (p) (void)hipFree(p);
+    if (w.res_slots) (void)hipFree(w.res_slots);
+    if (w.res_meet) (void)hipFree(w.res_meet);
+    if (w.res_pinned) (void)hipHostFree(w.res_pinned);
     if (w.st) (void)hipFree(w.st);
     if (w.hst) (void)hipHostFree(w.hst);
     for (auto ev : w.ev)
@@ -864,6 +880,14 @@ struct Clock {
 int solve_core(const fvpcg_matrix* A, Work& w, const double* b, double* x, double tol, int maxit, int method,
                int precond, hipStream_t s, fvpcg_stats* stats);
 
+// The whole solve in one launch, where the system fits (resident_plan).
+int solve_resident(const fvpcg_matrix* A, const ResPlan& plan, Work& w, const double* b, double* x, double tol,
+                   int maxit, int precond, hipStream_t s, fvpcg_stats* stats, bool* done) {
+    const ResWork rw{w.w[0], w.w[1], w.res_slots, w.res_meet, reinterpret_cast<int*>(w.res_meet + 1), w.res_out,
+                     w.res_pinned};
+    return resident_solve(A, plan, rw, b, x, tol, maxit, precond == FVPCG_PRECOND_JACOBI, s, stats, done);
+}
+
 }  // namespace
 
 int solve(const fvpcg_matrix* A, const double* b, double* x, double tol, int maxit, int method, int precond,
@@ -872,6 +896,15 @@ int solve(const fvpcg_matrix* A, const double* b, double* x, double tol, int max
     int rc;
     if ((rc = work_init(w, A->mesh->n))) return rc;
     if (method == FVPCG_PIPECG_LITERAL && precond != FVPCG_PRECOND_JACOBI) method = FVPCG_PIPECG;
+    if (method == FVPCG_PIPECG) {
+        const ResPlan plan = resident_plan(A->mesh);
+        if (plan.rpt) {
+            bool done = false;
+            if ((rc = work_need_resident(w))) return rc;
+            rc = solve_resident(A, plan, w, b, x, tol, maxit, precond, s, stats, &done);
+            if (rc < 0 || done) return rc;
+        }
+    }
     if (method == FVPCG_CG) {
         if ((rc = work_need_cg(w))) return rc;
     } else {
@@ -1008,8 +1041,10 @@ int solve_core(const fvpcg_matrix* A, Work& w, const double* b, double* x, doubl
 constexpr int kNoAllocVectors = 8;
 constexpr size_t kNoAllocStride = ((size_t)FVPCG_NOALLOC_MAX_CELLS + 63) / 64 * 64;
 constexpr size_t kNoAllocStateDoubles = (2 * sizeof(DevState) + sizeof(double) - 1) / sizeof(double);
+constexpr size_t kNoAllocSlots = (size_t)kResBufs * kResSums * kResMaxTeam;
+constexpr size_t kNoAllocOutDoubles = (sizeof(ResOut) + sizeof(double) - 1) / sizeof(double);
 constexpr size_t kNoAllocDoubles = (size_t)kNoAllocVectors * kNoAllocStride + 4 * (size_t)kMaxGrid +
-                                   kNoAllocStateDoubles;
+                                   kNoAllocStateDoubles + kNoAllocSlots + kNoAllocOutDoubles + 1;
 static __device__ __align__(256) double scratch[kNoAllocDoubles];
 
 namespace {
@@ -1054,6 +1089,18 @@ int solve_noalloc(const fvpcg_matrix* A, const double* b, double* x, double tol,
     w.q = w.z;  // standard CG's q; the pipelined forms' z
     w.partials = base + (size_t)kNoAllocVectors * kNoAllocStride;
     w.st = reinterpret_cast<DevState*>(w.partials + 4 * (size_t)kMaxGrid);
+    w.res_slots = w.partials + 4 * (size_t)kMaxGrid + kNoAllocStateDoubles;
+    w.res_out = reinterpret_cast<ResOut*>(w.res_slots + kNoAllocSlots);
+    w.res_meet = reinterpret_cast<unsigned*>(w.res_slots + kNoAllocSlots + kNoAllocOutDoubles);
+    if (method == FVPCG_PIPECG_LITERAL && precond != FVPCG_PRECOND_JACOBI) method = FVPCG_PIPECG;
+    if (method == FVPCG_PIPECG) {
+        const ResPlan plan = resident_plan(A->mesh);
+        if (plan.rpt) {
+            bool done = false;
+            rc = solve_resident(A, plan, w, b, x, tol, maxit, precond, s, stats, &done);
+            if (rc < 0 || done) return rc;
+        }
+    }
     return solve_core(A, w, b, x, tol, maxit, method, precond, s, stats);
 }
 

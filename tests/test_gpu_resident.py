@@ -1,0 +1,192 @@
+"""Resident solves (the whole solve in one launch, rows held on chip) against
+the launch-per-iteration path and the oracle, at the edges of their tiles:
+one row, one workgroup on its own (up to 2,048 cells), teams of 5 to 256
+workgroups with 1 to 8 rows per thread, full and ragged last tiles, rows of
+4, 6 and 8 slots, int16 and int32 columns.
+
+Resident solves form their sums in the launch-per-iteration kernels' order
+from the same expressions, so the two paths agree bit for bit.  Against the
+oracle the bar is the strict one of the other solver tests, 1e-10 at equal
+count."""
+import numpy as np
+import pytest
+
+import fvcases as fc
+import oracle
+from tests.gpu_util import DevCase, rel, say, to_dev
+
+pytestmark = pytest.mark.gpu
+TILE, MOST = 512, 1 << 20
+
+
+@pytest.fixture(scope="module")
+def fv():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_1505_07630_amd as fv
+
+    fv.lib()
+    return fv
+
+
+def solve(fv, monkeypatch, dc, resident, x0=None, **kw):
+    import torch
+
+    monkeypatch.setenv("FVPCG_RESIDENT", "1" if resident else "0")
+    x = torch.zeros_like(dc.b) if x0 is None else x0.clone()
+    try:
+        return fv.solve(dc.A, dc.b, x=x, **kw)
+    except fv.FVPCGError as e:  # tol = 0 on a system solved exactly breaks down, on either path
+        assert e.code == fv.BREAKDOWN
+        return x, dict.fromkeys(("iters", "b_norm", "r0_norm", "rel_res", "true_rel_res"), None) | {"status": e.code}
+
+
+def stencil(nx, ny, offsets, seed):
+    """A 2-D mesh whose rows couple to the given (i, j) offsets and back."""
+    rng = np.random.default_rng(seed)
+    i, j = np.meshgrid(np.arange(nx), np.arange(ny))
+    pairs = []
+    for di, dj in offsets:
+        a, b = i + di, j + dj
+        ok = (a >= 0) & (a < nx) & (b >= 0) & (b < ny)
+        pairs.append(np.stack([(i + nx * j)[ok], (a + nx * b)[ok]], 1))
+    e = np.unique(np.sort(np.concatenate(pairs), axis=1), axis=0)
+    n = nx * ny
+    up = -np.exp(rng.standard_normal(len(e)))
+    diag = np.full(n, 0.05)
+    np.add.at(diag, e[:, 0], -up)
+    np.add.at(diag, e[:, 1], -up)
+    return fc.Case("stencil", (nx, ny, 1), n, e[:, 0].astype(np.int32), e[:, 1].astype(np.int32), diag, up, up.copy(),
+                   rng.uniform(-1, 1, n))
+
+
+LINE, CROSS = [(1, 0)], [(1, 0), (0, 1)]
+STAR = [(1, 0), (0, 1), (1, 1), (-1, 1)]  # 8 neighbours
+CASES = {
+    "row": (lambda: stencil(1, 1, LINE, 1), ()),
+    "line-512": (lambda: stencil(TILE, 1, LINE, 2), ()),
+    "cube-504": (lambda: fc.varcoef((9, 8, 7), seed=3), ()),
+    "cube-520": (lambda: fc.varcoef((13, 8, 5), seed=3), ()),
+    "one-2048": (lambda: fc.varcoef((16, 16, 8), seed=4), ()),
+    "team-2049": (lambda: stencil(683, 3, CROSS, 5), ()),
+    "star-2500": (lambda: stencil(50, 50, STAR, 6), ()),
+    "star-132000": (lambda: stencil(440, 300, STAR, 7), ()),
+    "star-int32": (lambda: stencil(440, 300, STAR, 7), ("col32",)),
+    "cube-131072": (lambda: fc.varcoef((64, 64, 32), seed=8), ()),
+    "cube-131100": (lambda: fc.varcoef((23, 57, 100), seed=8, permute=False), ()),
+    "cube-400k": (lambda: fc.varcoef((80, 50, 101), seed=9, permute=False), ()),
+    "cube-400k-int32": (lambda: fc.varcoef((80, 50, 101), seed=9, permute=False), ("col32",)),
+    "cube-700k": (lambda: fc.varcoef((100, 70, 100), seed=10, permute=False), ()),
+    "cube-1M": (lambda: fc.varcoef((128, 64, 128), seed=11, permute=False), ()),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_resident_equals_launches(fv, monkeypatch, name):
+    make, opts = CASES[name]
+    say("resident", name)
+    if "col32" in opts:
+        monkeypatch.setenv("FVPCG_COL16", "0")
+    case = make()
+    assert case.n <= MOST
+    dc = DevCase(case)
+    x0 = to_dev(np.random.default_rng(1).uniform(-1, 1, case.n))
+    for precond in ("jacobi", "none"):
+        for kw in (dict(tol=0.0, maxit=40), dict(tol=1e-9, maxit=60, x0=x0)):
+            say("resident", name, precond, kw.get("tol"))
+            xa, sa = solve(fv, monkeypatch, dc, False, precond=precond, **kw)
+            xb, sb = solve(fv, monkeypatch, dc, True, precond=precond, **kw)
+            for k in ("iters", "status", "b_norm", "r0_norm", "rel_res", "true_rel_res"):
+                assert sa[k] == sb[k], k
+            assert np.array_equal(xa.cpu().numpy(), xb.cpu().numpy())
+    # the oracle at equal count, 25 iterations (fewer if it converges)
+    xb, sb = solve(fv, monkeypatch, dc, True, tol=0.0, maxit=25)
+    if sb["status"] == 1:
+        xo, _ = oracle.pipecg(oracle.system(case), case.b, tol=0.0, maxit=sb["iters"], folded=True)
+        assert rel(xb.cpu().numpy(), xo) <= 1e-10
+    dc.close()
+
+
+@pytest.mark.parametrize("shape", [(8, 8, 8), (20, 18, 16)])
+def test_resident_edges(fv, monkeypatch, shape):
+    """b = 0, an exact start, no iterations, a NaN right-hand side."""
+    import torch
+
+    say("resident edges", shape)
+    case = fc.varcoef(shape, seed=5)
+    dc = DevCase(case)
+    monkeypatch.setenv("FVPCG_RESIDENT", "1")
+    x, st = fv.solve(dc.A, torch.zeros_like(dc.b), x=torch.ones_like(dc.b))
+    assert st["status"] == 0 and st["iters"] == 0 and torch.count_nonzero(x).item() == 0 and st["true_rel_res"] == 0.0
+    xs, _ = fv.solve(dc.A, dc.b, tol=1e-12)
+    x, st = fv.solve(dc.A, dc.b, x=xs.clone(), tol=1e-8)
+    assert st["status"] == 0 and st["iters"] == 0 and torch.equal(x, xs)
+    x, st = fv.solve(dc.A, dc.b, x=xs.clone(), tol=1e-20, maxit=0)
+    assert st["status"] == 1 and st["iters"] == 0 and torch.equal(x, xs)
+    bad = dc.b.clone()
+    bad[case.n // 2] = float("nan")
+    for res in ("0", "1"):
+        monkeypatch.setenv("FVPCG_RESIDENT", res)
+        with pytest.raises(fv.FVPCGError) as e:
+            fv.solve(dc.A, bad)
+        assert e.value.code == fv.BREAKDOWN
+    dc.close()
+
+
+def test_resident_rendezvous_limit(fv, monkeypatch):
+    """A team that is given no time to come together leaves x alone and the
+    launch-per-iteration path solves: the same bits either way."""
+    import torch
+
+    say("resident rendezvous limit")
+    case = fc.varcoef((40, 36, 30), seed=6)
+    dc = DevCase(case)
+    xa, sa = solve(fv, monkeypatch, dc, False, tol=1e-10)
+    monkeypatch.setenv("FVPCG_RESIDENT_MEET_MS", "0")
+    for _ in range(3):
+        xb, sb = solve(fv, monkeypatch, dc, True, tol=1e-10)
+        assert sa["iters"] == sb["iters"] and torch.equal(xa, xb)
+    monkeypatch.delenv("FVPCG_RESIDENT_MEET_MS")
+    xb, sb = solve(fv, monkeypatch, dc, True, tol=1e-10)
+    assert sa["iters"] == sb["iters"] and torch.equal(xa, xb)
+    dc.close()
+
+
+def test_resident_threads_and_streams(fv, monkeypatch):
+    """Solves from several threads, each on its own stream and matrix: one
+    team at a time holds the GPU, the others solve by launches; every result
+    is bitwise that of the solve alone."""
+    import threading
+
+    import torch
+
+    monkeypatch.setenv("FVPCG_RESIDENT", "1")
+    cases = [DevCase(fc.varcoef(s, seed=7)) for s in ((40, 36, 30), (33, 31, 29), (12, 11, 10), (64, 32, 32))]
+    alone = [fv.solve(dc.A, dc.b, tol=1e-10)[0].clone() for dc in cases]
+    torch.cuda.synchronize()
+    got, errors = {}, []
+
+    def work(i):
+        try:
+            st = torch.cuda.Stream()
+            st.wait_stream(torch.cuda.default_stream())
+            with torch.cuda.stream(st):
+                for rep in range(4):
+                    got[i, rep] = fv.solve(cases[i].A, cases[i].b, tol=1e-10)[0]
+            st.synchronize()
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    say("resident threads")
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(len(cases))]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join(60)
+    assert not errors and len(got) == 4 * len(cases)
+    torch.cuda.synchronize()
+    for (i, _), x in got.items():
+        assert torch.equal(x, alone[i])
+    for dc in cases:
+        dc.close()

@@ -11,23 +11,6 @@ namespace fvpcg {
 
 namespace {
 
-// A team on its own launch: member r is workgroup r.
-template <int RPT, int WT, typename CI, bool JAC, bool ONE>
-__global__ __launch_bounds__(kResBs) void k_res_pipe(ResSystem sys, ResTeam t, ResOut* out) {
-    __shared__ double lds[ResLds<RPT, ONE>::doubles];
-    __shared__ int s_ok;
-    if (threadIdx.x == 0) s_ok = 1;
-    t.rank = (int)blockIdx.x;
-    t.ok = &s_ok;
-    if (ONE) {
-        t.size = 1;
-        __syncthreads();
-    } else if (!team_meet(t)) {
-        return;
-    }
-    resident_pipe<RPT, WT, CI, JAC, ONE>(sys, t, lds, out);
-}
-
 // Sentinels into the slots, the rendezvous word, abort flag and result cleared.
 __global__ void k_res_reset(double* slots, int count, unsigned* meet, int* abort_flag, ResOut* out) {
     const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
@@ -37,41 +20,6 @@ __global__ void k_res_reset(double* slots, int count, unsigned* meet, int* abort
         *abort_flag = 0;
         out->ok = 0;
     }
-}
-
-using ResKernel = void (*)(ResSystem, ResTeam, ResOut*);
-
-template <int RPT, int WT, bool ONE>
-ResKernel pick_pipe(bool col16, bool jac) {
-    if (col16) return jac ? k_res_pipe<RPT, WT, int16_t, true, ONE> : k_res_pipe<RPT, WT, int16_t, false, ONE>;
-    return jac ? k_res_pipe<RPT, WT, int, true, ONE> : k_res_pipe<RPT, WT, int, false, ONE>;
-}
-
-template <int WT>
-ResKernel pick_pipe_rpt(const ResPlan& p, bool col16, bool jac) {
-    if (p.one) {
-        if (p.rpt == 1) return pick_pipe<1, WT, true>(col16, jac);
-        if (p.rpt == 2) return pick_pipe<2, WT, true>(col16, jac);
-        return pick_pipe<4, WT, true>(col16, jac);
-    }
-    switch (p.rpt) {
-        case 1: return pick_pipe<1, WT, false>(col16, jac);
-        case 2: return pick_pipe<2, WT, false>(col16, jac);
-        case 3: return pick_pipe<3, WT, false>(col16, jac);
-        case 4: return pick_pipe<4, WT, false>(col16, jac);
-        default: break;
-    }
-    if constexpr (WT <= 6) {
-        if (p.rpt == 6) return pick_pipe<6, WT, false>(col16, jac);
-        return pick_pipe<8, WT, false>(col16, jac);
-    }
-    return nullptr;
-}
-
-ResKernel pick_kernel(const ResPlan& p, int wt, bool col16, bool jac) {
-    if (wt == 4) return pick_pipe_rpt<4>(p, col16, jac);
-    if (wt == 6) return pick_pipe_rpt<6>(p, col16, jac);
-    return pick_pipe_rpt<8>(p, col16, jac);
 }
 
 constexpr int kMaxDevices = 64;
@@ -103,26 +51,31 @@ std::mutex* resident_teams(int device) {
 
 // Up to 2,048 cells one workgroup holds the system and exchanges through LDS
 // (no rendezvous, no device-wide reduction).  Above that a team takes the
-// tiles of the launch-per-iteration kernels, at most kResMaxTeam workgroups
-// of up to kResMaxRpt rows per thread: 1,048,576 cells, as many as registers
-// and LDS hold.  Unpacked int32 columns leave room for 6 rows per thread,
-// rows of more than 6 slots for 4, rows of more than 8 slots for none.
-ResPlan resident_plan(const fvpcg_mesh* m) {
+// tiles of the launch-per-iteration kernels, at most kMaxGrid workgroups of up
+// to 4,096 rows: 1,048,576 cells, as many as registers and LDS hold.  Unpacked
+// int32 columns leave room for 3,072 rows, rows of more than 6 slots for
+// 2,048, rows of more than 8 slots for none; the literal recurrences' two more
+// vectors leave room for 2,048.
+ResPlan resident_plan(const fvpcg_mesh* m, int method) {
     ResPlan p;
     const char* env = getenv("FVPCG_RESIDENT");
     if (env && env[0] == '0') return p;
     if (m->WT > 8 || m->n < 1 || m->device < 0 || m->device >= kMaxDevices) return p;
-    const int tiles = (m->n + kResBs - 1) / kResBs;
-    if (tiles <= 4) {
+    const int bs = method == FVPCG_CG ? kResBsCg : kResBsPipe;
+    const int tiles = (m->n + bs - 1) / bs;
+    p.method = method;
+    p.block = bs;
+    if (tiles * bs <= 2048) {
         p.one = true;
         p.size = 1;
         p.rpt = tiles <= 2 ? tiles : 4;
         return p;
     }
-    const int g = std::min(tiles, kResMaxTeam);  // geom_for's workgroups
+    const int g = std::min(tiles, kMaxGrid);  // geom_for's workgroups
     int rpt = (tiles + g - 1) / g;
     if (rpt == 5 || rpt == 7) ++rpt;
-    if (rpt > (m->WT > 6 ? 4 : m->col16 ? kResMaxRpt : 6) || g > device_info(m->device).cus) return p;
+    const int rows = m->WT > 6 || method == FVPCG_PIPECG_LITERAL ? 2048 : m->col16 ? 4096 : 3072;
+    if (rpt * bs > rows || g > device_info(m->device).cus) return p;
     p.size = g;
     p.rpt = rpt;
     return p;
@@ -151,8 +104,9 @@ int resident_solve(const fvpcg_matrix* A, const ResPlan& plan, const ResWork& w,
     ResTeam t{0, plan.size, w.slots, w.meet, w.abort_flag, nullptr,
               (unsigned long long)(info.ticks_per_ms * meet_ms), (unsigned long long)(info.ticks_per_ms * kResSpinMs),
               0};
-    ResKernel k = pick_kernel(plan, m->WT, m->col16 != nullptr, jac);
-    hipLaunchKernelGGL(k, dim3(plan.size), dim3(kResBs), 0, s, sys, t, out);
+    ResKernel k = plan.method == FVPCG_CG ? res_kernel_cg(plan, m->WT, m->col16 != nullptr, jac)
+                                          : res_kernel_pipe(plan, m->WT, m->col16 != nullptr, jac);
+    hipLaunchKernelGGL(k, dim3(plan.size), dim3(plan.block), 0, s, sys, t, out);
     FV_LAUNCHED();
     if (!w.pinned) FV_HIP(hipMemcpyAsync(&host, w.out, sizeof(ResOut), hipMemcpyDeviceToHost, s));
     FV_HIP(hipStreamSynchronize(s));

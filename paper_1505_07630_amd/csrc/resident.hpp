@@ -46,9 +46,9 @@
 
 namespace fvpcg {
 
-constexpr int kResBs = 512;           // threads per workgroup (kBsPipe: the same tiles)
-constexpr int kResMaxTeam = 256;      // members of a team at most
-constexpr int kResMaxRpt = 8;         // rows per thread at most
+constexpr int kResBsPipe = 512, kResBsCg = 1024;  // threads per workgroup: the launch path's tiles
+static_assert(kResBsPipe == kBsPipe && kResBsCg == kBsCg, "the same tiles, the same sums");
+constexpr int kResMaxTeam = kMaxGrid;  // members of a team at most
 constexpr int kResBufs = 4;           // slot buffers
 constexpr int kResSums = 3;           // sums per reduction
 constexpr unsigned long long kResSentinel = 0x7ff8f1c3a5965e17ull;
@@ -234,19 +234,19 @@ __device__ __forceinline__ void tile_sums(double (&v)[RPT][NV], double (&tot)[NV
 }
 
 // A thread's partial sums of one reduction, kept per row for tile_sums.
-template <int NV, int RPT, bool ONE>
+template <int BS, int NV, int RPT, bool ONE>
 struct Sums {
     static constexpr int kR = ONE ? RPT : 1;
     double a[kR][NV] = {};
     __device__ __forceinline__ void add(int k, int i, double v) { a[ONE ? k : 0][i] += v; }
     __device__ __forceinline__ bool finish(ResTeam& t, double (&tot)[NV]) {
         if constexpr (ONE) {
-            tile_sums<kResBs, NV, RPT>(a, tot);
+            tile_sums<BS, NV, RPT>(a, tot);
             return true;
         } else {
 #pragma unroll
             for (int i = 0; i < NV; ++i) tot[i] = a[0][i];
-            return team_sum<kResBs, NV>(tot, t);
+            return team_sum<BS, NV>(tot, t);
         }
     }
 };
@@ -284,7 +284,10 @@ struct RowCols<WT, int> {
         for (int i = 0; i < WT; ++i) v[i] = ld_once(p + (size_t)i * n + c);
     }
     __device__ __forceinline__ int at(int i, int) const { return v[i]; }
-    __device__ __forceinline__ void pin() {}
+    __device__ __forceinline__ void pin() {
+#pragma unroll
+        for (int i = 0; i < WT; ++i) asm volatile("" : "+v"(v[i]));
+    }
 };
 
 // RPT doubles per thread in registers, or in LDS.
@@ -307,21 +310,26 @@ struct Store<BS, RPT, true> {
 
 // The exchanged vectors: device memory with agent scope, or, for a system one
 // workgroup solves alone (ONE), LDS.
-template <int RPT, bool ONE>
+template <int BS, int RPT, bool ONE>
 struct Exchange;
-template <int RPT>
-struct Exchange<RPT, false> {
+template <int BS, int RPT>
+struct Exchange<BS, RPT, false> {
     double* v[2];
     __device__ __forceinline__ Exchange(const ResSystem& sys, double*) : v{sys.e0, sys.e1} {}
-    __device__ __forceinline__ void put(int buf, int c, double a) { st_agent((buf ? v[1] : v[0]) + c, a); }
-    __device__ __forceinline__ double get(int buf, int c) const { return ld_agent((buf ? v[1] : v[0]) + c); }
+    // 32-bit byte offsets (resident vectors are below 4 GiB): scalar base, one
+    // address register per access
+    __device__ __forceinline__ double* at(int buf, int c) const {
+        return (double*)((char*)(buf ? v[1] : v[0]) + (unsigned)c * 8u);
+    }
+    __device__ __forceinline__ void put(int buf, int c, double a) { st_agent(at(buf, c), a); }
+    __device__ __forceinline__ double get(int buf, int c) const { return ld_agent(at(buf, c)); }
 };
-template <int RPT>
-struct Exchange<RPT, true> {
+template <int BS, int RPT>
+struct Exchange<BS, RPT, true> {
     double* v;
     __device__ __forceinline__ Exchange(const ResSystem& sys, double* lds) : v(lds - sys.c0) {}
-    __device__ __forceinline__ void put(int buf, int c, double a) { v[buf * RPT * kResBs + c] = a; }
-    __device__ __forceinline__ double get(int buf, int c) const { return v[buf * RPT * kResBs + c]; }
+    __device__ __forceinline__ void put(int buf, int c, double a) { v[buf * RPT * BS + c] = a; }
+    __device__ __forceinline__ double get(int buf, int c) const { return v[buf * RPT * BS + c]; }
 };
 
 // acc + sum_i val[i][c] v(col_i), the values streamed once (the residuals at
@@ -336,7 +344,7 @@ __device__ __forceinline__ double res_gather(const RowCols<WT, CI>& col, const d
         g[i] = v(col.at(i, c));
     }
 #pragma unroll
-    for (int i = 0; i < WT; ++i) acc += a[i] * g[i];
+    for (int i = 0; i < WT; ++i) acc = fma(a[i], g[i], acc);
     return acc;
 }
 
@@ -389,29 +397,49 @@ __device__ __forceinline__ void res_pipe_step(ResScalars& y, double gamma, doubl
     _Pragma("unroll") for (int k = 0; k < RPT; ++k)                 \
         if (const int c = sys.c0 + (k * t.size + t.rank) * BS + (int)threadIdx.x; c < sys.c1)
 
-// LDS of a resident solve: four vectors with RPT > 4, or the two exchange
+// LDS of a resident solve: four vectors where registers cannot hold them
+// (above 4 rows per thread at 512 threads, 2 at 1024), or the two exchange
 // vectors of a workgroup on its own.
-template <int RPT, bool ONE>
+template <int BS, int RPT, bool ONE>
 struct ResLds {
-    static constexpr bool vectors = RPT > 4;
+    static constexpr bool vectors = BS * RPT > 2048;
     static_assert(!(vectors && ONE), "a single workgroup's rows stay in registers");
-    static constexpr int doubles = ONE ? 2 * RPT * kResBs : vectors ? 4 * RPT * kResBs : 1;
+    static constexpr int doubles = ONE ? 2 * RPT * BS : vectors ? 4 * RPT * BS : 1;
 };
 
-// Folded pipelined CG (see solve.hip): registers hold the iteration values,
-// the columns, d, r and the row's own w; z, s, p and x are in LDS with
-// RPT > 4.
-template <int RPT, int WT, typename CI, bool JAC, bool ONE>
+__device__ __forceinline__ void res_report(const ResTeam& t, ResOut* out, const ResScalars& y, double bnorm,
+                                           double true_rr, bool zero_b, unsigned long long t0, unsigned long long t_it0,
+                                           unsigned long long t_it1) {
+    if (t.rank != 0 || threadIdx.x != 0) return;
+    ResOut o;
+    o.bnorm = bnorm;
+    o.r0norm = y.r0norm;
+    o.rho = y.rho;
+    o.true_rr = true_rr;
+    o.it_ticks = t_it1 - t_it0;
+    o.ticks = (unsigned long long)wall_clock64() - t0;
+    o.iter = y.iter;
+    o.status = y.status;
+    o.zero_b = zero_b ? 1 : 0;
+    o.ok = 1;
+    *out = o;
+}
+
+// Pipelined CG, folded or with its literal recurrences (LIT; see solve.hip):
+// registers hold the iteration values, the columns, d, r and the row's own w;
+// z, s, p and x are in LDS with RPT > 4.
+template <int RPT, int WT, typename CI, bool JAC, bool LIT, bool ONE>
 __device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, double* lds, ResOut* out) {
-    constexpr int BS = kResBs;
-    constexpr bool L = ResLds<RPT, ONE>::vectors;
+    constexpr int BS = kResBsPipe;
+    constexpr bool L = ResLds<BS, RPT, ONE>::vectors;
     const unsigned long long t_begin = (unsigned long long)wall_clock64();
-    Exchange<RPT, ONE> e(sys, lds);
+    Exchange<BS, RPT, ONE> e(sys, lds);
     RowCols<WT, CI> col[RPT];
     double d[RPT], r[RPT], w[RPT];
+    [[maybe_unused]] double u[LIT ? RPT : 1], q[LIT ? RPT : 1];
     Store<BS, RPT, L> z(lds), s(lds + RPT * BS), p(lds + 2 * RPT * BS), x(lds + 3 * RPT * BS);
     // r = b - A x through buffer 1, (b, b)
-    Sums<1, RPT, ONE> sb;
+    Sums<BS, 1, RPT, ONE> sb;
     RES_ROWS(k, c) {
         col[k].load(sys.col, sys.n, c);
         const double bc = sys.b[c], dc = sys.d[c], xc = sys.x[c];
@@ -422,6 +450,10 @@ __device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, 
         z.set(k, 0.0);
         s.set(k, 0.0);
         p.set(k, 0.0);
+        if constexpr (LIT) {
+            u[k] = JAC ? rc / dc : rc;
+            q[k] = 0.0;
+        }
         e.put(1, c, rc);
         sb.add(k, 0, bc * bc);
     }
@@ -437,7 +469,7 @@ __device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, 
         y.status = FVPCG_OK;
     } else if (ok) {
         // w = A M^-1 r
-        Sums<3, RPT, ONE> sa;
+        Sums<BS, 3, RPT, ONE> sa;
         RES_ROWS(k, c) {
             double g[WT];
 #pragma unroll
@@ -448,7 +480,7 @@ __device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, 
             const double rc = r[k], dc = d[k];
             double wc = JAC ? rc : dc * rc;
 #pragma unroll
-            for (int i = 0; i < WT; ++i) wc += val[k][i] * g[i];
+            for (int i = 0; i < WT; ++i) wc = fma(val[k][i], g[i], wc);
             w[k] = wc;
             e.put(0, c, wc);
             const double uc = JAC ? rc / dc : rc;
@@ -464,7 +496,7 @@ __device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, 
     for (int it = 0; ok && !y.done; ++it) {
         const int in = it & 1;
         const double alpha = y.alpha, beta = y.beta;
-        Sums<3, RPT, ONE> sa;
+        Sums<BS, 3, RPT, ONE> sa;
         RES_ROWS(k, c) {
             double g[WT];
             if (RPT > 3) col[k].pin();
@@ -473,13 +505,20 @@ __device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, 
             const double wc = w[k], dc = d[k];
             double nv = JAC ? wc : dc * wc;
 #pragma unroll
-            for (int i = 0; i < WT; ++i) nv += val[k][i] * g[i];
+            for (int i = 0; i < WT; ++i) nv = fma(val[k][i], g[i], nv);
             const double zc = nv + beta * z.get(k);
             const double wn = wc - alpha * zc;
             e.put(in ^ 1, c, wn);
             const double sc = wc + beta * s.get(k);
             double rc = r[k];
-            double uc = JAC ? rc / dc : rc;
+            double uc;
+            if constexpr (LIT) {
+                const double mc = JAC ? wc / dc : wc;
+                q[k] = mc + beta * q[k];
+                uc = u[k];
+            } else {
+                uc = JAC ? rc / dc : rc;
+            }
             const double pc = uc + beta * p.get(k);
             p.set(k, pc);
             x.set(k, x.get(k) + alpha * pc);
@@ -488,7 +527,12 @@ __device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, 
             s.set(k, sc);
             r[k] = rc;
             w[k] = wn;
-            uc = JAC ? rc / dc : rc;
+            if constexpr (LIT) {
+                uc -= alpha * q[k];
+                u[k] = uc;
+            } else {
+                uc = JAC ? rc / dc : rc;
+            }
             sa.add(k, 0, rc * uc);
             sa.add(k, 1, wn * uc);
             sa.add(k, 2, rc * rc);
@@ -507,27 +551,167 @@ __device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, 
         e.put(0, c, x.get(k));
     }
     double rr[1];
-    if (!Sums<1, RPT, ONE>().finish(t, rr)) return;
-    Sums<1, RPT, ONE> sr;
+    if (!Sums<BS, 1, RPT, ONE>().finish(t, rr)) return;
+    Sums<BS, 1, RPT, ONE> sr;
     RES_ROWS(k, c) {
         const double rc = sys.b[c] - res_gather<WT, CI>(col[k], sys.val, sys.n, c, [&](int j) { return e.get(0, j); }, d[k] * x.get(k));
         sr.add(k, 0, rc * rc);
     }
     if (!sr.finish(t, rr)) return;
-    if (t.rank == 0 && threadIdx.x == 0) {
-        ResOut o;
-        o.bnorm = bnorm;
-        o.r0norm = y.r0norm;
-        o.rho = y.rho;
-        o.true_rr = rr[0];
-        o.it_ticks = t_it1 - t_it0;
-        o.ticks = (unsigned long long)wall_clock64() - t_begin;
-        o.iter = y.iter;
-        o.status = y.status;
-        o.zero_b = zero_b ? 1 : 0;
-        o.ok = 1;
-        *out = o;
+    res_report(t, out, y, bnorm, rr[0], zero_b, t_begin, t_it0, t_it1);
+}
+
+// Standard preconditioned CG.  Its two reductions per iteration are the only
+// synchronisations: p = z + beta p is formed by the row that owns an entry and
+// again, from the same z and p with the same rounding, by every row that
+// gathers it, so no third one is needed between the new direction and the
+// product.  Registers hold the values, the columns and q; x, r, p and d are
+// in LDS with RPT > 2.  e0 carries z, e1 the previous p; both are stored after
+// the first reduction (everybody has gathered the old ones) and read after the
+// second.
+template <int RPT, int WT, typename CI, bool JAC, bool ONE>
+__device__ __forceinline__ void resident_cg(const ResSystem& sys, ResTeam& t, double* lds, ResOut* out) {
+    constexpr int BS = kResBsCg;
+    constexpr bool L = ResLds<BS, RPT, ONE>::vectors;
+    const unsigned long long t_begin = (unsigned long long)wall_clock64();
+    Exchange<BS, RPT, ONE> e(sys, lds);
+    RowCols<WT, CI> col[RPT];
+    double val[RPT][WT], q[RPT];
+    Store<BS, RPT, L> x(lds), r(lds + RPT * BS), p(lds + 2 * RPT * BS), d(lds + 3 * RPT * BS);
+    // r = b - A x, z = M^-1 r, p = z
+    Sums<BS, 3, RPT, ONE> s0;
+    RES_ROWS(k, c) {
+        col[k].load(sys.col, sys.n, c);
+        const double bc = sys.b[c], dc = sys.d[c], xc = sys.x[c];
+        double g[WT];
+#pragma unroll
+        for (int i = 0; i < WT; ++i) {
+            val[k][i] = ld_once(sys.val + (size_t)i * sys.n + c);
+            g[i] = sys.x[col[k].at(i, c)];
+        }
+        double ax = dc * xc;
+#pragma unroll
+        for (int i = 0; i < WT; ++i) ax = fma(val[k][i], g[i], ax);
+        const double rc = bc - ax;
+        const double zc = JAC ? rc / dc : rc;
+        x.set(k, xc);
+        r.set(k, rc);
+        p.set(k, zc);
+        d.set(k, dc);
+        e.put(0, c, zc);
+        e.put(1, c, 0.0);
+        s0.add(k, 0, rc * zc);
+        s0.add(k, 1, rc * rc);
+        s0.add(k, 2, bc * bc);
     }
+    double a0[3];
+    bool ok = s0.finish(t, a0);
+    ResScalars y;
+    const double bnorm = sqrt(a0[2]);
+    const bool zero_b = a0[2] == 0.0;
+    if (zero_b) {
+        y.done = true;
+        y.status = FVPCG_OK;
+    } else {
+        y.tol_abs = sys.tol * bnorm;
+        y.gamma = a0[0];
+        y.rho = a0[1];
+        y.r0norm = sqrt(a0[1]);
+        if (y.r0norm <= y.tol_abs) {
+            y.done = true;
+            y.status = FVPCG_OK;
+        } else if (sys.maxit <= 0) {
+            y.done = true;
+        }
+    }
+    const unsigned long long t_it0 = (unsigned long long)wall_clock64();
+    for (int it = 0; ok && !y.done; ++it) {
+        const double beta = y.beta;
+        const bool first = it == 0;
+        // q = A p; delta = (p, q)
+        Sums<BS, 1, RPT, ONE> s1;
+        RES_ROWS(k, c) {
+            double gz[WT], gp[WT];
+            if (RPT > 1) col[k].pin();
+#pragma unroll
+            for (int i = 0; i < WT; ++i) {
+                const int j = col[k].at(i, c);
+                gz[i] = e.get(0, j);
+                gp[i] = first ? 0.0 : e.get(1, j);
+            }
+            const double pc = p.get(k);
+            double qc = d.get(k) * pc;
+#pragma unroll
+            for (int i = 0; i < WT; ++i) qc = fma(val[k][i], first ? gz[i] : fma(beta, gp[i], gz[i]), qc);
+            q[k] = qc;
+            s1.add(k, 0, pc * qc);
+        }
+        double a1[1];
+        ok = s1.finish(t, a1);
+        if (!ok) break;
+        const double delta = a1[0];
+        if (!(delta > 0.0) || !isfinite(delta) || !isfinite(y.gamma)) {
+            y.done = true;
+            y.status = FVPCG_BREAKDOWN;
+            break;
+        }
+        const double alpha = y.gamma / delta;
+        // x += alpha p, r -= alpha q, z = M^-1 r
+        Sums<BS, 2, RPT, ONE> s2;
+        RES_ROWS(k, c) {
+            const double pc = p.get(k), dc = d.get(k);
+            const double rc = r.get(k) - alpha * q[k];
+            r.set(k, rc);
+            const double zc = JAC ? rc / dc : rc;
+            e.put(0, c, zc);
+            e.put(1, c, pc);
+            x.set(k, x.get(k) + alpha * pc);
+            s2.add(k, 0, rc * zc);
+            s2.add(k, 1, rc * rc);
+        }
+        double a2[2];
+        ok = s2.finish(t, a2);
+        y.iter += 1;
+        y.rho = a2[1];
+        if (sqrt(a2[1]) <= y.tol_abs) {
+            y.done = true;
+            y.status = FVPCG_OK;
+        } else if (y.iter >= sys.maxit) {
+            y.done = true;
+        } else {
+            y.beta = a2[0] / y.gamma;
+            y.gamma = a2[0];
+            RES_ROWS(k, c) {
+                const double rc = r.get(k);
+                const double zc = JAC ? rc / d.get(k) : rc;
+                p.set(k, fma(y.beta, p.get(k), zc));
+            }
+        }
+    }
+    const unsigned long long t_it1 = (unsigned long long)wall_clock64();
+    if (!ok) return;
+    // x, also through buffer 0 (see resident_pipe; a breakdown ends on the
+    // first reduction, after which nobody reads it either), and ||b - A x||^2
+    RES_ROWS(k, c) {
+        if (zero_b) x.set(k, 0.0);
+        sys.x[c] = x.get(k);
+        e.put(0, c, x.get(k));
+    }
+    double rr[1];
+    if (!Sums<BS, 1, RPT, ONE>().finish(t, rr)) return;
+    Sums<BS, 1, RPT, ONE> sr;
+    RES_ROWS(k, c) {
+        double g[WT];
+#pragma unroll
+        for (int i = 0; i < WT; ++i) g[i] = e.get(0, col[k].at(i, c));
+        double ax = d.get(k) * x.get(k);
+#pragma unroll
+        for (int i = 0; i < WT; ++i) ax = fma(val[k][i], g[i], ax);
+        const double rc = sys.b[c] - ax;
+        sr.add(k, 0, rc * rc);
+    }
+    if (!sr.finish(t, rr)) return;
+    res_report(t, out, y, bnorm, rr[0], zero_b, t_begin, t_it0, t_it1);
 }
 
 }  // namespace fvpcg

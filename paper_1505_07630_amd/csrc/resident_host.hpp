@@ -8,6 +8,9 @@
 namespace fvpcg {
 
 struct ResOut;
+struct ResSystem;
+struct ResTeam;
+using ResKernel = void (*)(ResSystem, ResTeam, ResOut*);
 
 // Rendezvous limit: past it (other work holds the GPU's CUs) the launch-per-
 // iteration path runs instead (FVPCG_RESIDENT_MEET_MS sets another;
@@ -18,6 +21,8 @@ constexpr double kResMeetMs = 20.0, kResSpinMs = 5000.0;
 struct ResPlan {
     int rpt = 0;   // rows per thread; 0: not resident
     int size = 0;  // workgroups
+    int block = 0; // threads per workgroup
+    int method = 0;
     bool one = false;
 };
 
@@ -35,7 +40,9 @@ struct ResWork {
 // two such launches side by side could each hold half of the CUs and wait.
 std::mutex* resident_teams(int device);
 
-ResPlan resident_plan(const fvpcg_mesh* m);
+ResPlan resident_plan(const fvpcg_mesh* m, int method);
+ResKernel res_kernel_pipe(const ResPlan& p, int wt, bool col16, bool jac);
+ResKernel res_kernel_cg(const ResPlan& p, int wt, bool col16, bool jac);
 
 // *done = false with FVPCG_OK: not solved here, solve by launches (x is still
 // a valid starting vector); a negative code is an error.

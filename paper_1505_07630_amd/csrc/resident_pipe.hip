@@ -1,0 +1,61 @@
+// The resident pipelined-CG kernels (resident.hpp) and their choice.
+#include "resident.hpp"
+#include "resident_host.hpp"
+
+namespace fvpcg {
+
+namespace {
+
+// A team on its own launch: member r is workgroup r.
+template <int RPT, int WT, typename CI, bool JAC, bool LIT, bool ONE>
+__global__ __launch_bounds__(kResBsPipe) void k_res_pipe(ResSystem sys, ResTeam t, ResOut* out) {
+    __shared__ double lds[ResLds<kResBsPipe, RPT, ONE>::doubles];
+    __shared__ int s_ok;
+    if (threadIdx.x == 0) s_ok = 1;
+    t.rank = (int)blockIdx.x;
+    t.ok = &s_ok;
+    if (ONE) {
+        t.size = 1;
+        __syncthreads();
+    } else if (!team_meet(t)) {
+        return;
+    }
+    resident_pipe<RPT, WT, CI, JAC, LIT, ONE>(sys, t, lds, out);
+}
+
+template <int RPT, int WT, bool ONE>
+ResKernel pick_form(bool col16, bool jac, bool lit) {
+    if constexpr (RPT <= 4)
+        if (lit) return col16 ? k_res_pipe<RPT, WT, int16_t, true, true, ONE> : k_res_pipe<RPT, WT, int, true, true, ONE>;
+    if constexpr (RPT <= 6)
+        if (!col16) return jac ? k_res_pipe<RPT, WT, int, true, false, ONE> : k_res_pipe<RPT, WT, int, false, false, ONE>;
+    return jac ? k_res_pipe<RPT, WT, int16_t, true, false, ONE> : k_res_pipe<RPT, WT, int16_t, false, false, ONE>;
+}
+
+template <int WT>
+ResKernel pick_rpt(const ResPlan& p, bool col16, bool jac, bool lit) {
+    if (p.one) {
+        if (p.rpt == 1) return pick_form<1, WT, true>(col16, jac, lit);
+        if (p.rpt == 2) return pick_form<2, WT, true>(col16, jac, lit);
+        return pick_form<4, WT, true>(col16, jac, lit);
+    }
+    if (p.rpt == 1) return pick_form<1, WT, false>(col16, jac, lit);
+    if (p.rpt == 2) return pick_form<2, WT, false>(col16, jac, lit);
+    if (p.rpt == 3) return pick_form<3, WT, false>(col16, jac, lit);
+    if constexpr (WT <= 6) {
+        if (p.rpt == 6) return pick_form<6, WT, false>(col16, jac, lit);
+        if (p.rpt == 8) return pick_form<8, WT, false>(col16, jac, lit);
+    }
+    return pick_form<4, WT, false>(col16, jac, lit);
+}
+
+}  // namespace
+
+ResKernel res_kernel_pipe(const ResPlan& p, int wt, bool col16, bool jac) {
+    const bool lit = p.method == FVPCG_PIPECG_LITERAL;
+    if (wt == 4) return pick_rpt<4>(p, col16, jac, lit);
+    if (wt == 6) return pick_rpt<6>(p, col16, jac, lit);
+    return pick_rpt<8>(p, col16, jac, lit);
+}
+
+}  // namespace fvpcg

@@ -19,7 +19,9 @@ __device__ __forceinline__ int slot_col_keep(const int* p, size_t o, int) { retu
 __device__ __forceinline__ int slot_col_keep(const int16_t* p, size_t o, int c) { return c + (int)p[o]; }
 
 // acc + sum_k val[k][c] * v[col[k][c]] over the WT slots of row c (KEEP:
-// columns loaded with slot_col_keep).
+// columns loaded with slot_col_keep).  The multiply-adds are explicit: with
+// acc = d x the compiler may otherwise contract either product of the first
+// sum, and kernels that must agree bit for bit could differ.
 template <typename T, int WT, typename CI, bool KEEP = false>
 __device__ __forceinline__ T row_gather(const CI* __restrict__ col, const T* __restrict__ val, int n, int c,
                                         const T* __restrict__ v, T acc) {
@@ -32,7 +34,7 @@ __device__ __forceinline__ T row_gather(const CI* __restrict__ col, const T* __r
         a[k] = ld_once(val + o);
     }
 #pragma unroll
-    for (int k = 0; k < WT; ++k) acc += a[k] * v[j[k]];
+    for (int k = 0; k < WT; ++k) acc = fma(a[k], v[j[k]], acc);
     return acc;
 }
 

@@ -896,14 +896,12 @@ int solve(const fvpcg_matrix* A, const double* b, double* x, double tol, int max
     int rc;
     if ((rc = work_init(w, A->mesh->n))) return rc;
     if (method == FVPCG_PIPECG_LITERAL && precond != FVPCG_PRECOND_JACOBI) method = FVPCG_PIPECG;
-    if (method == FVPCG_PIPECG) {
-        const ResPlan plan = resident_plan(A->mesh);
-        if (plan.rpt) {
-            bool done = false;
-            if ((rc = work_need_resident(w))) return rc;
-            rc = solve_resident(A, plan, w, b, x, tol, maxit, precond, s, stats, &done);
-            if (rc < 0 || done) return rc;
-        }
+    const ResPlan plan = resident_plan(A->mesh, method);
+    if (plan.rpt) {
+        bool done = false;
+        if ((rc = work_need_resident(w))) return rc;
+        rc = solve_resident(A, plan, w, b, x, tol, maxit, precond, s, stats, &done);
+        if (rc < 0 || done) return rc;
     }
     if (method == FVPCG_CG) {
         if ((rc = work_need_cg(w))) return rc;
@@ -1001,8 +999,13 @@ int solve_core(const fvpcg_matrix* A, Work& w, const double* b, double* x, doubl
     }
     std::chrono::steady_clock::time_point t_it1;
     if ((rc = clk.mark(w.t_it1, t_it1, s))) return rc;
-    FV_LAYOUT(m, hipLaunchKernelGGL((k_true_residual<kBsMisc, W_, CI_>), dim3(gm.grid), dim3(kBsMisc), 0, s, cols_, A->val,
-                                           A->d, n, gm, b, x, st, part));
+    if (method == FVPCG_CG) {  // the method's own tiles: the resident solve's sum
+        FV_LAYOUT(m, hipLaunchKernelGGL((k_true_residual<kBsCg, W_, CI_>), dim3(gc.grid), dim3(kBsCg), 0, s, cols_, A->val,
+                                        A->d, n, gc, b, x, st, part));
+    } else {
+        FV_LAYOUT(m, hipLaunchKernelGGL((k_true_residual<kBsPipe, W_, CI_>), dim3(gp.grid), dim3(kBsPipe), 0, s, cols_,
+                                        A->val, A->d, n, gp, b, x, st, part));
+    }
     FV_LAUNCHED();
     if (w.t_end) FV_HIP(hipEventRecord(w.t_end, s));
     if ((rc = state_read(w, 0, &h, s))) return rc;
@@ -1093,13 +1096,11 @@ int solve_noalloc(const fvpcg_matrix* A, const double* b, double* x, double tol,
     w.res_out = reinterpret_cast<ResOut*>(w.res_slots + kNoAllocSlots);
     w.res_meet = reinterpret_cast<unsigned*>(w.res_slots + kNoAllocSlots + kNoAllocOutDoubles);
     if (method == FVPCG_PIPECG_LITERAL && precond != FVPCG_PRECOND_JACOBI) method = FVPCG_PIPECG;
-    if (method == FVPCG_PIPECG) {
-        const ResPlan plan = resident_plan(A->mesh);
-        if (plan.rpt) {
-            bool done = false;
-            rc = solve_resident(A, plan, w, b, x, tol, maxit, precond, s, stats, &done);
-            if (rc < 0 || done) return rc;
-        }
+    const ResPlan plan = resident_plan(A->mesh, method);
+    if (plan.rpt) {
+        bool done = false;
+        rc = solve_resident(A, plan, w, b, x, tol, maxit, precond, s, stats, &done);
+        if (rc < 0 || done) return rc;
     }
     return solve_core(A, w, b, x, tol, maxit, method, precond, s, stats);
 }

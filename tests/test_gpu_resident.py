@@ -2,7 +2,8 @@
 the launch-per-iteration path and the oracle, at the edges of their tiles:
 one row, one workgroup on its own (up to 2,048 cells), teams of 5 to 256
 workgroups with 1 to 8 rows per thread, full and ragged last tiles, rows of
-4, 6 and 8 slots, int16 and int32 columns.
+4, 6 and 8 slots, int16 and int32 columns; pipelined CG (folded and literal)
+and standard CG.
 
 Resident solves form their sums in the launch-per-iteration kernels' order
 from the same expressions, so the two paths agree bit for bit.  Against the
@@ -82,6 +83,9 @@ CASES = {
 }
 
 
+FORMS = [("pipecg", "jacobi"), ("pipecg", "none"), ("pipecg_literal", "jacobi"), ("cg", "jacobi"), ("cg", "none")]
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_resident_equals_launches(fv, monkeypatch, name):
     make, opts = CASES[name]
@@ -92,19 +96,20 @@ def test_resident_equals_launches(fv, monkeypatch, name):
     assert case.n <= MOST
     dc = DevCase(case)
     x0 = to_dev(np.random.default_rng(1).uniform(-1, 1, case.n))
-    for precond in ("jacobi", "none"):
+    for method, precond in FORMS:
         for kw in (dict(tol=0.0, maxit=40), dict(tol=1e-9, maxit=60, x0=x0)):
-            say("resident", name, precond, kw.get("tol"))
-            xa, sa = solve(fv, monkeypatch, dc, False, precond=precond, **kw)
-            xb, sb = solve(fv, monkeypatch, dc, True, precond=precond, **kw)
+            say("resident", name, method, precond, kw.get("tol"))
+            xa, sa = solve(fv, monkeypatch, dc, False, method=method, precond=precond, **kw)
+            xb, sb = solve(fv, monkeypatch, dc, True, method=method, precond=precond, **kw)
             for k in ("iters", "status", "b_norm", "r0_norm", "rel_res", "true_rel_res"):
                 assert sa[k] == sb[k], k
             assert np.array_equal(xa.cpu().numpy(), xb.cpu().numpy())
     # the oracle at equal count, 25 iterations (fewer if it converges)
-    xb, sb = solve(fv, monkeypatch, dc, True, tol=0.0, maxit=25)
-    if sb["status"] == 1:
-        xo, _ = oracle.pipecg(oracle.system(case), case.b, tol=0.0, maxit=sb["iters"], folded=True)
-        assert rel(xb.cpu().numpy(), xo) <= 1e-10
+    for method, run in (("pipecg", oracle.pipecg), ("cg", oracle.cg)):
+        xb, sb = solve(fv, monkeypatch, dc, True, method=method, tol=0.0, maxit=25)
+        if sb["status"] == 1:
+            xo, _ = run(oracle.system(case), case.b, tol=0.0, maxit=sb["iters"])
+            assert rel(xb.cpu().numpy(), xo) <= 1e-10
     dc.close()
 
 
@@ -116,21 +121,24 @@ def test_resident_edges(fv, monkeypatch, shape):
     say("resident edges", shape)
     case = fc.varcoef(shape, seed=5)
     dc = DevCase(case)
-    monkeypatch.setenv("FVPCG_RESIDENT", "1")
-    x, st = fv.solve(dc.A, torch.zeros_like(dc.b), x=torch.ones_like(dc.b))
-    assert st["status"] == 0 and st["iters"] == 0 and torch.count_nonzero(x).item() == 0 and st["true_rel_res"] == 0.0
-    xs, _ = fv.solve(dc.A, dc.b, tol=1e-12)
-    x, st = fv.solve(dc.A, dc.b, x=xs.clone(), tol=1e-8)
-    assert st["status"] == 0 and st["iters"] == 0 and torch.equal(x, xs)
-    x, st = fv.solve(dc.A, dc.b, x=xs.clone(), tol=1e-20, maxit=0)
-    assert st["status"] == 1 and st["iters"] == 0 and torch.equal(x, xs)
-    bad = dc.b.clone()
-    bad[case.n // 2] = float("nan")
-    for res in ("0", "1"):
-        monkeypatch.setenv("FVPCG_RESIDENT", res)
-        with pytest.raises(fv.FVPCGError) as e:
-            fv.solve(dc.A, bad)
-        assert e.value.code == fv.BREAKDOWN
+    for method in ("pipecg", "pipecg_literal", "cg"):
+        monkeypatch.setenv("FVPCG_RESIDENT", "1")
+        kw = dict(method=method)
+        x, st = fv.solve(dc.A, torch.zeros_like(dc.b), x=torch.ones_like(dc.b), **kw)
+        assert st["status"] == 0 and st["iters"] == 0 and st["true_rel_res"] == 0.0
+        assert torch.count_nonzero(x).item() == 0
+        xs, _ = fv.solve(dc.A, dc.b, tol=1e-12, **kw)
+        x, st = fv.solve(dc.A, dc.b, x=xs.clone(), tol=1e-8, **kw)
+        assert st["status"] == 0 and st["iters"] == 0 and torch.equal(x, xs)
+        x, st = fv.solve(dc.A, dc.b, x=xs.clone(), tol=1e-20, maxit=0, **kw)
+        assert st["status"] == 1 and st["iters"] == 0 and torch.equal(x, xs)
+        bad = dc.b.clone()
+        bad[case.n // 2] = float("nan")
+        for res in ("0", "1"):
+            monkeypatch.setenv("FVPCG_RESIDENT", res)
+            with pytest.raises(fv.FVPCGError) as e:
+                fv.solve(dc.A, bad, **kw)
+            assert e.value.code == fv.BREAKDOWN
     dc.close()
 
 

@@ -26,6 +26,8 @@
 #include <vector>
 
 #include "handles.hpp"
+#include "resident.hpp"
+#include "resident_host.hpp"
 
 namespace fvpcg {
 int mesh_create(int32_t n, int32_t F, const int32_t* owner, const int32_t* nb, hipStream_t s, fvpcg_mesh** out);
@@ -69,6 +71,14 @@ struct BatchArgs {
     unsigned long long spin_ticks;  // team barrier timeout, wall-clock ticks
 };
 
+// A resident launch's plan; block 0: none made, rpt 0: not resident.
+struct ResBatchPlan {
+    int block = 0, rpt = 0, grid = 0;
+    int members = 0;  // of all teams
+    std::vector<int4> tasks;
+    std::vector<int> list;
+};
+
 struct Tuning {
     int block = 256;
     int per_cu = 4;
@@ -105,6 +115,14 @@ struct fvpcg_batch {
     int* h_order = nullptr;    // pinned staging
     int* h_abort = nullptr;    // pinned
     unsigned long long spin_ticks = 0;
+    // resident solves (resident.hpp): the plan's work lists and buffers
+    fvpcg::ResBatchPlan res;
+    int4* d_rtasks = nullptr;
+    int* d_rlist = nullptr;
+    double* d_rslots = nullptr;
+    unsigned* d_rmeet = nullptr;  // rendezvous word, abort flag
+    fvpcg::ResOut* d_rout = nullptr;
+    fvpcg::ResOut* h_rout = nullptr;  // pinned
     // cached graph
     hipGraphExec_t gexec = nullptr;
     std::string gkey;
@@ -144,9 +162,6 @@ __device__ __forceinline__ void block_allreduce(double (&v)[NV]) {
     __syncthreads();
 }
 
-__device__ __forceinline__ int slot_col(const int* p, size_t o, int) { return p[o]; }
-__device__ __forceinline__ int slot_col(const int16_t* p, size_t o, int c) { return c + (int)p[o]; }
-
 template <int WT, typename CI>
 __device__ __forceinline__ double gather(const void* colv, const double* __restrict__ val, int n, int c,
                                          const double* __restrict__ v, double acc) {
@@ -156,7 +171,7 @@ __device__ __forceinline__ double gather(const void* colv, const double* __restr
 #pragma unroll
     for (int k = 0; k < WT; ++k) {
         const size_t o = (size_t)k * n + c;
-        j[k] = slot_col(col, o, c);
+        j[k] = slot_col_keep(col, o, c);
         a[k] = val[o];
     }
 #pragma unroll
@@ -862,6 +877,20 @@ int check_abort(fvpcg_batch* bt, hipStream_t s) {
     return FVPCG_OK;
 }
 
+void batch_stats(const BatchStat& h, float ms, fvpcg_stats* o) {
+    if (!o) return;
+    o->iters = h.iters;
+    o->outer_iters = 0;
+    o->status = h.status;
+    o->reserved = 0;
+    o->b_norm = h.bnorm;
+    o->r0_norm = h.r0norm;
+    o->rel_res = h.bnorm > 0 ? sqrt(h.rho) / h.bnorm : 0.0;
+    o->true_rel_res = h.bnorm > 0 ? sqrt(h.true_rr) / h.bnorm : 0.0;
+    o->device_ms = ms;
+    o->iter_ms = ms;
+}
+
 // Pick block size, workgroups per CU and teams on/off by timing each
 // candidate on this batch (a copy of x0, the caller's tolerance), fastest
 // wins.
@@ -929,8 +958,166 @@ int autotune(fvpcg_batch* bt, const double* b, const double* x0, double tol, int
     return FVPCG_OK;
 }
 
+// ------------------------------------------------------------ resident solves
+
+// The resident launch for tiles of bs rows: every system gets a team with
+// room for its rows, rpt tiles per member, and the teams are placed on the
+// launch's workgroups (one per CU) in one global order: longest solve first
+// (iterations grow like the mesh edge), each on the workgroups that are free
+// first.  rpt is the smallest with which all teams run side by side, else the
+// largest.
+// Resident wins where a team's rows fill its threads.  Below an average of
+// 2,048 cells per system a whole CU per system is more than it can use and
+// the queue (several workgroups per CU) is the better form.
+void resident_batch_plan(const fvpcg_batch* bt, int bs, ResBatchPlan& p) {
+    p = ResBatchPlan();
+    p.block = bs;
+    int cus = 0;
+    double ticks = 0;
+    resident_device(bt->mesh->device, &cus, &ticks);
+    const bool col16 = bt->mesh->col16 != nullptr;
+    const int most = bt->mesh->WT > 8 ? 0 : (bt->mesh->WT > 6 || !col16 ? 2048 : 4096) / bs;
+    if (!most || ticks <= 0 || cus < 1 || bt->ncells >= (1 << 29)) return;
+    if ((double)bt->ncells < 2048.0 * bt->nsys) return;
+    const int grid = std::min(cus, kResMaxTeam);
+    std::vector<int> tiles(bt->nsys);
+    int largest = 0;
+    for (int i = 0; i < bt->nsys; ++i) {
+        tiles[i] = (bt->cell_off[i + 1] - bt->cell_off[i] + bs - 1) / bs;
+        largest = std::max(largest, tiles[i]);
+    }
+    if (largest > grid * most) return;
+    auto members = [&](int rpt) {
+        long long m = 0;
+        for (int t : tiles) m += std::max(1, (t + rpt - 1) / rpt);
+        return m;
+    };
+    int rpt = most;
+    while (rpt > 1024 / bs && members(rpt / 2) <= grid && largest <= grid * (rpt / 2)) rpt /= 2;
+    std::vector<int> order(bt->nsys);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return tiles[x] > tiles[y]; });
+    std::vector<std::pair<double, int>> free_at(grid);
+    for (int b = 0; b < grid; ++b) free_at[b] = {0.0, b};
+    std::vector<std::vector<int4>> lists(grid);
+    int offset = 0;
+    for (int i : order) {
+        const int g = std::max(1, (tiles[i] + rpt - 1) / rpt);
+        std::partial_sort(free_at.begin(), free_at.begin() + g, free_at.end());
+        const double end = free_at[g - 1].first + std::cbrt((double)(bt->cell_off[i + 1] - bt->cell_off[i]) + 1.0);
+        for (int r = 0; r < g; ++r) {
+            lists[free_at[r].second].push_back(make_int4(i, r, g, offset));
+            free_at[r].first = end;
+        }
+        offset += g;
+    }
+    p.list.push_back(0);
+    for (auto& l : lists) {
+        p.tasks.insert(p.tasks.end(), l.begin(), l.end());
+        p.list.push_back((int)p.tasks.size());
+    }
+    p.rpt = rpt;
+    p.grid = grid;
+    p.members = offset;
+}
+
+// *done = false with FVPCG_OK: not solved here (see resident_solve).
+int solve_batched_resident(fvpcg_batch* bt, const double* b, double* x, double tol, int maxit, bool jac, int method,
+                           hipStream_t s, fvpcg_stats* stats, bool* done, int* overall) {
+    *done = false;
+    const char* env = getenv("FVPCG_RESIDENT");
+    if ((env && env[0] == '0') || teams_mode() != 'a') return FVPCG_OK;
+    const int bs = method == 0 ? kResBsCg : kResBsPipe;
+    int rc;
+    if (bt->res.block != bs) {
+        resident_batch_plan(bt, bs, bt->res);
+        dev_free(bt->d_rtasks);
+        dev_free(bt->d_rlist);
+        dev_free(bt->d_rslots);
+        if (!bt->res.rpt) return FVPCG_OK;
+        ResBatchPlan& p = bt->res;
+        if ((rc = dev_alloc(&bt->d_rtasks, p.tasks.size(), "resident tasks")) ||
+            (rc = dev_alloc(&bt->d_rlist, p.list.size(), "resident task lists")) ||
+            (rc = dev_alloc(&bt->d_rslots, res_slots(p.members), "resident slots")) ||
+            (!bt->d_rmeet && (rc = dev_alloc(&bt->d_rmeet, 2, "resident rendezvous"))) ||
+            (!bt->d_rout && (rc = dev_alloc(&bt->d_rout, (size_t)bt->nsys, "resident results")))) {
+            p.block = 0;
+            return rc;
+        }
+        if (!bt->h_rout &&
+            hipHostMalloc((void**)&bt->h_rout, sizeof(ResOut) * bt->nsys, hipHostMallocDefault) != hipSuccess) {
+            bt->h_rout = nullptr;
+            p.block = 0;
+            (void)hipGetLastError();
+            return set_error(FVPCG_OUT_OF_MEMORY, "pinned allocation failed");
+        }
+        // the vectors stay until the next plan: copied synchronously
+        if (hipMemcpy(bt->d_rtasks, p.tasks.data(), sizeof(int4) * p.tasks.size(), hipMemcpyHostToDevice) != hipSuccess ||
+            hipMemcpy(bt->d_rlist, p.list.data(), sizeof(int) * p.list.size(), hipMemcpyHostToDevice) != hipSuccess) {
+            p.block = 0;
+            return hip_fail(hipGetLastError(), "resident task copy", __FILE__, __LINE__);
+        }
+    }
+    const ResBatchPlan& p = bt->res;
+    if (!p.rpt) return FVPCG_OK;
+    const fvpcg_mesh* m = bt->mesh;
+    std::mutex* mu = resident_teams(m->device);
+    if (!mu) return FVPCG_OK;
+    std::unique_lock<std::mutex> lock(*mu, std::try_to_lock);
+    if (!lock.owns_lock()) return FVPCG_OK;  // another team has the GPU
+    int cus = 0;
+    double ticks = 0;
+    resident_device(m->device, &cus, &ticks);
+    int* abort_flag = reinterpret_cast<int*>(bt->d_rmeet + 1);
+    FV_HIP(hipEventRecord(bt->e0, s));
+    if ((rc = resident_reset(bt->d_rslots, res_slots(p.members), bt->d_rmeet, abort_flag, bt->d_rout, bt->nsys, s)))
+        return rc;
+    ResSystem sys{m->col16 ? (const void*)m->col16 : (const void*)m->col,
+                  bt->mat->val,
+                  jac ? bt->mat->val_cs : bt->mat->val,
+                  bt->mat->d,
+                  b,
+                  x,
+                  bt->w0,
+                  bt->w1,
+                  (size_t)bt->ncells,
+                  0,
+                  0,
+                  tol,
+                  maxit};
+    ResTeam t{0, p.grid, bt->d_rslots, bt->d_rmeet, abort_flag, nullptr, (unsigned long long)(ticks * resident_meet_ms()),
+              (unsigned long long)(ticks * kResSpinMs), 0};
+    ResBatch rb{bt->d_cell_off, bt->d_rtasks, bt->d_rlist, bt->d_rout};
+    ResBatchKernel k = method == 0 ? res_batch_cg(p.rpt, m->WT, m->col16 != nullptr, jac)
+                                   : res_batch_pipe(p.rpt, m->WT, m->col16 != nullptr, jac);
+    hipLaunchKernelGGL(k, dim3(p.grid), dim3(p.block), 0, s, sys, t, rb);
+    FV_LAUNCHED();
+    FV_HIP(hipEventRecord(bt->e1, s));
+    FV_HIP(hipMemcpyAsync(bt->h_rout, bt->d_rout, sizeof(ResOut) * bt->nsys, hipMemcpyDeviceToHost, s));
+    FV_HIP(hipStreamSynchronize(s));
+    for (int i = 0; i < bt->nsys; ++i)
+        if (!bt->h_rout[i].ok) return FVPCG_OK;  // x holds a valid start for the other path
+    *done = true;
+    float ms = 0;
+    (void)hipEventElapsedTime(&ms, bt->e0, bt->e1);
+    *overall = FVPCG_OK;
+    for (int i = 0; i < bt->nsys; ++i) {
+        const ResOut& h = bt->h_rout[i];
+        const BatchStat st{h.iter, h.status, h.bnorm, h.r0norm, h.rho, h.true_rr};
+        batch_stats(st, ms, stats ? &stats[i] : nullptr);
+        if (*overall == FVPCG_OK && h.status != FVPCG_OK) *overall = h.status;
+    }
+    return FVPCG_OK;
+}
+
 void batch_free(fvpcg_batch* bt) {
     if (!bt) return;
+    dev_free(bt->d_rtasks);
+    dev_free(bt->d_rlist);
+    dev_free(bt->d_rslots);
+    dev_free(bt->d_rmeet);
+    dev_free(bt->d_rout);
+    if (bt->h_rout) (void)hipHostFree(bt->h_rout);
     if (bt->gexec) (void)hipGraphExecDestroy(bt->gexec);
     if (bt->mat) matrix_destroy(bt->mat);
     if (bt->mesh) mesh_destroy(bt->mesh);
@@ -1068,6 +1255,13 @@ int solve_batched(const fvpcg_batch* cbt, const double* b, double* x, double tol
     }
     const int m = method == FVPCG_CG ? 0 : 1;
     int rc;
+    bool done = false;
+    int overall = FVPCG_OK;
+    if ((rc = solve_batched_resident(bt, b, x, tol, maxit, jac, m, s, stats, &done, &overall))) return rc;
+    if (done) {
+        if (overall == FVPCG_BREAKDOWN) set_error(overall, "breakdown in at least one system");
+        return overall;
+    }
     Tuning t;
     if ((rc = autotune(bt, b, x, tol, maxit, jac, m, s, &t))) return rc;
     int grid = 0, nq = 0;
@@ -1105,22 +1299,9 @@ int solve_batched(const fvpcg_batch* cbt, const double* b, double* x, double tol
     if ((rc = check_abort(bt, s))) return rc;
     float ms = 0;
     (void)hipEventElapsedTime(&ms, bt->e0, bt->e1);
-    int overall = FVPCG_OK;
     for (int i = 0; i < bt->nsys; ++i) {
         const BatchStat& h = bt->h_stats[i];
-        if (stats) {
-            fvpcg_stats& o = stats[i];
-            o.iters = h.iters;
-            o.outer_iters = 0;
-            o.status = h.status;
-            o.reserved = 0;
-            o.b_norm = h.bnorm;
-            o.r0_norm = h.r0norm;
-            o.rel_res = h.bnorm > 0 ? sqrt(h.rho) / h.bnorm : 0.0;
-            o.true_rel_res = h.bnorm > 0 ? sqrt(h.true_rr) / h.bnorm : 0.0;
-            o.device_ms = ms;
-            o.iter_ms = ms;
-        }
+        batch_stats(h, ms, stats ? &stats[i] : nullptr);
         if (overall == FVPCG_OK && h.status != FVPCG_OK) overall = h.status;
     }
     if (overall == FVPCG_BREAKDOWN) set_error(overall, "breakdown in at least one system");

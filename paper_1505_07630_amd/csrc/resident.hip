@@ -11,14 +11,14 @@ namespace fvpcg {
 
 namespace {
 
-// Sentinels into the slots, the rendezvous word, abort flag and result cleared.
-__global__ void k_res_reset(double* slots, int count, unsigned* meet, int* abort_flag, ResOut* out) {
-    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i < count) slots[i] = __longlong_as_double((long long)kResSentinel);
-    if (i == 0) {
+// Sentinels into the slots, the rendezvous word, abort flag and results cleared.
+__global__ void k_res_reset(double* slots, size_t count, unsigned* meet, int* abort_flag, ResOut* out, int nout) {
+    const size_t first = (size_t)blockIdx.x * blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = first; i < count; i += step) slots[i] = __longlong_as_double((long long)kResSentinel);
+    for (size_t i = first; i < (size_t)nout; i += step) out[i].ok = 0;
+    if (first == 0) {
         *meet = 0u;
         *abort_flag = 0;
-        out->ok = 0;
     }
 }
 
@@ -47,6 +47,30 @@ const DeviceInfo& device_info(int dev) {
 
 std::mutex* resident_teams(int device) {
     return device >= 0 && device < kMaxDevices ? &g_dev[device].teams : nullptr;
+}
+
+void resident_device(int device, int* cus, double* ticks_per_ms) {
+    if (device < 0 || device >= kMaxDevices) {
+        *cus = 0;
+        *ticks_per_ms = 0;
+        return;
+    }
+    const DeviceInfo& d = device_info(device);
+    *cus = d.cus;
+    *ticks_per_ms = d.ticks_per_ms;
+}
+
+double resident_meet_ms() {
+    const char* env = getenv("FVPCG_RESIDENT_MEET_MS");
+    return env && *env ? std::max(0.0, atof(env)) : kResMeetMs;
+}
+
+int resident_reset(double* slots, size_t count, unsigned* meet, int* abort_flag, ResOut* out, int nout, hipStream_t s) {
+    const size_t work = std::max(count, (size_t)nout);
+    hipLaunchKernelGGL(k_res_reset, dim3((unsigned)std::min<size_t>((work + 255) / 256, 256)), dim3(256), 0, s, slots, count,
+                       meet, abort_flag, out, nout);
+    FV_LAUNCHED();
+    return FVPCG_OK;
 }
 
 // Up to 2,048 cells one workgroup holds the system and exchanges through LDS
@@ -94,15 +118,10 @@ int resident_solve(const fvpcg_matrix* A, const ResPlan& plan, const ResWork& w,
     ResOut host{};
     ResOut* out = w.pinned ? w.pinned : w.out;
     if (w.pinned) w.pinned->ok = 0;
-    if (!plan.one) {
-        const int count = (int)res_slots(plan.size);
-        hipLaunchKernelGGL(k_res_reset, dim3((count + 255) / 256), dim3(256), 0, s, w.slots, count, w.meet, w.abort_flag,
-                           out);
-    }
-    const char* env = getenv("FVPCG_RESIDENT_MEET_MS");
-    const double meet_ms = env && *env ? std::max(0.0, atof(env)) : kResMeetMs;
+    int rc;
+    if (!plan.one && (rc = resident_reset(w.slots, res_slots(plan.size), w.meet, w.abort_flag, out, 1, s))) return rc;
     ResTeam t{0, plan.size, w.slots, w.meet, w.abort_flag, nullptr,
-              (unsigned long long)(info.ticks_per_ms * meet_ms), (unsigned long long)(info.ticks_per_ms * kResSpinMs),
+              (unsigned long long)(info.ticks_per_ms * resident_meet_ms()), (unsigned long long)(info.ticks_per_ms * kResSpinMs),
               0};
     ResKernel k = plan.method == FVPCG_CG ? res_kernel_cg(plan, m->WT, m->col16 != nullptr, jac)
                                           : res_kernel_pipe(plan, m->WT, m->col16 != nullptr, jac);

@@ -80,6 +80,13 @@ struct ResSystem {
     int maxit;
 };
 
+struct ResBatch {
+    const int* cell_off;
+    const int4* tasks;  // (system, rank, team size, slot offset in members)
+    const int* list;    // [grid + 1] each workgroup's range of tasks
+    ResOut* out;        // [systems]
+};
+
 struct ResTeam {
     int rank, size;
     double* slots;            // [kResBufs][kResSums][size], sentinels at the start

@@ -10,6 +10,8 @@ namespace fvpcg {
 struct ResOut;
 struct ResSystem;
 struct ResTeam;
+struct ResBatch;
+using ResBatchKernel = void (*)(ResSystem, ResTeam, ResBatch);
 using ResKernel = void (*)(ResSystem, ResTeam, ResOut*);
 
 // Rendezvous limit: past it (other work holds the GPU's CUs) the launch-per-
@@ -43,6 +45,14 @@ std::mutex* resident_teams(int device);
 ResPlan resident_plan(const fvpcg_mesh* m, int method);
 ResKernel res_kernel_pipe(const ResPlan& p, int wt, bool col16, bool jac);
 ResKernel res_kernel_cg(const ResPlan& p, int wt, bool col16, bool jac);
+ResBatchKernel res_batch_pipe(int rpt, int wt, bool col16, bool jac);
+ResBatchKernel res_batch_cg(int rpt, int wt, bool col16, bool jac);
+double resident_meet_ms();
+// CUs, and wall-clock ticks per ms (0: unknown) of a device.
+void resident_device(int device, int* cus, double* ticks_per_ms);
+// Enqueues the reset of `count` slot doubles, the rendezvous word, the abort
+// flag and nout results.
+int resident_reset(double* slots, size_t count, unsigned* meet, int* abort_flag, ResOut* out, int nout, hipStream_t s);
 
 // *done = false with FVPCG_OK: not solved here, solve by launches (x is still
 // a valid starting vector); a negative code is an error.

@@ -23,6 +23,33 @@ __global__ __launch_bounds__(kResBsPipe) void k_res_pipe(ResSystem sys, ResTeam 
     resident_pipe<RPT, WT, CI, JAC, LIT, ONE>(sys, t, lds, out);
 }
 
+// Many systems in one launch: workgroup b works through its list of (system,
+// rank, team size, slot offset), all lists in one global order, so the first
+// unfinished system always has its whole team.
+template <int RPT, int WT, typename CI, bool JAC>
+__global__ __launch_bounds__(kResBsPipe) void k_res_batch_pipe(ResSystem sys, ResTeam t, ResBatch bt) {
+    __shared__ double lds[ResLds<kResBsPipe, RPT, false>::doubles];
+    __shared__ int s_ok;
+    if (threadIdx.x == 0) s_ok = 1;
+    t.rank = (int)blockIdx.x;
+    t.ok = &s_ok;
+    if (!team_meet(t)) return;
+    const int end = bt.list[blockIdx.x + 1];
+    for (int i = bt.list[blockIdx.x]; i < end; ++i) {
+        const int4 task = bt.tasks[i];
+        ResTeam tm = t;
+        tm.rank = task.y;
+        tm.size = task.z;
+        tm.slots = t.slots + (size_t)kResBufs * kResSums * task.w;
+        tm.k = 0;
+        sys.c0 = bt.cell_off[task.x];
+        sys.c1 = bt.cell_off[task.x + 1];
+        resident_pipe<RPT, WT, CI, JAC, false, false>(sys, tm, lds, bt.out + task.x);
+        __syncthreads();
+        if (!s_ok) return;
+    }
+}
+
 template <int RPT, int WT, bool ONE>
 ResKernel pick_form(bool col16, bool jac, bool lit) {
     if constexpr (RPT <= 4)
@@ -56,6 +83,28 @@ ResKernel res_kernel_pipe(const ResPlan& p, int wt, bool col16, bool jac) {
     if (wt == 4) return pick_rpt<4>(p, col16, jac, lit);
     if (wt == 6) return pick_rpt<6>(p, col16, jac, lit);
     return pick_rpt<8>(p, col16, jac, lit);
+}
+
+namespace {
+
+template <int WT>
+ResBatchKernel pick_batch(int rpt, bool col16, bool jac) {
+    if constexpr (WT <= 6)
+        if (rpt == 8) return jac ? k_res_batch_pipe<8, WT, int16_t, true> : k_res_batch_pipe<8, WT, int16_t, false>;
+    if (rpt == 4) {
+        if (col16) return jac ? k_res_batch_pipe<4, WT, int16_t, true> : k_res_batch_pipe<4, WT, int16_t, false>;
+        return jac ? k_res_batch_pipe<4, WT, int, true> : k_res_batch_pipe<4, WT, int, false>;
+    }
+    if (col16) return jac ? k_res_batch_pipe<2, WT, int16_t, true> : k_res_batch_pipe<2, WT, int16_t, false>;
+    return jac ? k_res_batch_pipe<2, WT, int, true> : k_res_batch_pipe<2, WT, int, false>;
+}
+
+}  // namespace
+
+ResBatchKernel res_batch_pipe(int rpt, int wt, bool col16, bool jac) {
+    if (wt == 4) return pick_batch<4>(rpt, col16, jac);
+    if (wt == 6) return pick_batch<6>(rpt, col16, jac);
+    return pick_batch<8>(rpt, col16, jac);
 }
 
 }  // namespace fvpcg

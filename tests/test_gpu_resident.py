@@ -198,3 +198,50 @@ def test_resident_threads_and_streams(fv, monkeypatch):
         assert torch.equal(x, alone[i])
     for dc in cases:
         dc.close()
+
+
+# ------------------------------------------------------------------ batches
+
+BATCHES = {
+    # members per launch: all side by side at 2, 4 and 8 (standard CG 1, 2, 4) tiles each, then queued teams
+    "side-by-side": lambda: [fc.varcoef(s, seed=1, permute=False) for s in ((20, 20, 20), (33, 20, 17), (5, 1, 1))],
+    "queued": lambda: [fc.varcoef((e, e + 1, e + 3), seed=e, permute=False) for e in (60, 48, 47, 40, 31, 16, 16, 9)]
+    + [stencil(683, 3, CROSS, 5), stencil(1, 1, LINE, 1)],
+    "wide-rows": lambda: [stencil(50, 50, STAR, 6), stencil(130, 110, STAR, 7)],
+}
+
+
+@pytest.mark.parametrize("name", list(BATCHES))
+@pytest.mark.parametrize("col32", [False, True])
+def test_resident_batch(fv, monkeypatch, name, col32):
+    """Every system of a resident batch against the oracle at its iteration
+    count (the strict bar), bitwise reproducible, and the same statuses and
+    counts within 2 as the queue's; a team without time to come together
+    leaves the batch to the queue."""
+    import torch
+
+    say("resident batch", name, col32)
+    monkeypatch.setenv("FVPCG_TUNE", "0")
+    monkeypatch.setenv("FVPCG_COL16", "0" if col32 else "1")
+    cases = BATCHES[name]()
+    bt = fc.concat(cases)
+    B = fv.Batch(bt.cell_off, bt.face_off, to_dev(bt.owner, torch.int32), to_dev(bt.neighbour, torch.int32),
+                 to_dev(bt.diag), to_dev(bt.upper))
+    b = to_dev(bt.b)
+    for method, run in (("pipecg", oracle.pipecg), ("cg", oracle.cg)):
+        got = {}
+        for mode in ("queue", "resident", "again", "no-time"):
+            say("resident batch", name, method, mode)
+            monkeypatch.setenv("FVPCG_RESIDENT", "0" if mode == "queue" else "1")
+            monkeypatch.setenv("FVPCG_RESIDENT_MEET_MS", "0" if mode == "no-time" else "20")
+            x, st, code = fv.solve_batched(B, b, x=torch.zeros_like(b), tol=1e-9, maxit=20000, method=method)
+            assert code == 0 and all(s["status"] == 0 for s in st)
+            got[mode] = x.cpu().numpy(), [s["iters"] for s in st]
+        assert np.array_equal(got["resident"][0], got["again"][0])
+        x, its = got["resident"]
+        for s, case in enumerate(cases):
+            xs = x[bt.cell_off[s]:bt.cell_off[s + 1]]
+            assert abs(its[s] - got["queue"][1][s]) <= 2 and abs(its[s] - got["no-time"][1][s]) <= 2
+            xo, _ = run(oracle.system(case), case.b, tol=0.0, maxit=its[s])
+            assert rel(xs, xo) <= 1e-10, s
+    B.close()

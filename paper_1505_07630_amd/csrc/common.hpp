@@ -123,11 +123,15 @@ int hip_fail(hipError_t e, const char* what, const char* file, int line);
         if (fv_e_ != hipSuccess) return ::fvpcg::hip_fail(fv_e_, "kernel launch", __FILE__, __LINE__); \
     } while (0)
 
+// Device memory, kept for reuse when freed (memory.hip).
+hipError_t pool_alloc(void** out, size_t bytes);
+void pool_free(void* p);
+
 template <typename T>
 int dev_alloc(T** p, size_t count, const char* what) {
     *p = nullptr;
     if (count == 0) count = 1;
-    hipError_t e = hipMalloc((void**)p, count * sizeof(T));
+    hipError_t e = pool_alloc((void**)p, count * sizeof(T));
     if (e != hipSuccess) {
         *p = nullptr;
         (void)hipGetLastError();
@@ -139,7 +143,7 @@ int dev_alloc(T** p, size_t count, const char* what) {
 
 template <typename T>
 void dev_free(T*& p) {
-    if (p) (void)hipFree((void*)p);
+    if (p) pool_free((void*)p);
     p = nullptr;
 }
 

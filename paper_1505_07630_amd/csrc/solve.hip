@@ -724,15 +724,13 @@ int work_need_resident(Work& w) {
 
 void work_free(Work& w) {
     double* dv[] = {w.r, w.p, w.q, w.z, w.s, w.w[0], w.w[1], w.u, w.qq, w.lam, w.partials};
-    for (double* p : dv)
-        if (p) (void)hipFree(p);
+    for (double* p : dv) dev_free(p);
     float* fv[] = {w.r32, w.r32b, w.w32[0], w.w32[1], w.z32, w.s32, w.p32, w.c32};
-    for (float* p : fv)
-        if (p) (void)hipFree(p);
-    if (w.res_slots) (void)hipFree(w.res_slots);
-    if (w.res_meet) (void)hipFree(w.res_meet);
+    for (float* p : fv) dev_free(p);
+    dev_free(w.res_slots);
+    dev_free(w.res_meet);
     if (w.res_pinned) (void)hipHostFree(w.res_pinned);
-    if (w.st) (void)hipFree(w.st);
+    dev_free(w.st);
     if (w.hst) (void)hipHostFree(w.hst);
     for (auto ev : w.ev)
         if (ev) (void)hipEventDestroy(ev);

@@ -62,7 +62,7 @@ struct AmgLevel {
     double* r_val = nullptr;
     long long p_nnz = 0;  // stored entries of P (and of R)
     double *b = nullptr, *x = nullptr, *r = nullptr, *y = nullptr;  // work
-    int ga = 1, gp = 1, gr = 1;  // lanes per row for A, P, R (1, 16 or 64)
+    bool wa = false, wp = false, wr = false;  // A, P, R: a wavefront per row (else by runs of entries)
     int* agg = nullptr;          // device: aggregate of every row (levels with a coarser one)
     // kept for the numeric refresh (levels with a coarser one)
     int *ap_ptr = nullptr, *ap_col = nullptr;  // A P
@@ -72,11 +72,13 @@ struct AmgLevel {
     ProdPlan plan_p, plan_ap, plan_c;  // kernels of P = S P_t, A P and A_c = R (A P)
 };
 
-// lanes per row from the operator's mean row length (measured at 7M cells:
-// 44-entry rows run fastest with 16 lanes, hundreds with 64)
-inline int lanes_for(size_t nnz, int rows) {
-    const double avg = (double)nnz / (double)(rows > 1 ? rows : 1);
-    return avg <= 6.0 ? 1 : (avg <= 48.0 ? 16 : 64);
+// How the cycle takes a CSR operator.  By contiguous runs of entries where
+// rows hold at most 48; longer rows too where the operator is large (2.4M
+// entries in rows of 157: 9.8 us against 12.0 by wavefronts).  A small
+// operator with long rows has few runs and more wavefronts (30k entries: 4.5
+// us against 6.1).
+inline bool wave_rows(size_t nnz, int rows) {
+    return (double)nnz > 48.0 * (double)(rows > 1 ? rows : 1) && nnz < ((size_t)1 << 21);
 }
 
 // The hierarchy into h (freed by the caller on failure).

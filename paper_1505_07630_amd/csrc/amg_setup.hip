@@ -1475,7 +1475,7 @@ int amg_build(fvpcg_amg* h, const fvpcg_matrix* A, double theta, int max_levels,
         if (hbad || !(rho > 0.0) || !std::isfinite(rho))
             return set_error(FVPCG_BREAKDOWN, "AMG: level %d has a diagonal entry that is not finite and positive", l);
         v.omega = 4.0 / (3.0 * rho);
-        v.ga = lanes_for((size_t)cur.nnz, cur.n);
+        v.wa = wave_rows((size_t)cur.nnz, cur.n);
         if (l > 0) {
             if ((rc = dev_alloc(&v.a_val_cs, (size_t)std::max(cur.nnz, 1LL), "AMG level scaled values"))) return rc;
             hipLaunchKernelGGL(k_lvl_colscale, dim3(grid1d(cur.nnz)), dim3(kSetupBs), 0, s, cur.col, cur.val, d,
@@ -1555,8 +1555,8 @@ int amg_build(fvpcg_amg* h, const fvpcg_matrix* A, double theta, int max_levels,
         FV_LAUNCHED();
         v.nc = na;
         v.p_nnz = P.nnz;
-        v.gp = lanes_for((size_t)P.nnz, P.n);
-        v.gr = lanes_for((size_t)R.nnz, R.n);
+        v.wp = wave_rows((size_t)P.nnz, P.n);
+        v.wr = wave_rows((size_t)R.nnz, R.n);
         AmgLevel& next = h->lev[l + 1];
         next.a_ptr = Ac.ptr;
         next.a_col = Ac.col;

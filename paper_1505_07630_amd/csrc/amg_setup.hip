@@ -13,13 +13,12 @@
 //                   that maximum becomes a root, one that sees a root drops
 //                   out; the host repeats until none is undecided;
 //   k_agg_round1/2  the aggregates (roots numbered by an exclusive scan);
-//   P = S P_t, R = P^T, A P, A_c = R (A P): sparse products by a row-wise
-//                   k-way merge (one thread per output row keeps a binary heap
-//                   of the heads of the rows of the right operand that the
-//                   left row selects, keyed by (column, list index); equal
-//                   columns are summed in list order, so every entry is summed
-//                   in the left row's column order), R by counting, scatter
-//                   and a per-row heapsort;
+//   P = S P_t, R = P^T, A P, A_c = R (A P): sparse products by rows, a hash
+//                   table of the row's columns in LDS (very wide rows: LDS
+//                   column tiles, or a k-way merge with a heap keyed by
+//                   (column, list index)); every entry is summed in the left
+//                   row's column order.  R by counting, scatter and a sort of
+//                   each row;
 //   last level      dense, inverted by Gauss-Jordan elimination in one
 //                   workgroup (SPD: no pivoting; a non-positive pivot is a
 //                   breakdown).
@@ -458,10 +457,8 @@ __global__ __launch_bounds__(kSetupBs) void k_gemm_bound(const int* __restrict__
     block_atomic_max<int>(maxlen, m);
 }
 
-// binary min-heap of keys (column, list index): 64-bit keys (column << 32 |
-// index), or 32-bit ones (column << 6 | index) when there are at most 64
-// lists and under 2^26 columns; both order the heads alike.
-template <typename K>
+// binary min-heap of keys (column << 32 | list index)
+using K = unsigned long long;
 __device__ __forceinline__ void heap_up(K* H, int i) {
     const K v = H[i];
     while (i > 0) {
@@ -474,7 +471,6 @@ __device__ __forceinline__ void heap_up(K* H, int i) {
     H[i] = v;
 }
 
-template <typename K>
 __device__ __forceinline__ void heap_down(K* H, int h, int i) {
     const K v = H[i];
     for (;;) {
@@ -495,19 +491,6 @@ __device__ __forceinline__ void heap_down(K* H, int h, int i) {
     H[i] = v;
 }
 
-template <typename K>
-struct HeapKey;
-template <>
-struct HeapKey<unsigned long long> {
-    static constexpr int kShift = 32;
-};
-template <>
-struct HeapKey<unsigned int> {
-    static constexpr int kShift = 6;  // up to 64 lists
-};
-constexpr int kKey32Lists = 64;
-constexpr int kKey32Cols = 1 << 26;
-
 #pragma clang fp contract(off)
 // Row i of C = X Y by a k-way merge of the rows Y(k, :) for k in X(i, :):
 // the heap H holds (column << 32 | list index) of each list's head, P each
@@ -515,13 +498,12 @@ constexpr int kKey32Cols = 1 << 26;
 // and, for equal columns, the lists in X's column order, in which their
 // products are summed (each product rounded, then added).  Output: the
 // row's distinct columns and sums at off[i] in (tcol, tval), and its count.
-template <typename K>
 __device__ __forceinline__ void merge_row(long long i, const int* __restrict__ xptr, const int* __restrict__ xcol,
                                           const double* __restrict__ xval, const int* __restrict__ yptr,
                                           const int* __restrict__ ycol, const double* __restrict__ yval,
                                           const long long* __restrict__ off, K* H, int* P,
                                           int* __restrict__ tcol, double* __restrict__ tval, int* __restrict__ cnt) {
-    constexpr int kS = HeapKey<K>::kShift;
+    constexpr int kS = 32;
     constexpr K kMask = ((K)1 << kS) - 1;
     const int base = xptr[i], L = xptr[i + 1] - base;
     int h = 0;
@@ -574,70 +556,6 @@ __device__ __forceinline__ void merge_row(long long i, const int* __restrict__ x
 }
 #pragma clang fp contract(on)
 
-// Row i of C = X Y for rows of X with at most SM entries (level 0's
-// products): the heads of the lists Y(k_t, :) stay in registers; each step
-// takes the smallest head column and adds, in X's column order t, the
-// products of the lists whose head it is (each product rounded, then added,
-// the first one taken as it is), then advances those lists.  Every column
-// thus receives its products in the heap merge's order, so the sums are
-// bitwise the merge's; the loads of the advanced heads are independent of
-// each other, where the heap merge waits on one load per product.
-constexpr int kShortLists = 8;
-#pragma clang fp contract(off)
-template <int SM>
-__global__ __launch_bounds__(kSetupBs) void k_gemm_short(const int* __restrict__ xptr, const int* __restrict__ xcol,
-                                                        const double* __restrict__ xval, const int* __restrict__ yptr,
-                                                        const int* __restrict__ ycol, const double* __restrict__ yval,
-                                                        int rows, const long long* __restrict__ off,
-                                                        int* __restrict__ tcol, double* __restrict__ tval,
-                                                        int* __restrict__ cnt) {
-    constexpr int kNone = 0x7fffffff;
-    FV_GRID_LOOP(i, rows) {
-        const int base = xptr[i], L = xptr[i + 1] - base;
-        int head[SM], pos[SM], end[SM];
-        double xv[SM];
-#pragma unroll
-        for (int t = 0; t < SM; ++t) {
-            head[t] = kNone;
-            pos[t] = 0;
-            end[t] = 0;
-            xv[t] = 0.0;
-            if (t < L) {
-                const int k = xcol[base + t];
-                xv[t] = xval[base + t];
-                pos[t] = yptr[k];
-                end[t] = yptr[k + 1];
-                if (pos[t] < end[t]) head[t] = ycol[pos[t]];
-            }
-        }
-        const long long o = off[i];
-        int out = 0;
-        for (;;) {
-            int c = kNone;
-#pragma unroll
-            for (int t = 0; t < SM; ++t) c = head[t] < c ? head[t] : c;
-            if (c == kNone) break;
-            double acc = 0.0;
-            bool first = true;
-#pragma unroll
-            for (int t = 0; t < SM; ++t) {
-                if (head[t] == c) {
-                    const double v = xv[t] * yval[pos[t]];
-                    acc = first ? v : acc + v;
-                    first = false;
-                    ++pos[t];
-                    head[t] = pos[t] < end[t] ? ycol[pos[t]] : kNone;
-                }
-            }
-            tcol[o + out] = c;
-            tval[o + out] = acc;
-            ++out;
-        }
-        cnt[i] = out;
-    }
-}
-#pragma clang fp contract(on)
-
 // One row per thread, heap and positions in device memory indexed like X
 // (rows whose list count exceeds the LDS budget).
 __global__ __launch_bounds__(kSetupBs) void k_gemm_merge(const int* __restrict__ xptr, const int* __restrict__ xcol,
@@ -649,7 +567,7 @@ __global__ __launch_bounds__(kSetupBs) void k_gemm_merge(const int* __restrict__
                                                         int* __restrict__ cnt) {
     FV_GRID_LOOP(i, rows) {
         const int base = xptr[i];
-        merge_row<unsigned long long>(i, xptr, xcol, xval, yptr, ycol, yval, off, heap + base, pos + base, tcol,
+        merge_row(i, xptr, xcol, xval, yptr, ycol, yval, off, heap + base, pos + base, tcol,
                                       tval, cnt);
     }
 }
@@ -660,8 +578,6 @@ __global__ __launch_bounds__(kSetupBs) void k_gemm_merge(const int* __restrict__
 // latency, which decides the coarse levels' long rows.
 constexpr int kLdsBs = 64;
 constexpr int kLdsBytes = 65536;
-constexpr long long kDenseEntries = 1LL << 27;  // rows x columns of a product accumulated densely (1.2 GB)
-template <typename K>
 __global__ __launch_bounds__(kLdsBs) void k_gemm_merge_lds(const int* __restrict__ xptr, const int* __restrict__ xcol,
                                                           const double* __restrict__ xval,
                                                           const int* __restrict__ yptr, const int* __restrict__ ycol,
@@ -669,78 +585,14 @@ __global__ __launch_bounds__(kLdsBs) void k_gemm_merge_lds(const int* __restrict
                                                           int lcap, const long long* __restrict__ off,
                                                           int* __restrict__ tcol, double* __restrict__ tval,
                                                           int* __restrict__ cnt) {
-    extern __shared__ unsigned long long lds_heap_raw[];
-    K* lds_heap = reinterpret_cast<K*>(lds_heap_raw);
+    extern __shared__ K lds_heap[];
     const int t = (int)threadIdx.x;
     const long long i = (long long)blockIdx.x * per_wg + t;
     if (t >= per_wg || i >= rows) return;
     K* H = lds_heap + (size_t)t * lcap;
     int* P = reinterpret_cast<int*>(lds_heap + (size_t)per_wg * lcap) + (size_t)t * lcap;
-    merge_row<K>(i, xptr, xcol, xval, yptr, ycol, yval, off, H, P, tcol, tval, cnt);
+    merge_row(i, xptr, xcol, xval, yptr, ycol, yval, off, H, P, tcol, tval, cnt);
 }
-
-// Row i of C = X Y with one wavefront per row and a dense accumulator of
-// the row in device memory (acc/touched: nc entries per row), for products
-// whose column count nc is small: lane k owns the columns [k w, (k+1) w)
-// and walks the rows Y(k_t, :) for t in X's column order, adding the
-// products that fall in its columns (found by binary search in each sorted
-// Y row).  Every column therefore receives its products in the merge's
-// order, so the sums are bitwise the merge's; the touched columns are
-// written in ascending order at off[i].
-#pragma clang fp contract(off)
-__global__ __launch_bounds__(64) void k_gemm_dense(const int* __restrict__ xptr, const int* __restrict__ xcol,
-                                                  const double* __restrict__ xval, const int* __restrict__ yptr,
-                                                  const int* __restrict__ ycol, const double* __restrict__ yval,
-                                                  int rows, int nc, const long long* __restrict__ off,
-                                                  double* __restrict__ acc_all, uint8_t* __restrict__ touched_all,
-                                                  int* __restrict__ tcol, double* __restrict__ tval,
-                                                  int* __restrict__ cnt) {
-    const int lane = (int)threadIdx.x;
-    const int w = (nc + 63) / 64;
-    const int c0 = min(lane * w, nc), c1 = min(c0 + w, nc);
-    for (long long i = blockIdx.x; i < rows; i += gridDim.x) {
-        double* acc = acc_all + (size_t)i * nc;
-        uint8_t* touched = touched_all + (size_t)i * nc;
-        for (int c = c0; c < c1; ++c) {
-            acc[c] = 0.0;
-            touched[c] = 0;
-        }
-        const int base = xptr[i], L = xptr[i + 1] - base;
-        for (int t = 0; t < L; ++t) {
-            const int k = xcol[base + t];
-            const double xv = xval[base + t];
-            int lo = yptr[k], hi = yptr[k + 1];
-            while (lo < hi) {  // first entry with column >= c0
-                const int mid = (lo + hi) >> 1;
-                if (ycol[mid] < c0) lo = mid + 1;
-                else hi = mid;
-            }
-            for (int p = lo, e = yptr[k + 1]; p < e; ++p) {
-                const int c = ycol[p];
-                if (c >= c1) break;
-                acc[c] += xv * yval[p];
-                touched[c] = 1;
-            }
-        }
-        int mine = 0;
-        for (int c = c0; c < c1; ++c) mine += touched[c];
-        // exclusive prefix of the lanes' counts (lanes own ascending ranges)
-        int incl = mine;
-        for (int d = 1; d < 64; d <<= 1) {
-            const int v = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += v;
-        }
-        long long o = off[i] + (incl - mine);
-        for (int c = c0; c < c1; ++c)
-            if (touched[c]) {
-                tcol[o] = c;
-                tval[o] = acc[c];
-                ++o;
-            }
-        if (lane == 63) cnt[i] = incl;
-    }
-}
-#pragma clang fp contract(on)
 
 // Row i of C = X Y by one wavefront per row over tiles of kTileCols output
 // columns accumulated in LDS, for products whose rows gather many long rows
@@ -756,7 +608,6 @@ __global__ __launch_bounds__(64) void k_gemm_dense(const int* __restrict__ xptr,
 constexpr int kTileCols = 4096;
 constexpr int kTileGroup = 8;
 constexpr int kTileMaxLists = 4096;
-constexpr long long kTileMinWork = 2048;  // mean product entries per row from which the tiles pay
 
 __device__ __forceinline__ int wave_min_int(int v) {
 #pragma unroll
@@ -875,6 +726,134 @@ __global__ __launch_bounds__(64) void k_gemm_tiled(const int* __restrict__ xptr,
 }
 #pragma clang fp contract(on)
 
+// Row i of C = X Y by G lanes with a hash table of the row's columns in LDS (T
+// slots, linear probing).  The lists Y(k_t, :) are visited in X's column
+// order, G at a time: each lane reads one list's bounds, then the G lists'
+// entries are loaded together, a lane per entry, and added list by list (a
+// list's columns are distinct, so its lanes meet in no slot): a column's first
+// product is stored, later ones added.  Every column receives its products in
+// the merge's order, so the sums are bitwise the merge's.  The row's columns are
+// then packed, and each is written at the place its rank gives it.  Unlike a merge,
+// whose every step waits for one list's next entry, a row here waits for
+// memory three times per G lists.  At 7.08M cells, all
+// products of a setup: 32 ms with heap merges (22 ms), register merges of short
+// rows and dense rows; 5 ms with tables (setup 80 -> 37 ms, refresh 41 -> 15 ms).  A row with more than 7/8 T columns sets
+// *full and is left out: the caller takes a larger table.
+#pragma clang fp contract(off)
+template <int G, int T>
+__global__ __launch_bounds__(64) void k_gemm_hash(const int* __restrict__ xptr, const int* __restrict__ xcol,
+                                                 const double* __restrict__ xval, const int* __restrict__ yptr,
+                                                 const int* __restrict__ ycol, const double* __restrict__ yval, int rows,
+                                                 const long long* __restrict__ off, int* __restrict__ tcol,
+                                                 double* __restrict__ tval, int* __restrict__ cnt, int* full) {
+    constexpr int R = 64 / G, kMost = T / 8 * 7, kB = G < 16 ? G : 16, kEmpty = -1;
+    __shared__ double s_val[R][T];
+    __shared__ int s_key[R][T + 1];  // the groups' probes start in different banks
+    const int lane = (int)threadIdx.x, sub = lane / G, gl = lane % G;
+    double* tv = s_val[sub];
+    int* tk = s_key[sub];
+    for (long long i0 = (long long)blockIdx.x * R; i0 < rows; i0 += (long long)gridDim.x * R) {
+        const long long i = i0 + sub;
+        for (int q = gl; q < T; q += G) tk[q] = kEmpty;
+        const int base = i < rows ? xptr[i] : 0, L = i < rows ? xptr[i + 1] - base : 0;
+        int mine = 0;  // columns this lane has entered
+        bool over = false;
+        int longest = L;
+#pragma unroll
+        for (int d = G; d < 64; d <<= 1) longest = max(longest, __shfl_xor(longest, d, 64));
+        for (int t0 = 0; t0 < longest; t0 += kB) {
+            // lane g of the group reads list t0 + g
+            int y0 = 0, y1 = 0;
+            double xv = 0.0;
+            if (gl < kB && t0 + gl < L) {
+                const int k = xcol[base + t0 + gl];
+                xv = xval[base + t0 + gl];
+                y0 = yptr[k];
+                y1 = yptr[k + 1];
+            }
+            int b[kB], e[kB], c[kB];
+            double v[kB];
+#pragma unroll
+            for (int g = 0; g < kB; ++g) {
+                b[g] = __shfl(y0, sub * G + g, 64) + gl;
+                e[g] = __shfl(y1, sub * G + g, 64);
+                const int p = max(min(b[g], e[g] - 1), 0);  // in bounds: a list's last entry again
+                c[g] = ycol[p];
+                v[g] = yval[p];
+            }
+#pragma unroll
+            for (int g = 0; g < kB; ++g) {
+                const double x = __shfl(xv, sub * G + g, 64);
+                int p = b[g], col = c[g];
+                double y = v[g];
+                while (p < e[g]) {
+                    if (!over) {
+                        const double prod = x * y;
+                        unsigned h = (unsigned)col * 2654435761u;
+                        h = (h >> 15) & (T - 1);
+                        for (int n = 0;; ++n) {
+                            const int was = atomicCAS(&tk[h], kEmpty, col);
+                            if (was == kEmpty) {
+                                tv[h] = prod;
+                                ++mine;
+                                break;
+                            }
+                            if (was == col) {
+                                tv[h] += prod;
+                                break;
+                            }
+                            if (n >= T) {  // table full
+                                over = true;
+                                break;
+                            }
+                            h = (h + 1) & (T - 1);
+                        }
+                    }
+                    p += G;
+                    if (p < e[g]) {
+                        col = ycol[p];
+                        y = yval[p];
+                    }
+                }
+            }
+            // the group's count so far: stop entering once the table is nearly full
+            int total = mine;
+#pragma unroll
+            for (int d = 1; d < G; d <<= 1) total += __shfl_xor(total, d, 64);
+            over = over || total > kMost;
+        }
+        int any = over ? 1 : 0;
+#pragma unroll
+        for (int d = 1; d < G; d <<= 1) any |= __shfl_xor(any, d, 64);
+        if (any && gl == 0) *full = 1;
+        // the used slots to the table's front, G slots at a time (a step writes
+        // only at or before the slots it has read)
+        int m = 0;
+        for (int q = 0; q < T; q += G) {
+            const int key = tk[q + gl];
+            const double v = tv[q + gl];
+            const unsigned long long used = (__ballot(key != kEmpty) >> (sub * G)) & (G == 64 ? ~0ull : (1ull << (G & 63)) - 1);
+            if (key != kEmpty) {
+                const int to = m + __popcll(used & ((1ull << gl) - 1));
+                tk[to] = key;
+                tv[to] = v;
+            }
+            m += __popcll(used);
+        }
+        if (any) m = 0;
+        const long long o = i < rows ? off[i] : 0;
+        for (int q = gl; q < m; q += G) {
+            const int key = tk[q];
+            int rank = 0;
+            for (int u = 0; u < m; ++u) rank += tk[u] < key;
+            tcol[o + rank] = key;
+            tval[o + rank] = tv[q];
+        }
+        if (gl == 0 && i < rows) cnt[i] = m;
+    }
+}
+#pragma clang fp contract(on)
+
 // the longest row of a CSR matrix
 __global__ __launch_bounds__(kSetupBs) void k_max_rowlen(const int* __restrict__ ptr, int rows, int* out) {
     int m = 0;
@@ -981,6 +960,32 @@ __global__ __launch_bounds__(kLdsBs) void k_row_heapsort_lds(const int* __restri
     for (int k = 0; k < n; ++k) {
         col[b + k] = a[k];
         val[b + k] = v[k];
+    }
+}
+
+// the same with G lanes per row of at most T entries: the row is copied into
+// LDS and every entry written at its rank (one thread's heap sort of a row
+// waits on a chain of LDS accesses: 990 us per sort at 7.08M cells)
+template <int G, int T>
+__global__ __launch_bounds__(64) void k_row_ranksort(const int* __restrict__ ptr, int rows, int* __restrict__ col,
+                                                    double* __restrict__ val) {
+    constexpr int R = 64 / G;
+    __shared__ double s_val[R][T];
+    __shared__ int s_key[R][T + 1];
+    const int lane = (int)threadIdx.x, sub = lane / G, gl = lane % G;
+    const long long i = (long long)blockIdx.x * R + sub;
+    const int b = i < rows ? ptr[i] : 0, n = i < rows ? ptr[i + 1] - b : 0;
+    for (int k = gl; k < n; k += G) {
+        s_key[sub][k] = col[b + k];
+        s_val[sub][k] = val[b + k];
+    }
+    __syncthreads();
+    for (int k = gl; k < n; k += G) {
+        const int key = s_key[sub][k];
+        int rank = 0;
+        for (int u = 0; u < n; ++u) rank += s_key[sub][u] < key;
+        col[b + rank] = key;
+        val[b + rank] = s_val[sub][k];
     }
 }
 
@@ -1103,44 +1108,40 @@ int lds_plan(const int* ptr, int rows, hipStream_t s, int* lcap, int* per_wg) {
 
 // Launch the product kernel a plan names: every output row i's distinct
 // columns and sums at off[i] in (tcol, tval), and its count in cnt[i].
-// Scratch (dense accumulators, device-memory heaps) is allocated here and
-// freed after a synchronisation.
+// Scratch (device-memory heaps) is allocated here and freed after a
+// synchronisation.  `full` (hash products): set when a row's table filled up.
 int spgemm_launch(const CsrView& X, const CsrView& Y, const ProdPlan& plan, const long long* off, int* tcol,
-                  double* tval, int* cnt, hipStream_t s) {
+                  double* tval, int* cnt, int* full, hipStream_t s) {
     int rc;
     const int rows = X.n;
-    DevBuf<double> dacc;
-    DevBuf<uint8_t> dtouch;
     DevBuf<unsigned long long> heap;
     DevBuf<int> pos;
     switch (plan.mode) {
-        case kProdDense:  // narrow product: dense rows, a wavefront each
-            if ((rc = dacc.alloc((size_t)rows * std::max(Y.m, 1), "product accumulators")) ||
-                (rc = dtouch.alloc((size_t)rows * std::max(Y.m, 1), "product flags")))
-                return rc;
-            hipLaunchKernelGGL(k_gemm_dense, dim3((unsigned)std::min(rows, 65536)), dim3(64), 0, s, X.ptr, X.col,
-                               X.val, Y.ptr, Y.col, Y.val, rows, Y.m, off, dacc.p, dtouch.p, tcol, tval, cnt);
-            break;
         case kProdTiled:  // long rows: LDS column tiles
             hipLaunchKernelGGL(k_gemm_tiled, dim3((unsigned)std::min(rows, 65536)), dim3(64), 0, s, X.ptr, X.col,
                                X.val, Y.ptr, Y.col, Y.val, rows, off, tcol, tval, cnt);
             break;
-        case kProdShort:  // rows of X of at most kShortLists entries
-            hipLaunchKernelGGL(k_gemm_short<kShortLists>, dim3(grid1d(rows)), dim3(kSetupBs), 0, s, X.ptr, X.col,
-                               X.val, Y.ptr, Y.col, Y.val, rows, off, tcol, tval, cnt);
-            break;
-        case kProdMergeLds: {
-            const long long blocks = ((long long)rows + plan.per_wg - 1) / plan.per_wg;
-            hipLaunchKernelGGL(k_gemm_merge_lds<unsigned long long>, dim3((unsigned)std::max(blocks, 1LL)),
-                               dim3(kLdsBs), (size_t)plan.per_wg * plan.lcap * 12, s, X.ptr, X.col, X.val, Y.ptr,
-                               Y.col, Y.val, rows, plan.per_wg, plan.lcap, off, tcol, tval, cnt);
+        case kProdHash: {
+#define FV_HASH(G, T)                                                                                            \
+    if (plan.lanes == G && plan.slots == T)                                                                      \
+        hipLaunchKernelGGL((k_gemm_hash<G, T>), dim3((unsigned)std::min((rows + 64 / G - 1) / (64 / G), 1 << 20)), \
+                           dim3(64), 0, s, X.ptr, X.col, X.val, Y.ptr, Y.col, Y.val, rows, off, tcol, tval, cnt, full)
+            FV_HASH(8, 64);
+            FV_HASH(8, 128);
+            FV_HASH(8, 512);
+            FV_HASH(16, 128);
+            FV_HASH(16, 512);
+            FV_HASH(64, 512);
+            FV_HASH(64, 2048);
+            FV_HASH(64, 4096);
+#undef FV_HASH
             break;
         }
-        case kProdMergeLds32: {  // 32-bit heap keys: 8 bytes of LDS per list, more rows per CU
+        case kProdMergeLds: {
             const long long blocks = ((long long)rows + plan.per_wg - 1) / plan.per_wg;
-            hipLaunchKernelGGL(k_gemm_merge_lds<unsigned int>, dim3((unsigned)std::max(blocks, 1LL)), dim3(kLdsBs),
-                               (size_t)plan.per_wg * plan.lcap * 8, s, X.ptr, X.col, X.val, Y.ptr, Y.col, Y.val,
-                               rows, plan.per_wg, plan.lcap, off, tcol, tval, cnt);
+            hipLaunchKernelGGL(k_gemm_merge_lds, dim3((unsigned)std::max(blocks, 1LL)),
+                               dim3(kLdsBs), (size_t)plan.per_wg * plan.lcap * 12, s, X.ptr, X.col, X.val, Y.ptr,
+                               Y.col, Y.val, rows, plan.per_wg, plan.lcap, off, tcol, tval, cnt);
             break;
         }
         default:
@@ -1152,7 +1153,7 @@ int spgemm_launch(const CsrView& X, const CsrView& Y, const ProdPlan& plan, cons
             break;
     }
     FV_LAUNCHED();
-    if (dacc.p || heap.p) FV_HIP(hipStreamSynchronize(s));  // their scratch is freed on return
+    if (heap.p) FV_HIP(hipStreamSynchronize(s));  // their scratch is freed on return
     return FVPCG_OK;
 }
 
@@ -1181,38 +1182,54 @@ int spgemm(const CsrView& X, const CsrView& Y, CsrOut& C, hipStream_t s, ProdPla
     int lcap = 0, per_wg = 0, mlen = 0;
     if ((rc = read_scalar(&mlen, mx.p, s))) return rc;
     lds_fit(mlen, &lcap, &per_wg);
-    // Kernel choice: dense rows for narrow products, LDS column tiles for
-    // long rows, list heads in registers for rows of X of at most
-    // kShortLists entries, else the heap merge (32-bit keys where they
-    // fit).  FVPCG_AMG_PRODUCT = merge | merge32 | tiled | dense | short
-    // forces one where it applies (all give the same sums); tests use it.
+    // Kernel choice: hash tables in LDS, and for rows too wide for the largest
+    // (3,584 columns) LDS column tiles, or the heap merge where a row of X has
+    // more lists than the tiles hold.  All give the same sums;
+    // FVPCG_AMG_PRODUCT = hash | tiled | merge forces one where it applies.
     const char* force = getenv("FVPCG_AMG_PRODUCT");
     const std::string fk = force ? force : "";
-    const bool dense_ok = (long long)rows * Y.m <= kDenseEntries, tiled_ok = mlen <= kTileMaxLists;
-    const bool use_dense = dense_ok && (fk.empty() || fk == "dense");
-    const bool use_tiled = !use_dense && tiled_ok &&
-                           (fk == "tiled" || (fk.empty() && (total >= kTileMinWork * (long long)rows || per_wg < 1)));
-    const bool use_short = !use_dense && !use_tiled && mlen <= kShortLists && (fk.empty() || fk == "short");
-    // the LDS merge with 32-bit keys where the lists and columns fit them:
-    // 8 instead of 12 bytes of LDS per list, so more rows share a CU
-    const int per_wg32 = std::min(kLdsBs, kLdsBytes / (8 * lcap));
-    const bool use_k32 = !use_dense && !use_tiled && !use_short && per_wg >= 1 && mlen <= kKey32Lists &&
-                         Y.m < kKey32Cols && (fk.empty() || fk == "merge32");
-    plan->mode = use_dense ? kProdDense
-                 : use_tiled ? kProdTiled
-                 : use_short ? kProdShort
-                 : use_k32 ? kProdMergeLds32
-                 : per_wg >= 1 ? kProdMergeLds
-                               : kProdMerge;
-    plan->lcap = lcap;
-    plan->per_wg = use_k32 ? per_wg32 : per_wg;
-    if ((rc = spgemm_launch(X, Y, *plan, off.p, tcol.p, tval.p, cnt.p, s))) return rc;
+    int nnz = 0;
+    bool hashed = false;
+    if (fk.empty() || fk == "hash") {
+        // Lanes per row by the mean list; the smallest table that the mean
+        // product count does not already rule out (measured on the Galerkin
+        // products: 4 to 35 products per distinct column), the next larger one
+        // when a row fills it.  64 slots only for rows of X of up to 8 entries
+        // (level 0's).
+        const double list = (double)Y.nnz / (double)std::max(Y.n, 1);
+        const double work = (double)total / (double)std::max(rows, 1);
+        const int lanes = list <= 8.0 ? 8 : list <= 24.0 ? 16 : 64;
+        DevBuf<int> full;
+        if ((rc = full.alloc(1, "product table flag"))) return rc;
+        for (int slots : {64, 128, 512, 2048, 4096}) {
+            if (slots == 64 && (mlen > 8 || lanes != 8)) continue;
+            if (slots == 128 && lanes == 64) continue;
+            if (slots < 4096 && work > 32.0 * slots) continue;
+            plan->mode = kProdHash;
+            plan->lanes = slots > 512 ? 64 : lanes;
+            plan->slots = slots;
+            FV_HIP(hipMemsetAsync(full.p, 0, sizeof(int), s));
+            if ((rc = spgemm_launch(X, Y, *plan, off.p, tcol.p, tval.p, cnt.p, full.p, s))) return rc;
+            int f = 0;
+            if ((rc = read_scalar(&f, full.p, s))) return rc;
+            if (!f) {
+                hashed = true;
+                break;
+            }
+        }
+    }
+    if (!hashed) {
+        const bool use_tiled = mlen <= kTileMaxLists && (fk.empty() || fk == "hash" || fk == "tiled");
+        plan->mode = use_tiled ? kProdTiled : per_wg >= 1 ? kProdMergeLds : kProdMerge;
+        plan->lcap = lcap;
+        plan->per_wg = per_wg;
+    }
+    if (!hashed && (rc = spgemm_launch(X, Y, *plan, off.p, tcol.p, tval.p, cnt.p, nullptr, s))) return rc;
     C.n = rows;
     C.m = Y.m;
     if ((rc = dev_alloc(&C.ptr, (size_t)rows + 1, "product row pointers"))) return rc;
     // counts fit in int: a row's distinct columns are at most Y.m
     if ((rc = scan_excl<int>(cnt.p, C.ptr, rows, s))) return rc;
-    int nnz = 0;
     if ((rc = read_scalar(&nnz, C.ptr + rows, s))) return rc;
     if (nnz < 0) return set_error(FVPCG_UNSUPPORTED, "AMG: a coarse operator exceeds 2^31 entries");
     C.nnz = nnz;
@@ -1244,7 +1261,8 @@ int spgemm_numeric(const CsrView& X, const CsrView& Y, int* ccol, double* cval, 
     DevBuf<int> cnt;
     int rc;
     if ((rc = cnt.alloc((size_t)X.n + 1, "product counts"))) return rc;
-    if ((rc = spgemm_launch(X, Y, plan, off64, ccol, cval, cnt.p, s))) return rc;
+    // (the patterns are those the tables were sized for: none fills up)
+    if ((rc = spgemm_launch(X, Y, plan, off64, ccol, cval, cnt.p, cnt.p + X.n, s))) return rc;
     FV_HIP(hipStreamSynchronize(s));
     return FVPCG_OK;
 }
@@ -1272,7 +1290,13 @@ int transpose(const CsrView& X, CsrOut& T, hipStream_t s) {
     FV_LAUNCHED();
     int lcap = 0, per_wg = 0;
     if ((rc = lds_plan(T.ptr, T.n, s, &lcap, &per_wg))) return rc;
-    if (per_wg >= 1) {
+    if (lcap <= 128) {
+        hipLaunchKernelGGL((k_row_ranksort<16, 128>), dim3((unsigned)std::max((T.n + 3) / 4, 1)), dim3(64), 0, s, T.ptr,
+                           T.n, T.col, T.val);
+    } else if (lcap <= 1024) {
+        hipLaunchKernelGGL((k_row_ranksort<64, 1024>), dim3((unsigned)std::max(T.n, 1)), dim3(64), 0, s, T.ptr, T.n, T.col,
+                           T.val);
+    } else if (per_wg >= 1) {
         const long long blocks = ((long long)T.n + per_wg - 1) / per_wg;
         hipLaunchKernelGGL(k_row_heapsort_lds, dim3((unsigned)std::max(blocks, 1LL)), dim3(kLdsBs),
                            (size_t)per_wg * lcap * 12, s, T.ptr, T.n, per_wg, lcap, T.col, T.val);

@@ -206,6 +206,11 @@ __device__ __forceinline__ void block_sum(double (&v)[NV]) {
 // partial sums (layout [NV][G]) and takes a ticket; the workgroup that draws
 // the last ticket sums all partials in a fixed order and returns true with
 // the totals in thread 0's `tot`.  Deterministic for a given G.
+// The partials are stored and loaded with agent scope (past the XCD's L2),
+// and the ticket is taken once those stores have completed, so a workgroup
+// that sees the last ticket sees every partial.  Nothing else is published
+// here: an acquire-release ticket would write back the L2's dirty lines, the
+// kernel's own results, once per workgroup.
 template <int BS, int NV>
 __device__ __forceinline__ bool device_reduce(double (&v)[NV], double* partials, uint32_t* ticket, int blk,
                                               int G, double (&tot)[NV]) {
@@ -215,12 +220,12 @@ __device__ __forceinline__ bool device_reduce(double (&v)[NV], double* partials,
 #pragma unroll
         for (int k = 0; k < NV; ++k)
             __hip_atomic_store(&partials[(size_t)k * G + blk], v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        uint32_t t = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        uint32_t t = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_last = (t == (uint32_t)(G - 1));
     }
     __syncthreads();
     if (!s_last) return false;
-    __atomic_thread_fence(__ATOMIC_ACQUIRE);
     double acc[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) acc[k] = 0.0;

@@ -49,7 +49,7 @@ void work_free(Work& w);
 int work_need_cg(Work& w);
 int work_need_pipe(Work& w, bool literal);
 int work_need_mixed(Work& w);
-int work_need_resident(Work& w);
+int work_need_resident(Work& w, bool exchange);
 
 }  // namespace fvpcg
 

@@ -105,6 +105,38 @@ ResPlan resident_plan(const fvpcg_mesh* m, int method) {
     return p;
 }
 
+ResPlan resident_plan32(const fvpcg_mesh* m) {
+    ResPlan p;
+    const char* env = getenv("FVPCG_RESIDENT");
+    if (env && env[0] == '0') return p;
+    if (m->WT > 8 || m->n < 1 || m->device < 0 || m->device >= kMaxDevices) return p;
+    const DeviceInfo& info = device_info(m->device);
+    const int tiles = (m->n + kResBsMixed - 1) / kResBsMixed;
+    const int g = std::min(tiles, kMaxGrid);  // geom_for's workgroups
+    int rpt = (tiles + g - 1) / g;
+    rpt = rpt <= 2 ? rpt : rpt <= 4 ? 4 : rpt <= 6 ? 6 : rpt;
+    if (rpt == 7) rpt = 8;
+    if (rpt > (m->WT > 6 || !m->col16 ? 4 : 8) || g > info.cus || info.ticks_per_ms <= 0) return p;
+    p.block = kResBsMixed;
+    p.size = g;
+    p.rpt = rpt;
+    return p;
+}
+
+int resident_run32(const fvpcg_mesh* m, const ResPlan& plan, const ResWork& w, const PipeVec<float>& a, int iters,
+                   DevState* st, DevState* st_skip, hipStream_t s) {
+    const DeviceInfo& info = device_info(m->device);
+    int rc;
+    if ((rc = resident_reset(w.slots, res_slots(plan.size), w.meet, w.abort_flag, nullptr, 0, s))) return rc;
+    ResTeam t{0, plan.size, w.slots, w.meet, w.abort_flag, nullptr,
+              (unsigned long long)(info.ticks_per_ms * resident_meet_ms()),
+              (unsigned long long)(info.ticks_per_ms * kResSpinMs), 0};
+    hipLaunchKernelGGL(res_kernel_mixed(plan.rpt, m->WT, m->col16 != nullptr), dim3(plan.size), dim3(plan.block), 0, s, a,
+                       m->n, iters, t, st, st_skip);
+    FV_LAUNCHED();
+    return FVPCG_OK;
+}
+
 int resident_solve(const fvpcg_matrix* A, const ResPlan& plan, const ResWork& w, const double* b, double* x, double tol,
                    int maxit, bool jac, hipStream_t s, fvpcg_stats* stats, bool* done) {
     *done = false;

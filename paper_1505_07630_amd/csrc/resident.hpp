@@ -46,8 +46,8 @@
 
 namespace fvpcg {
 
-constexpr int kResBsPipe = 512, kResBsCg = 1024;  // threads per workgroup: the launch path's tiles
-static_assert(kResBsPipe == kBsPipe && kResBsCg == kBsCg, "the same tiles, the same sums");
+constexpr int kResBsPipe = 512, kResBsCg = 1024, kResBsMixed = 1024;  // threads per workgroup: the launch path's tiles
+static_assert(kResBsPipe == kBsPipe && kResBsCg == kBsCg && kResBsMixed == kBsMixed, "the same tiles, the same sums");
 constexpr int kResMaxTeam = kMaxGrid;  // members of a team at most
 constexpr int kResBufs = 4;           // slot buffers
 constexpr int kResSums = 3;           // sums per reduction
@@ -103,6 +103,17 @@ __device__ __forceinline__ void st_agent(double* p, double v) {
 }
 __device__ __forceinline__ double ld_agent(const double* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The same at element i of an exchanged vector below 4 GiB: a scalar base and
+// one address register per access.
+template <typename T>
+__device__ __forceinline__ void put_agent(T* p, int i, T v) {
+    __hip_atomic_store((T*)((char*)p + (unsigned)i * (unsigned)sizeof(T)), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T get_agent(const T* p, int i) {
+    return __hip_atomic_load((const T*)((const char*)p + (unsigned)i * (unsigned)sizeof(T)), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
 }
 // The wave's earlier stores have completed.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -297,22 +308,22 @@ struct RowCols<WT, int> {
     }
 };
 
-// RPT doubles per thread in registers, or in LDS.
-template <int BS, int RPT, bool LDS>
+// RPT values per thread in registers, or in LDS.
+template <int BS, int RPT, bool LDS, typename T = double>
 struct Store;
-template <int BS, int RPT>
-struct Store<BS, RPT, false> {
-    double v[RPT];
-    __device__ __forceinline__ Store(double*) {}
-    __device__ __forceinline__ double get(int k) const { return v[k]; }
-    __device__ __forceinline__ void set(int k, double a) { v[k] = a; }
+template <int BS, int RPT, typename T>
+struct Store<BS, RPT, false, T> {
+    T v[RPT];
+    __device__ __forceinline__ Store(T*) {}
+    __device__ __forceinline__ T get(int k) const { return v[k]; }
+    __device__ __forceinline__ void set(int k, T a) { v[k] = a; }
 };
-template <int BS, int RPT>
-struct Store<BS, RPT, true> {
-    double* p;
-    __device__ __forceinline__ Store(double* base) : p(base + threadIdx.x) {}
-    __device__ __forceinline__ double get(int k) const { return p[k * BS]; }
-    __device__ __forceinline__ void set(int k, double a) { p[k * BS] = a; }
+template <int BS, int RPT, typename T>
+struct Store<BS, RPT, true, T> {
+    T* p;
+    __device__ __forceinline__ Store(T* base) : p(base + threadIdx.x) {}
+    __device__ __forceinline__ T get(int k) const { return p[k * BS]; }
+    __device__ __forceinline__ void set(int k, T a) { p[k * BS] = a; }
 };
 
 // The exchanged vectors: device memory with agent scope, or, for a system one
@@ -323,13 +334,8 @@ template <int BS, int RPT>
 struct Exchange<BS, RPT, false> {
     double* v[2];
     __device__ __forceinline__ Exchange(const ResSystem& sys, double*) : v{sys.e0, sys.e1} {}
-    // 32-bit byte offsets (resident vectors are below 4 GiB): scalar base, one
-    // address register per access
-    __device__ __forceinline__ double* at(int buf, int c) const {
-        return (double*)((char*)(buf ? v[1] : v[0]) + (unsigned)c * 8u);
-    }
-    __device__ __forceinline__ void put(int buf, int c, double a) { st_agent(at(buf, c), a); }
-    __device__ __forceinline__ double get(int buf, int c) const { return ld_agent(at(buf, c)); }
+    __device__ __forceinline__ void put(int buf, int c, double a) { put_agent(buf ? v[1] : v[0], c, a); }
+    __device__ __forceinline__ double get(int buf, int c) const { return get_agent(buf ? v[1] : v[0], c); }
 };
 template <int BS, int RPT>
 struct Exchange<BS, RPT, true> {
@@ -358,6 +364,7 @@ __device__ __forceinline__ double res_gather(const RowCols<WT, CI>& col, const d
 // Scalars of the recurrences, the same in every thread of the team.
 struct ResScalars {
     double gamma = 0, alpha = 0, beta = 0, tol_abs = 0, r0norm = 0, rho = 0;
+    double delta = 0, gamma_old = 0, alpha_old = 0;
     int iter = 0, status = FVPCG_NOT_CONVERGED;
     bool done = false;
 };
@@ -394,7 +401,10 @@ __device__ __forceinline__ void res_pipe_step(ResScalars& y, double gamma, doubl
         y.status = FVPCG_BREAKDOWN;
         return;
     }
+    y.gamma_old = y.gamma;
+    y.alpha_old = y.alpha;
     y.gamma = gamma;
+    y.delta = delta;
     y.alpha = alpha;
     y.beta = beta;
 }
@@ -719,6 +729,118 @@ __device__ __forceinline__ void resident_cg(const ResSystem& sys, ResTeam& t, do
     }
     if (!sr.finish(t, rr)) return;
     res_report(t, out, y, bnorm, rr[0], zero_b, t_begin, t_it0, t_it1);
+}
+
+// A run of FP32 folded pipelined iterations of the mixed-precision solve
+// (solve.hip, between two FP64 updates): the recurrence vectors are read from
+// memory at the start and written back at the end, the iterations between
+// keep them on chip, r, w, the values and the columns in registers, z, s, p and
+// the correction c in LDS.  d comes from the L2 (4 bytes a row).  The scalars
+// are those of `st`, as pipe_scalars steps them; member 0 writes them back.
+// A team that does not come together sets st_skip->done = kResNoTeam, which
+// makes the update kernels that follow do nothing; a wait given up sets
+// kResLost.
+constexpr int32_t kResNoTeam = 2, kResLost = 3;
+
+template <int RPT, int WT, typename CI>
+__device__ __forceinline__ void resident_pipe32(const PipeVec<float>& a, int n, int iters, ResTeam& t, DevState* st,
+                                                DevState* st_skip, float* lds) {
+    constexpr int BS = kResBsMixed;
+    struct {
+        int c0, c1;
+    } sys{0, n};
+    RowCols<WT, CI> col[RPT];
+    float val[RPT][WT], r[RPT], w[RPT];
+    Store<BS, RPT, true, float> z(lds), s(lds + RPT * BS), p(lds + 2 * RPT * BS), x(lds + 3 * RPT * BS);
+    RES_ROWS(k, c) {
+        col[k].load(a.col, (size_t)n, c);
+#pragma unroll
+        for (int i = 0; i < WT; ++i) val[k][i] = ld_once(a.val + (size_t)i * n + c);
+        r[k] = a.r[c];
+        w[k] = a.w_in[c];
+        z.set(k, a.z[c]);
+        s.set(k, a.s[c]);
+        p.set(k, a.p[c]);
+        x.set(k, a.x[c]);
+    }
+    ResScalars y;
+    y.gamma = st->gamma;
+    y.delta = st->delta;
+    y.alpha = st->alpha;
+    y.beta = st->beta;
+    y.gamma_old = st->gamma_old;
+    y.alpha_old = st->alpha_old;
+    y.tol_abs = st->tol_abs;
+    y.rho = st->rho;
+    y.iter = st->iter;
+    y.status = st->status;
+    const int maxit = st->maxit;
+    float* const e0 = const_cast<float*>(a.w_in);
+    bool ok = true;
+    for (int it = 0; it < iters && !y.done; ++it) {
+        const float* w_in = (it & 1) ? a.w_out : e0;
+        float* w_out = (it & 1) ? e0 : a.w_out;
+        const float alpha = (float)y.alpha, beta = (float)y.beta;
+        Sums<BS, 3, RPT, false> sa;
+        RES_ROWS(k, c) {
+            float g[WT];
+            col[k].pin();
+#pragma unroll
+            for (int i = 0; i < WT; ++i) g[i] = get_agent(w_in, col[k].at(i, c));
+            const float dc = a.d[c];
+            const float wc = w[k];
+            float nv = wc;
+#pragma unroll
+            for (int i = 0; i < WT; ++i) nv = fma(val[k][i], g[i], nv);
+            const float zc = nv + beta * z.get(k);
+            const float wn = wc - alpha * zc;
+            put_agent(w_out, c, wn);
+            const float sc = wc + beta * s.get(k);
+            float rc = r[k];
+            float uc = rc / dc;
+            const float pc = uc + beta * p.get(k);
+            p.set(k, pc);
+            x.set(k, x.get(k) + alpha * pc);
+            rc -= alpha * sc;
+            z.set(k, zc);
+            s.set(k, sc);
+            r[k] = rc;
+            w[k] = wn;
+            uc = rc / dc;
+            sa.add(k, 0, (double)rc * (double)uc);
+            sa.add(k, 1, (double)wn * (double)uc);
+            sa.add(k, 2, (double)rc * (double)rc);
+        }
+        double q[3];
+        ok = sa.finish(t, q);
+        if (!ok) break;
+        res_pipe_step(y, q[0], q[1], q[2], false, maxit);
+    }
+    if (!ok) {
+        if (threadIdx.x == 0) st_skip->done = kResLost;
+        return;
+    }
+    // w lies where the launches would have left it (a stopped run leaves w as
+    // its last iteration's; nobody reads it then)
+    RES_ROWS(k, c) {
+        a.r[c] = r[k];
+        a.z[c] = z.get(k);
+        a.s[c] = s.get(k);
+        a.p[c] = p.get(k);
+        a.x[c] = x.get(k);
+    }
+    if (t.rank == 0 && threadIdx.x == 0) {
+        st->gamma = y.gamma;
+        st->delta = y.delta;
+        st->alpha = y.alpha;
+        st->beta = y.beta;
+        st->gamma_old = y.gamma_old;
+        st->alpha_old = y.alpha_old;
+        st->rho = y.rho;
+        st->iter = y.iter;
+        st->status = y.status;
+        st->done = y.done ? 1 : 0;
+    }
 }
 
 }  // namespace fvpcg

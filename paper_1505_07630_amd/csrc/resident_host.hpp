@@ -11,6 +11,9 @@ struct ResOut;
 struct ResSystem;
 struct ResTeam;
 struct ResBatch;
+template <typename T>
+struct PipeVec;
+using ResMixedKernel = void (*)(PipeVec<float>, int, int, ResTeam, DevState*, DevState*);
 using ResBatchKernel = void (*)(ResSystem, ResTeam, ResBatch);
 using ResKernel = void (*)(ResSystem, ResTeam, ResOut*);
 
@@ -45,6 +48,7 @@ std::mutex* resident_teams(int device);
 ResPlan resident_plan(const fvpcg_mesh* m, int method);
 ResKernel res_kernel_pipe(const ResPlan& p, int wt, bool col16, bool jac);
 ResKernel res_kernel_cg(const ResPlan& p, int wt, bool col16, bool jac);
+ResMixedKernel res_kernel_mixed(int rpt, int wt, bool col16);
 ResBatchKernel res_batch_pipe(int rpt, int wt, bool col16, bool jac);
 ResBatchKernel res_batch_cg(int rpt, int wt, bool col16, bool jac);
 double resident_meet_ms();
@@ -53,6 +57,14 @@ void resident_device(int device, int* cus, double* ticks_per_ms);
 // Enqueues the reset of `count` slot doubles, the rendezvous word, the abort
 // flag and nout results.
 int resident_reset(double* slots, size_t count, unsigned* meet, int* abort_flag, ResOut* out, int nout, hipStream_t s);
+
+// A run of `iters` FP32 pipelined iterations (resident_pipe32): up to 2,097,152
+// cells (8 rows per thread; int32 columns or rows of more than 6 slots leave
+// room for 4).  The caller holds resident_teams() from the launch until it has
+// seen what became of it in st_skip.
+ResPlan resident_plan32(const fvpcg_mesh* m);
+int resident_run32(const fvpcg_mesh* m, const ResPlan& plan, const ResWork& w, const PipeVec<float>& a, int iters,
+                   DevState* st, DevState* st_skip, hipStream_t s);
 
 // *done = false with FVPCG_OK: not solved here, solve by launches (x is still
 // a valid starting vector); a negative code is an error.

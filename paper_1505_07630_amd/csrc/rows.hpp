@@ -206,4 +206,21 @@ __device__ __forceinline__ void pipe_scalars(DevState* st, double gamma, double 
     st->beta = beta;
 }
 
+// The vectors of a pipelined iteration (solve.hip).
+template <typename T>
+struct PipeVec {
+    const void* col;  // int32 columns or int16 offsets (the kernel's CI)
+    const T* val;  // column-scaled with Jacobi, plain otherwise
+    const T* d;
+    const T* w_in;
+    T* w_out;
+    T* z;
+    T* s;
+    T* p;
+    T* x;
+    T* r;
+    T* u;  // literal only
+    T* q;  // literal only
+};
+
 }  // namespace fvpcg

@@ -194,23 +194,6 @@ __global__ __launch_bounds__(BS) void k_cg_update_xp(double* __restrict__ x, dou
 //   beta = gamma / gamma_prev,
 //   alpha = gamma / (delta - beta * gamma / alpha_prev).
 
-template <typename T>
-struct PipeVec {
-    const void* col;  // int32 columns or int16 offsets (the kernel's CI)
-    const T* val;  // column-scaled with Jacobi, plain otherwise
-    const T* d;
-    const T* w_in;
-    T* w_out;
-    T* z;
-    T* s;
-    T* p;
-    T* x;
-    T* r;
-    T* u;  // literal only
-    T* q;  // literal only
-};
-
-
 // r = b - A x; (b, b) -> bnorm and the absolute tolerance; clears the
 // pipelined recurrences (z, s, p[, q]) and sets u = M^-1 r (literal).
 template <int BS, int WT, typename CI, bool JAC, bool LIT>
@@ -708,10 +691,11 @@ int work_need_mixed(Work& w) {
     return FVPCG_OK;
 }
 
-int work_need_resident(Work& w) {
+// `exchange`: the FP64 solves' exchange vectors too.
+int work_need_resident(Work& w, bool exchange) {
     int rc;
-    if (!w.w[0] && (rc = dev_alloc(&w.w[0], (size_t)w.n, "w0"))) return rc;
-    if (!w.w[1] && (rc = dev_alloc(&w.w[1], (size_t)w.n, "w1"))) return rc;
+    if (exchange && !w.w[0] && (rc = dev_alloc(&w.w[0], (size_t)w.n, "w0"))) return rc;
+    if (exchange && !w.w[1] && (rc = dev_alloc(&w.w[1], (size_t)w.n, "w1"))) return rc;
     if (!w.res_slots && (rc = dev_alloc(&w.res_slots, res_slots(kResMaxTeam), "resident slots"))) return rc;
     if (!w.res_meet && (rc = dev_alloc(&w.res_meet, 2, "resident rendezvous"))) return rc;
     if (!w.res_pinned && hipHostMalloc((void**)&w.res_pinned, sizeof(ResOut), hipHostMallocDefault) != hipSuccess) {
@@ -897,7 +881,7 @@ int solve(const fvpcg_matrix* A, const double* b, double* x, double tol, int max
     const ResPlan plan = resident_plan(A->mesh, method);
     if (plan.rpt) {
         bool done = false;
-        if ((rc = work_need_resident(w))) return rc;
+        if ((rc = work_need_resident(w, true))) return rc;
         rc = solve_resident(A, plan, w, b, x, tol, maxit, precond, s, stats, &done);
         if (rc < 0 || done) return rc;
     }
@@ -1208,6 +1192,17 @@ int solve_mixed_reliable(const fvpcg_matrix* A, const double* b, double* x, doub
     FV_LAUNCHED();
     if ((rc = state_read(w, 0, &h, s))) return rc;
     int offset = 0, updates = 0, wi = 0;
+    // the K FP32 iterations between two updates in one launch, rows held on
+    // chip, where the system fits (resident_pipe32) and no other team runs
+    ResPlan plan = resident_plan32(m);
+    ResWork rw{};
+    std::unique_lock<std::mutex> lock;
+    if (plan.rpt && !h.done) {
+        if ((rc = work_need_resident(w, false))) return rc;
+        rw = {nullptr, nullptr, w.res_slots, w.res_meet, reinterpret_cast<int*>(w.res_meet + 1), nullptr, nullptr};
+        lock = std::unique_lock<std::mutex>(*resident_teams(m->device), std::try_to_lock);
+        if (!lock.owns_lock()) plan.rpt = 0;
+    }
     FV_HIP(hipEventRecord(w.t_it0, s));
     if (!h.done) {
         hipLaunchKernelGGL((k_mixed_cast<kBsMixed>), dim3(gx.grid), dim3(kBsMixed), 0, s, w.r, n, gx, so, w.r32, w.r32b,
@@ -1216,7 +1211,14 @@ int solve_mixed_reliable(const fvpcg_matrix* A, const double* b, double* x, doub
                                         s, cols_, A->val32_cs, A->d32, n, gx, w.r32, w.w32[wi], si, part));
         FV_LAUNCHED();
         for (;;) {
-            for (int k = 0; k < K; ++k) {
+            const int wi0 = wi;
+            if (plan.rpt) {
+                const PipeVec<float> a{mesh_cols(m), A->val32_cs, A->d32, w.w32[wi], w.w32[wi ^ 1], w.z32, w.s32, w.p32,
+                                       w.c32, w.r32, nullptr, nullptr};
+                if ((rc = resident_run32(m, plan, rw, a, K, si, so, s))) return rc;
+                wi ^= K & 1;
+            }
+            for (int k = 0; !plan.rpt && k < K; ++k) {
                 PipeVec<float> a{mesh_cols(m), A->val32_cs, A->d32, w.w32[wi], w.w32[wi ^ 1], w.z32, w.s32, w.p32,
                                  w.c32, w.r32, nullptr, nullptr};
                 FV_LAYOUT(m, hipLaunchKernelGGL((k_pipe_iter<kBsMixed, float, W_, CI_, true, false>), dim3(gx.grid),
@@ -1233,6 +1235,16 @@ int solve_mixed_reliable(const fvpcg_matrix* A, const double* b, double* x, doub
                                             so, part));
             FV_LAUNCHED();
             if ((rc = state_read_both(w, &h, &hi, s))) return rc;
+            if (h.done == kResLost)
+                return set_error(FVPCG_DEVICE_ERROR, "mixed solve: a wait between workgroups timed out");
+            if (h.done == kResNoTeam) {  // nothing was done since the last update: go on by launches
+                plan.rpt = 0;
+                lock.unlock();
+                --updates;
+                wi = wi0;
+                FV_HIP(hipMemsetAsync(&so->done, 0, sizeof(so->done), s));
+                continue;
+            }
             if (h.done) break;
             if (hi.done) {
                 // the FP32 recurrences stopped (breakdown): restart them from

@@ -245,3 +245,43 @@ def test_resident_batch(fv, monkeypatch, name, col32):
             xo, _ = run(oracle.system(case), case.b, tol=0.0, maxit=its[s])
             assert rel(xs, xo) <= 1e-10, s
     B.close()
+
+
+# ------------------------------------------------------------------ mixed precision
+
+MIXED = {
+    "cube-504": lambda: fc.varcoef((9, 8, 7), seed=3),
+    "line-1030": lambda: stencil(1030, 1, LINE, 2),
+    "star-132000": lambda: stencil(440, 300, STAR, 7),
+    "cube-262144": lambda: fc.varcoef((64, 64, 64), seed=8, permute=False),
+    "cube-300k": lambda: fc.varcoef((67, 61, 75), seed=8, permute=False),
+    "cube-1.3M": lambda: fc.varcoef((110, 109, 111), seed=10, permute=False),
+    "cube-2M": lambda: fc.varcoef((128, 128, 127), seed=11, permute=False),
+}
+
+
+@pytest.mark.parametrize("name", list(MIXED))
+def test_resident_mixed_equals_launches(fv, monkeypatch, name):
+    """The FP32 iterations between two FP64 updates in one launch: bitwise the
+    launches' results (odd and even update periods, int32 columns too), also
+    when the team is given no time to come together."""
+    import torch
+
+    case = MIXED[name]()
+    for col16 in ("1", "0"):
+        monkeypatch.setenv("FVPCG_COL16", col16)
+        dc = DevCase(case, fp32_copy=True)
+        for every, tol, maxit in ((16, 1e-9, 160), (7, 0.0, 21)):
+            got = []
+            for mode in ("launches", "resident", "no-time"):
+                say("resident mixed", name, col16, every, mode)
+                monkeypatch.setenv("FVPCG_RESIDENT", "0" if mode == "launches" else "1")
+                monkeypatch.setenv("FVPCG_RESIDENT_MEET_MS", "0" if mode == "no-time" else "20")
+                x, st = fv.solve_mixed_reliable(dc.A, dc.b, tol=tol, update_every=every, maxit=maxit)
+                got.append((x, st))
+            (xa, sa) = got[0]
+            for xb, sb in got[1:]:
+                for k in ("iters", "outer_iters", "status", "b_norm", "r0_norm", "rel_res"):
+                    assert sa[k] == sb[k], k
+                assert torch.equal(xa, xb)
+        dc.close()

@@ -115,6 +115,15 @@ __device__ __forceinline__ T get_agent(const T* p, int i) {
     return __hip_atomic_load((const T*)((const char*)p + (unsigned)i * (unsigned)sizeof(T)), __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
 }
+// Plain accesses (own rows) addressed alike.
+template <typename T>
+__device__ __forceinline__ void put_plain(T* p, int i, T v) {
+    *(T*)((char*)p + (unsigned)i * (unsigned)sizeof(T)) = v;
+}
+template <typename T>
+__device__ __forceinline__ T get_plain(const T* p, int i) {
+    return *(const T*)((const char*)p + (unsigned)i * (unsigned)sizeof(T));
+}
 // The wave's earlier stores have completed.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -409,10 +418,31 @@ __device__ __forceinline__ void res_pipe_step(ResScalars& y, double gamma, doubl
     y.beta = beta;
 }
 
+// A row index the compiler does not keep in a register from one pass to the
+// next.
+__device__ __forceinline__ int res_row(int c) {
+    asm volatile("" : "+v"(c));
+    return c;
+}
+
 // The k-th row of this thread and whether the system has it.
 #define RES_ROWS(k, c)                                              \
     _Pragma("unroll") for (int k = 0; k < RPT; ++k)                 \
-        if (const int c = sys.c0 + (k * t.size + t.rank) * BS + (int)threadIdx.x; c < sys.c1)
+        if (const int c = res_row(sys.c0 + (k * t.size + t.rank) * BS + (int)threadIdx.x); c < sys.c1)
+
+// Rows of an iteration are taken GR at a time: the gathers of a group are issued
+// together, before any of its arithmetic and outside any branch (a row past
+// the system's end reads the last row's entries and is then left out), so a
+// wave waits for memory once per group and not once per row.
+// RES_BASE starts a pass over the rows: the thread's first row, opaque to the
+// compiler, which would otherwise form every row's indices and addresses once
+// before the iterations and keep them in registers.
+#define RES_BASE                                                             \
+    const int base_ = res_row(sys.c0 + t.rank * BS + (int)threadIdx.x)
+#define RES_ROW(k, c, cx)                                                    \
+    const int c = base_ + (k) * t.size * BS;                                  \
+    const int cx = c < sys.c1 ? c : sys.c1 - 1
+constexpr int res_group(int rpt) { return rpt <= 4 ? rpt : 2; }
 
 // LDS of a resident solve: four vectors where registers cannot hold them
 // (above 4 rows per thread at 512 threads, 2 at 1024), or the two exchange
@@ -453,15 +483,20 @@ __device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, 
     Exchange<BS, RPT, ONE> e(sys, lds);
     RowCols<WT, CI> col[RPT];
     double d[RPT], r[RPT], w[RPT];
-    [[maybe_unused]] double u[LIT ? RPT : 1], q[LIT ? RPT : 1];
+    [[maybe_unused]] double u[LIT ? RPT : 1], qv[LIT ? RPT : 1];
     Store<BS, RPT, L> z(lds), s(lds + RPT * BS), p(lds + 2 * RPT * BS), x(lds + 3 * RPT * BS);
     // r = b - A x through buffer 1, (b, b)
     Sums<BS, 1, RPT, ONE> sb;
+    RES_BASE;
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+        RES_ROW(k, c, cx);
+        col[k].load(sys.col, sys.n, cx);
+        d[k] = sys.d[cx];
+    }
     RES_ROWS(k, c) {
-        col[k].load(sys.col, sys.n, c);
-        const double bc = sys.b[c], dc = sys.d[c], xc = sys.x[c];
+        const double bc = sys.b[c], dc = d[k], xc = sys.x[c];
         const double rc = bc - res_gather<WT, CI>(col[k], sys.val, sys.n, c, [&](int j) { return sys.x[j]; }, dc * xc);
-        d[k] = dc;
         r[k] = rc;
         x.set(k, xc);
         z.set(k, 0.0);
@@ -469,7 +504,7 @@ __device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, 
         p.set(k, 0.0);
         if constexpr (LIT) {
             u[k] = JAC ? rc / dc : rc;
-            q[k] = 0.0;
+            qv[k] = 0.0;
         }
         e.put(1, c, rc);
         sb.add(k, 0, bc * bc);
@@ -514,24 +549,35 @@ __device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, 
         const int in = it & 1;
         const double alpha = y.alpha, beta = y.beta;
         Sums<BS, 3, RPT, ONE> sa;
-        RES_ROWS(k, c) {
-            double g[WT];
-            if (RPT > 3) col[k].pin();
+        constexpr int GR = res_group(RPT);
+        RES_BASE;
 #pragma unroll
-            for (int i = 0; i < WT; ++i) g[i] = e.get(in, col[k].at(i, c));
+        for (int k0 = 0; k0 < RPT; k0 += GR) {
+        double g[GR][WT];
+#pragma unroll
+        for (int q = 0; q < GR; ++q) {
+            RES_ROW(k0 + q, c, cx);
+            if (RPT > 3) col[k0 + q].pin();
+#pragma unroll
+            for (int i = 0; i < WT; ++i) g[q][i] = e.get(in, col[k0 + q].at(i, cx));
+        }
+#pragma unroll
+        for (int k = k0; k < k0 + GR; ++k) {
+            RES_ROW(k, c, cx);
+            (void)cx;
             const double wc = w[k], dc = d[k];
             double nv = JAC ? wc : dc * wc;
 #pragma unroll
-            for (int i = 0; i < WT; ++i) nv = fma(val[k][i], g[i], nv);
+            for (int i = 0; i < WT; ++i) nv = fma(val[k][i], g[k - k0][i], nv);
             const double zc = nv + beta * z.get(k);
             const double wn = wc - alpha * zc;
-            e.put(in ^ 1, c, wn);
+            if (c < sys.c1) e.put(in ^ 1, c, wn);
             const double sc = wc + beta * s.get(k);
             double rc = r[k];
             double uc;
             if constexpr (LIT) {
                 const double mc = JAC ? wc / dc : wc;
-                q[k] = mc + beta * q[k];
+                qv[k] = mc + beta * qv[k];
                 uc = u[k];
             } else {
                 uc = JAC ? rc / dc : rc;
@@ -545,14 +591,17 @@ __device__ __forceinline__ void resident_pipe(const ResSystem& sys, ResTeam& t, 
             r[k] = rc;
             w[k] = wn;
             if constexpr (LIT) {
-                uc -= alpha * q[k];
+                uc -= alpha * qv[k];
                 u[k] = uc;
             } else {
                 uc = JAC ? rc / dc : rc;
             }
-            sa.add(k, 0, rc * uc);
-            sa.add(k, 1, wn * uc);
-            sa.add(k, 2, rc * rc);
+            if (c < sys.c1) {
+                sa.add(k, 0, rc * uc);
+                sa.add(k, 1, wn * uc);
+                sa.add(k, 2, rc * rc);
+            }
+        }
         }
         double a[3];
         ok = sa.finish(t, a);
@@ -597,8 +646,13 @@ __device__ __forceinline__ void resident_cg(const ResSystem& sys, ResTeam& t, do
     Store<BS, RPT, L> x(lds), r(lds + RPT * BS), p(lds + 2 * RPT * BS), d(lds + 3 * RPT * BS);
     // r = b - A x, z = M^-1 r, p = z
     Sums<BS, 3, RPT, ONE> s0;
+    RES_BASE;
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+        RES_ROW(k, c, cx);
+        col[k].load(sys.col, sys.n, cx);
+    }
     RES_ROWS(k, c) {
-        col[k].load(sys.col, sys.n, c);
         const double bc = sys.b[c], dc = sys.d[c], xc = sys.x[c];
         double g[WT];
 #pragma unroll
@@ -647,21 +701,24 @@ __device__ __forceinline__ void resident_cg(const ResSystem& sys, ResTeam& t, do
         const bool first = it == 0;
         // q = A p; delta = (p, q)
         Sums<BS, 1, RPT, ONE> s1;
-        RES_ROWS(k, c) {
+        RES_BASE;
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            RES_ROW(k, c, cx);
             double gz[WT], gp[WT];
             if (RPT > 1) col[k].pin();
 #pragma unroll
             for (int i = 0; i < WT; ++i) {
-                const int j = col[k].at(i, c);
+                const int j = col[k].at(i, cx);
                 gz[i] = e.get(0, j);
-                gp[i] = first ? 0.0 : e.get(1, j);
+                gp[i] = e.get(1, j);  // zeros before the first iteration
             }
             const double pc = p.get(k);
             double qc = d.get(k) * pc;
 #pragma unroll
             for (int i = 0; i < WT; ++i) qc = fma(val[k][i], first ? gz[i] : fma(beta, gp[i], gz[i]), qc);
             q[k] = qc;
-            s1.add(k, 0, pc * qc);
+            if (c < sys.c1) s1.add(k, 0, pc * qc);
         }
         double a1[1];
         ok = s1.finish(t, a1);
@@ -734,8 +791,9 @@ __device__ __forceinline__ void resident_cg(const ResSystem& sys, ResTeam& t, do
 // A run of FP32 folded pipelined iterations of the mixed-precision solve
 // (solve.hip, between two FP64 updates): the recurrence vectors are read from
 // memory at the start and written back at the end, the iterations between
-// keep them on chip, r, w, the values and the columns in registers, z, s, p and
-// the correction c in LDS.  d comes from the L2 (4 bytes a row).  The scalars
+// keep them on chip, w, the values and the columns in registers, z, s, p and r
+// in LDS.  d and the correction, which only its own row reads, come from the L2
+// (4 and 8 bytes a row).  The scalars
 // are those of `st`, as pipe_scalars steps them; member 0 writes them back.
 // A team that does not come together sets st_skip->done = kResNoTeam, which
 // makes the update kernels that follow do nothing; a wait given up sets
@@ -750,18 +808,21 @@ __device__ __forceinline__ void resident_pipe32(const PipeVec<float>& a, int n, 
         int c0, c1;
     } sys{0, n};
     RowCols<WT, CI> col[RPT];
-    float val[RPT][WT], r[RPT], w[RPT];
-    Store<BS, RPT, true, float> z(lds), s(lds + RPT * BS), p(lds + 2 * RPT * BS), x(lds + 3 * RPT * BS);
-    RES_ROWS(k, c) {
-        col[k].load(a.col, (size_t)n, c);
+    float val[RPT][WT], w[RPT];
+    Store<BS, RPT, true, float> z(lds), s(lds + RPT * BS), p(lds + 2 * RPT * BS), r(lds + 3 * RPT * BS);
+    RES_BASE;
 #pragma unroll
-        for (int i = 0; i < WT; ++i) val[k][i] = ld_once(a.val + (size_t)i * n + c);
-        r[k] = a.r[c];
-        w[k] = a.w_in[c];
-        z.set(k, a.z[c]);
-        s.set(k, a.s[c]);
-        p.set(k, a.p[c]);
-        x.set(k, a.x[c]);
+    for (int k = 0; k < RPT; ++k) {
+        RES_ROW(k, c, cx);
+        (void)c;
+        col[k].load(a.col, (size_t)n, cx);
+#pragma unroll
+        for (int i = 0; i < WT; ++i) val[k][i] = ld_once(a.val + (size_t)i * n + cx);
+        w[k] = a.w_in[cx];
+        r.set(k, a.r[cx]);
+        z.set(k, a.z[cx]);
+        s.set(k, a.s[cx]);
+        p.set(k, a.p[cx]);
     }
     ResScalars y;
     y.gamma = st->gamma;
@@ -782,34 +843,51 @@ __device__ __forceinline__ void resident_pipe32(const PipeVec<float>& a, int n, 
         float* w_out = (it & 1) ? e0 : a.w_out;
         const float alpha = (float)y.alpha, beta = (float)y.beta;
         Sums<BS, 3, RPT, false> sa;
-        RES_ROWS(k, c) {
-            float g[WT];
-            col[k].pin();
+        constexpr int GR = res_group(RPT);
+        RES_BASE;
 #pragma unroll
-            for (int i = 0; i < WT; ++i) g[i] = get_agent(w_in, col[k].at(i, c));
-            const float dc = a.d[c];
+        for (int k0 = 0; k0 < RPT; k0 += GR) {
+        float g[GR][WT], dg[GR], xg[GR];
+#pragma unroll
+        for (int q = 0; q < GR; ++q) {
+            RES_ROW(k0 + q, c, cx);
+            (void)c;
+            col[k0 + q].pin();
+#pragma unroll
+            for (int i = 0; i < WT; ++i) g[q][i] = get_agent(w_in, col[k0 + q].at(i, cx));
+            dg[q] = get_plain(a.d, cx);
+            xg[q] = get_plain(a.x, cx);
+        }
+#pragma unroll
+        for (int k = k0; k < k0 + GR; ++k) {
+            RES_ROW(k, c, cx);
+            (void)cx;
+            const float dc = dg[k - k0];
             const float wc = w[k];
             float nv = wc;
 #pragma unroll
-            for (int i = 0; i < WT; ++i) nv = fma(val[k][i], g[i], nv);
+            for (int i = 0; i < WT; ++i) nv = fma(val[k][i], g[k - k0][i], nv);
             const float zc = nv + beta * z.get(k);
             const float wn = wc - alpha * zc;
-            put_agent(w_out, c, wn);
             const float sc = wc + beta * s.get(k);
-            float rc = r[k];
+            float rc = r.get(k);
             float uc = rc / dc;
             const float pc = uc + beta * p.get(k);
             p.set(k, pc);
-            x.set(k, x.get(k) + alpha * pc);
             rc -= alpha * sc;
             z.set(k, zc);
             s.set(k, sc);
-            r[k] = rc;
+            r.set(k, rc);
             w[k] = wn;
             uc = rc / dc;
-            sa.add(k, 0, (double)rc * (double)uc);
-            sa.add(k, 1, (double)wn * (double)uc);
-            sa.add(k, 2, (double)rc * (double)rc);
+            if (c < sys.c1) {
+                put_agent(w_out, c, wn);
+                put_plain(a.x, c, xg[k - k0] + alpha * pc);
+                sa.add(k, 0, (double)rc * (double)uc);
+                sa.add(k, 1, (double)wn * (double)uc);
+                sa.add(k, 2, (double)rc * (double)rc);
+            }
+        }
         }
         double q[3];
         ok = sa.finish(t, q);
@@ -823,11 +901,10 @@ __device__ __forceinline__ void resident_pipe32(const PipeVec<float>& a, int n, 
     // w lies where the launches would have left it (a stopped run leaves w as
     // its last iteration's; nobody reads it then)
     RES_ROWS(k, c) {
-        a.r[c] = r[k];
+        a.r[c] = r.get(k);
         a.z[c] = z.get(k);
         a.s[c] = s.get(k);
         a.p[c] = p.get(k);
-        a.x[c] = x.get(k);
     }
     if (t.rank == 0 && threadIdx.x == 0) {
         st->gamma = y.gamma;

@@ -44,6 +44,10 @@ __global__ __launch_bounds__(kResBsPipe) void k_res_batch_pipe(ResSystem sys, Re
         tm.k = 0;
         sys.c0 = bt.cell_off[task.x];
         sys.c1 = bt.cell_off[task.x + 1];
+        if (sys.c0 == sys.c1) {  // no rows: b = 0
+            if (threadIdx.x == 0) bt.out[task.x] = ResOut{0.0, 0.0, 0.0, 0.0, 0, 0, 0, FVPCG_OK, 1, 1};
+            continue;
+        }
         resident_pipe<RPT, WT, CI, JAC, false, false>(sys, tm, lds, bt.out + task.x);
         __syncthreads();
         if (!s_ok) return;

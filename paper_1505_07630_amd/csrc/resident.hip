@@ -105,6 +105,49 @@ ResPlan resident_plan(const fvpcg_mesh* m, int method) {
     return p;
 }
 
+ResPlan resident_plan_stream(const fvpcg_mesh* m) {
+    ResPlan p;
+    const char* env = getenv("FVPCG_RESIDENT");
+    if (env && env[0] == '0') return p;
+    if (m->WT > 8 || m->n < 1 || m->device < 0 || m->device >= kMaxDevices) return p;
+    const DeviceInfo& info = device_info(m->device);
+    const int tiles = (m->n + kResBsPipe - 1) / kResBsPipe;
+    const int g = std::min(tiles, kMaxGrid);  // geom_for's workgroups
+    const int per = (tiles + g - 1) / g;
+    if (per > kStreamTiles || g > info.cus || info.ticks_per_ms <= 0) return p;
+    p.block = kResBsPipe;
+    p.size = g;
+    p.rpt = per <= 16 ? 16 : per <= 32 ? 32 : 64;
+    return p;
+}
+
+int resident_stream_run(const fvpcg_mesh* m, const ResPlan& plan, const ResWork& w, const PipeVec<double>& a, bool jac,
+                        DevState* st, hipStream_t s, bool* done) {
+    *done = false;
+    const DeviceInfo& info = device_info(m->device);
+    std::unique_lock<std::mutex> lock(g_dev[m->device].teams, std::try_to_lock);
+    if (!lock.owns_lock()) return FVPCG_OK;  // another team has the GPU
+    int rc;
+    w.pinned->ok = 0;
+    if ((rc = resident_reset(w.slots, res_slots(plan.size), w.meet, w.abort_flag, nullptr, 0, s))) return rc;
+    ResTeam t{0, plan.size, w.slots, w.meet, w.abort_flag, nullptr,
+              (unsigned long long)(info.ticks_per_ms * resident_meet_ms()),
+              (unsigned long long)(info.ticks_per_ms * kResSpinMs), 0};
+    hipLaunchKernelGGL(res_kernel_stream(plan.rpt, m->WT, m->col16 != nullptr, jac), dim3(plan.size), dim3(plan.block), 0,
+                       s, a, m->n, t, st, w.pinned);
+    FV_LAUNCHED();
+    FV_HIP(hipStreamSynchronize(s));
+    if (w.pinned->ok) {
+        *done = true;
+        return FVPCG_OK;
+    }
+    int gave_up = 0;
+    FV_HIP(hipMemcpyAsync(&gave_up, w.abort_flag, sizeof(int), hipMemcpyDeviceToHost, s));
+    FV_HIP(hipStreamSynchronize(s));
+    if (gave_up) return set_error(FVPCG_DEVICE_ERROR, "pipelined CG: a wait between workgroups timed out");
+    return FVPCG_OK;
+}
+
 ResPlan resident_plan32(const fvpcg_mesh* m) {
     ResPlan p;
     const char* env = getenv("FVPCG_RESIDENT");

@@ -442,7 +442,7 @@ __device__ __forceinline__ int res_row(int c) {
 #define RES_ROW(k, c, cx)                                                    \
     const int c = base_ + (k) * t.size * BS;                                  \
     const int cx = c < sys.c1 ? c : sys.c1 - 1
-constexpr int res_group(int rpt) { return rpt <= 4 ? rpt : 2; }
+constexpr int res_group(int rpt) { return rpt % 2 ? 1 : 2; }
 
 // LDS of a resident solve: four vectors where registers cannot hold them
 // (above 4 rows per thread at 512 threads, 2 at 1024), or the two exchange
@@ -917,6 +917,164 @@ __device__ __forceinline__ void resident_pipe32(const PipeVec<float>& a, int n, 
         st->iter = y.iter;
         st->status = y.status;
         st->done = y.done ? 1 : 0;
+    }
+}
+
+// Folded pipelined CG of systems beyond what the chip holds whole (up to 64
+// tiles per member, 8.4M cells): the iterations of k_pipe_iter (solve.hip) in
+// one launch, with the matrix streamed and as many of the recurrence vectors
+// on chip as fit.  A thread has 64 doubles of registers for them, as four
+// vectors of 16 indexed by the (uniform) tile number, and 32 in LDS:
+//   up to 16 tiles (2.1M cells)  z, s, p and r in registers, x and d in LDS;
+//   up to 32 tiles (4.2M)        z and s in registers, p in LDS;
+//   up to 64 tiles (8.4M)        z in registers, s in LDS for 32 tiles.
+// Every resident vector saves its read and its write.  Per iteration, against
+// the launches (bandwidth-bound at 6.3 TB/s): 35.5 us against 62.7 at 2.1M
+// cells, 75 against 109 at 4.1M, 146 against 182 at 7.1M.  A row's loads are all
+// issued before its gathers are waited for: with r and p read after them 209 us
+// at 7.1M.  w is stored with agent
+// scope; its gathers go through the L2 caches (uncached they would fetch every
+// entry six times), so each member invalidates them after the reduction.  x in
+// memory is updated every second iteration (PairX), pending updates at the
+// end.  The scalars are those of `st`, read at the start and written back by
+// member 0, with out->ok = 1.
+using Tile16 = double __attribute__((ext_vector_type(16)));
+constexpr int kStreamTiles = 64, kStreamLdsTiles = 32;
+
+template <int NT, int WT, typename CI, bool JAC>
+__device__ __forceinline__ void resident_stream(const PipeVec<double>& a, int n, ResTeam& t, double* lds, DevState* st,
+                                                ResOut* out) {
+    constexpr int BS = kResBsPipe, CH = NT / 16;
+    static_assert(NT == 16 || NT == 32 || NT == 64, "16 tiles to a register vector");
+    constexpr bool kSReg = NT <= 32, kPR = NT == 16;  // s in registers; p, r in registers and x, d in LDS
+    // What the 256 MB last-level cache keeps from one iteration to the next: w
+    // and d, and the columns if they are int16 (85 MB at 7.08M cells), else r
+    // (57 MB, read and written; with int32 columns kept 172 us against 157).
+    constexpr bool kKeepCol = sizeof(CI) == 2;
+    Tile16 z[CH], s[kSReg ? CH : 1], p[kPR ? CH : 1], r[kPR ? CH : 1];
+    double* const l0 = lds + threadIdx.x;               // x | p | s
+    double* const l1 = lds + NT * BS + threadIdx.x;     // d (16 tiles only)
+    const int G = t.size, tiles = (n + BS - 1) / BS;
+    const int mine = t.rank < tiles ? (tiles - t.rank + G - 1) / G : 0;
+    const CI* __restrict__ col = (const CI*)a.col;
+#pragma unroll
+    for (int h = 0; h < CH; ++h) {
+        z[h] = 0.0;
+        if constexpr (kSReg) s[h] = 0.0;
+        if constexpr (kPR) p[h] = 0.0;
+    }
+    for (int k = 0; k < mine; ++k) {
+        const int c = (k * G + t.rank) * BS + (int)threadIdx.x;
+        const int cx = c < n ? c : n - 1;
+        if constexpr (kPR) {
+            r[0][k] = a.r[cx];
+            l0[k * BS] = a.x[cx];
+            l1[k * BS] = a.d[cx];
+        } else if constexpr (kSReg) {
+            l0[k * BS] = 0.0;
+        } else {
+            if (k < kStreamLdsTiles) l0[k * BS] = 0.0;
+        }
+    }
+    ResScalars y;
+    y.gamma = st->gamma;
+    y.alpha = st->alpha;
+    y.beta = st->beta;
+    y.alpha_old = st->alpha_old;
+    y.gamma_old = st->gamma_old;
+    y.tol_abs = st->tol_abs;
+    y.r0norm = st->r0norm;
+    y.rho = st->rho;
+    y.iter = st->iter;
+    const int maxit = st->maxit;
+    double* const e0 = const_cast<double*>(a.w_in);
+    const unsigned long long t0 = (unsigned long long)wall_clock64();
+    bool ok = true;
+    for (int it = 0; !y.done; ++it) {
+        const double* w_in = (it & 1) ? a.w_out : e0;
+        double* w_out = (it & 1) ? e0 : a.w_out;
+        const double alpha = y.alpha, beta = y.beta, alpha_prev = y.alpha_old;
+        const bool odd = (it & 1) != 0;
+        double q[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int h = 0; h < CH; ++h) {
+            const int m = min(16, mine - 16 * h);
+            for (int j = 0; j < m; ++j) {
+                const int k = 16 * h + j;
+                const int c = (k * G + t.rank) * BS + (int)threadIdx.x;
+                if (c >= n) continue;
+                // every load of the row before the gather's wait
+                const bool s_lds = !kSReg && 16 * h < kStreamLdsTiles;  // known per h
+                const double wc = w_in[c];
+                const double dc = kPR ? l1[k * BS] : a.d[c];
+                double rc = kPR ? r[h][j] : kKeepCol ? ld_once(a.r + c) : a.r[c];
+                const double pold = kPR ? p[h][j] : kSReg ? l0[k * BS] : ld_once(a.p + c);
+                const double so = kSReg ? s[h][j] : s_lds ? l0[k * BS] : ld_once(a.s + c);
+                double xc = 0.0;
+                if constexpr (!kPR)
+                    if (odd) xc = ld_once(a.x + c);
+                const double nv = row_gather<double, WT, CI, kKeepCol>(col, a.val, n, c, w_in, JAC ? wc : dc * wc);
+                const double zc = nv + beta * z[h][j];
+                z[h][j] = zc;
+                const double sc = wc + beta * so;
+                if constexpr (kSReg)
+                    s[h][j] = sc;
+                else if (s_lds)
+                    l0[k * BS] = sc;
+                else
+                    st_once(a.s + c, sc);
+                double uc = JAC ? rc / dc : rc;
+                const double pc = uc + beta * pold;
+                if constexpr (kPR) {
+                    p[h][j] = pc;
+                    l0[k * BS] = l0[k * BS] + alpha * pc;
+                } else {
+                    if constexpr (kSReg)
+                        l0[k * BS] = pc;
+                    else
+                        st_once(a.p + c, pc);
+                    if (odd) {
+                        const double xa = xc + alpha_prev * pold;
+                        st_once(a.x + c, xa + alpha * pc);
+                    }
+                }
+                rc -= alpha * sc;
+                const double wn = wc - alpha * zc;
+                if constexpr (kPR)
+                    r[h][j] = rc;
+                else if constexpr (kKeepCol)
+                    st_once(a.r + c, rc);
+                else
+                    a.r[c] = rc;
+                st_agent(w_out + c, wn);
+                uc = JAC ? rc / dc : rc;
+                q[0] += rc * uc;
+                q[1] += wn * uc;
+                q[2] += rc * rc;
+            }
+        }
+        ok = team_sum<BS, 3>(q, t);
+        if (!ok) return;
+        // the members' w: no stale copy in this XCD's caches
+        if (threadIdx.x < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __syncthreads();
+        res_pipe_step(y, q[0], q[1], q[2], false, maxit);
+    }
+    for (int k = 0; k < mine; ++k) {
+        const int c = (k * G + t.rank) * BS + (int)threadIdx.x;
+        if (c >= n) continue;
+        if constexpr (kPR)
+            a.x[c] = l0[k * BS];
+        else if (y.iter & 1)
+            a.x[c] += y.alpha * (kSReg ? l0[k * BS] : a.p[c]);
+    }
+    if (t.rank == 0 && threadIdx.x == 0) {
+        st->rho = y.rho;
+        st->iter = y.iter;
+        st->status = y.status;
+        st->done = 1;
+        out->it_ticks = (unsigned long long)wall_clock64() - t0;
+        out->ok = 1;
     }
 }
 

@@ -13,6 +13,7 @@ struct ResTeam;
 struct ResBatch;
 template <typename T>
 struct PipeVec;
+using ResStreamKernel = void (*)(PipeVec<double>, int, ResTeam, DevState*, ResOut*);
 using ResMixedKernel = void (*)(PipeVec<float>, int, int, ResTeam, DevState*, DevState*);
 using ResBatchKernel = void (*)(ResSystem, ResTeam, ResBatch);
 using ResKernel = void (*)(ResSystem, ResTeam, ResOut*);
@@ -49,6 +50,7 @@ ResPlan resident_plan(const fvpcg_mesh* m, int method);
 ResKernel res_kernel_pipe(const ResPlan& p, int wt, bool col16, bool jac);
 ResKernel res_kernel_cg(const ResPlan& p, int wt, bool col16, bool jac);
 ResMixedKernel res_kernel_mixed(int rpt, int wt, bool col16);
+ResStreamKernel res_kernel_stream(int nt, int wt, bool col16, bool jac);
 ResBatchKernel res_batch_pipe(int rpt, int wt, bool col16, bool jac);
 ResBatchKernel res_batch_cg(int rpt, int wt, bool col16, bool jac);
 double resident_meet_ms();
@@ -65,6 +67,13 @@ int resident_reset(double* slots, size_t count, unsigned* meet, int* abort_flag,
 ResPlan resident_plan32(const fvpcg_mesh* m);
 int resident_run32(const fvpcg_mesh* m, const ResPlan& plan, const ResWork& w, const PipeVec<float>& a, int iters,
                    DevState* st, DevState* st_skip, hipStream_t s);
+
+// The iterations of a larger folded pipelined solve in one launch
+// (resident_stream), the initial residual and first reduction done (st, a).
+// *done = false with FVPCG_OK: nothing was done, iterate by launches.
+ResPlan resident_plan_stream(const fvpcg_mesh* m);
+int resident_stream_run(const fvpcg_mesh* m, const ResPlan& plan, const ResWork& w, const PipeVec<double>& a, bool jac,
+                        DevState* st, hipStream_t s, bool* done);
 
 // *done = false with FVPCG_OK: not solved here, solve by launches (x is still
 // a valid starting vector); a negative code is an error.

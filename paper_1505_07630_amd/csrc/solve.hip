@@ -860,7 +860,7 @@ struct Clock {
 };
 
 int solve_core(const fvpcg_matrix* A, Work& w, const double* b, double* x, double tol, int maxit, int method,
-               int precond, hipStream_t s, fvpcg_stats* stats);
+               int precond, const ResPlan& stream, hipStream_t s, fvpcg_stats* stats);
 
 // The whole solve in one launch, where the system fits (resident_plan).
 int solve_resident(const fvpcg_matrix* A, const ResPlan& plan, Work& w, const double* b, double* x, double tol,
@@ -890,13 +890,19 @@ int solve(const fvpcg_matrix* A, const double* b, double* x, double tol, int max
     } else {
         if ((rc = work_need_pipe(w, method == FVPCG_PIPECG_LITERAL))) return rc;
     }
-    return solve_core(A, w, b, x, tol, maxit, method, precond, s, stats);
+    ResPlan stream;
+    if (method == FVPCG_PIPECG) {
+        stream = resident_plan_stream(A->mesh);
+        if (stream.rpt && (rc = work_need_resident(w, false))) return rc;
+    }
+    return solve_core(A, w, b, x, tol, maxit, method, precond, stream, s, stats);
 }
 
 namespace {
 
+// `stream`: how the pipelined iterations run in one launch (rpt 0: they do not)
 int solve_core(const fvpcg_matrix* A, Work& w, const double* b, double* x, double tol, int maxit, int method,
-               int precond, hipStream_t s, fvpcg_stats* stats) {
+               int precond, const ResPlan& stream, hipStream_t s, fvpcg_stats* stats) {
     const fvpcg_mesh* m = A->mesh;
     const int n = m->n;
     const bool jac = precond == FVPCG_PRECOND_JACOBI;
@@ -939,6 +945,7 @@ int solve_core(const fvpcg_matrix* A, Work& w, const double* b, double* x, doubl
     if ((rc = state_read(w, 0, &h, s))) return rc;
     std::chrono::steady_clock::time_point t_it0;
     if ((rc = clk.mark(w.t_it0, t_it0, s))) return rc;
+    bool streamed = false;
     if (h.zero_b) {
         FV_HIP(hipMemsetAsync(x, 0, sizeof(double) * (size_t)n, s));
     } else if (!h.done) {
@@ -960,7 +967,15 @@ int solve_core(const fvpcg_matrix* A, Work& w, const double* b, double* x, doubl
             });
         } else {
             const bool lit = method == FVPCG_PIPECG_LITERAL;
-            rc = iterate(w, 0, maxit, s, [&](int it) {
+            rc = FVPCG_OK;
+            if (stream.rpt) {
+                const ResWork rw{nullptr, nullptr, w.res_slots, w.res_meet, reinterpret_cast<int*>(w.res_meet + 1),
+                                 nullptr, w.res_pinned};
+                const PipeVec<double> a{mesh_cols(m), jac ? A->val_cs : A->val, A->d, w.w[0], w.w[1], w.z,
+                                        w.s, w.p, x, w.r, nullptr, nullptr};
+                rc = resident_stream_run(m, stream, rw, a, jac, st, s, &streamed);
+            }
+            if (!rc && !streamed) rc = iterate(w, 0, maxit, s, [&](int it) {
                 PipeVec<double> a{mesh_cols(m), jac ? A->val_cs : A->val, A->d, w.w[it & 1], w.w[(it + 1) & 1], w.z,
                                   w.s, w.p, x, w.r, w.u, w.qq};
                 FV_LAYOUT(
@@ -975,7 +990,7 @@ int solve_core(const fvpcg_matrix* A, Work& w, const double* b, double* x, doubl
         }
         if (rc) return rc;
     }
-    if (method == FVPCG_PIPECG && !h.zero_b && !h.done) {
+    if (method == FVPCG_PIPECG && !h.zero_b && !h.done && !streamed) {
         hipLaunchKernelGGL((k_x_fixup<kBsPipe>), dim3(gp.grid), dim3(kBsPipe), 0, s, x, w.p, n, gp, st);
         FV_LAUNCHED();
     }
@@ -1084,7 +1099,7 @@ int solve_noalloc(const fvpcg_matrix* A, const double* b, double* x, double tol,
         rc = solve_resident(A, plan, w, b, x, tol, maxit, precond, s, stats, &done);
         if (rc < 0 || done) return rc;
     }
-    return solve_core(A, w, b, x, tol, maxit, method, precond, s, stats);
+    return solve_core(A, w, b, x, tol, maxit, method, precond, ResPlan(), s, stats);
 }
 
 int solve_mixed(const fvpcg_matrix* A, const double* b, double* x, double outer_tol, double inner_tol, int max_outer,

@@ -200,6 +200,45 @@ def test_resident_threads_and_streams(fv, monkeypatch):
         dc.close()
 
 
+# ------------------------------------------------------------------ beyond what the chip holds whole
+
+STREAMED = {
+    "cube-830k-int32": (lambda: fc.varcoef((94, 94, 94), seed=12, permute=False), "0"),
+    "star-600k": (lambda: stencil(800, 750, STAR, 13), "1"),
+    "line-1.05M": (lambda: stencil(1050001, 1, LINE, 14), "1"),
+    "cube-2097152": (lambda: fc.varcoef((128, 128, 128), seed=15, permute=False), "1"),
+    "cube-2.1M": (lambda: fc.varcoef((129, 128, 128), seed=16, permute=False), "1"),
+    "cube-4.2M-int32": (lambda: fc.varcoef((161, 162, 162), seed=17, permute=False), "0"),
+    "cube-4.2M": (lambda: fc.varcoef((161, 162, 162), seed=17, permute=False), "1"),
+}
+
+
+@pytest.mark.parametrize("name", list(STREAMED))
+def test_streamed_equals_launches(fv, monkeypatch, name):
+    """Systems whose matrix is streamed, their vectors partly on chip: bitwise
+    the launches' results (odd and even counts, a warm start that converges, no
+    preconditioner), also when the team is given no time to come together."""
+    import torch
+
+    make, col16 = STREAMED[name]
+    monkeypatch.setenv("FVPCG_COL16", col16)
+    case = make()
+    dc = DevCase(case)
+    x0 = to_dev(np.random.default_rng(1).uniform(-1, 1, case.n))
+    for kw in (dict(tol=0.0, maxit=8), dict(tol=0.0, maxit=7, x0=x0, precond="none"), dict(tol=3e-2, maxit=400)):
+        got = []
+        for mode in ("launches", "resident", "no-time"):
+            say("streamed", name, mode, kw.get("tol"), kw["maxit"])
+            monkeypatch.setenv("FVPCG_RESIDENT_MEET_MS", "0" if mode == "no-time" else "20")
+            got.append(solve(fv, monkeypatch, dc, mode != "launches", **kw))
+        (xa, sa) = got[0]
+        for xb, sb in got[1:]:
+            for k in ("iters", "status", "b_norm", "r0_norm", "rel_res", "true_rel_res"):
+                assert sa[k] == sb[k], k
+            assert torch.equal(xa, xb)
+    dc.close()
+
+
 # ------------------------------------------------------------------ batches
 
 BATCHES = {

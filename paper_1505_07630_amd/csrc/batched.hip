@@ -997,6 +997,11 @@ void resident_batch_plan(const fvpcg_batch* bt, int bs, ResBatchPlan& p) {
     std::vector<int> order(bt->nsys);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return tiles[x] > tiles[y]; });
+    // workgroups in XCD order (b % 8, then b), so that a team's members, and
+    // among them those with neighbouring tiles, share an XCD (see res_rank)
+    std::vector<int> wg;
+    for (int x = 0; x < 8; ++x)
+        for (int b = x; b < grid; b += 8) wg.push_back(b);
     std::vector<std::pair<double, int>> free_at(grid);
     for (int b = 0; b < grid; ++b) free_at[b] = {0.0, b};
     std::vector<std::vector<int4>> lists(grid);
@@ -1004,9 +1009,12 @@ void resident_batch_plan(const fvpcg_batch* bt, int bs, ResBatchPlan& p) {
     for (int i : order) {
         const int g = std::max(1, (tiles[i] + rpt - 1) / rpt);
         std::partial_sort(free_at.begin(), free_at.begin() + g, free_at.end());
-        const double end = free_at[g - 1].first + std::cbrt((double)(bt->cell_off[i + 1] - bt->cell_off[i]) + 1.0);
+        std::sort(free_at.begin(), free_at.begin() + g, [](auto& x, auto& y) { return x.second < y.second; });
+        double start = 0.0;
+        for (int r = 0; r < g; ++r) start = std::max(start, free_at[r].first);
+        const double end = start + std::cbrt((double)(bt->cell_off[i + 1] - bt->cell_off[i]) + 1.0);
         for (int r = 0; r < g; ++r) {
-            lists[free_at[r].second].push_back(make_int4(i, r, g, offset));
+            lists[wg[free_at[r].second]].push_back(make_int4(i, r, g, offset));
             free_at[r].first = end;
         }
         offset += g;

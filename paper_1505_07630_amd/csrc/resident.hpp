@@ -127,6 +127,16 @@ __device__ __forceinline__ T get_plain(const T* p, int i) {
 // The wave's earlier stores have completed.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Member number of workgroup b of G.  The hardware deals workgroups to the 8
+// XCDs in turn; the members of one XCD take consecutive numbers, hence
+// consecutive tiles, so most entries a row gathers were stored by its own XCD
+// (levels order: 11.3 -> 9.8 us per iteration at 1M cells, 6.6 -> 5.6 at 262k;
+// the sums are taken by member number either way).
+__device__ __forceinline__ int res_rank(int b, int G) {
+    const int x = b & 7, q = G >> 3, rem = G & 7;
+    return x * q + (x < rem ? x : rem) + (b >> 3);
+}
+
 // True once the whole team runs; false if it did not come together in time.
 // The word counts arrivals; a member whose time is up sets the abort bit
 // unless the last one has arrived meanwhile, so all members agree.

@@ -6,15 +6,16 @@ namespace fvpcg {
 
 namespace {
 
-// A team on its own launch: member r is workgroup r.
+// A team on its own launch.
 template <int RPT, int WT, typename CI, bool JAC, bool ONE>
 __global__ __launch_bounds__(kResBsCg) void k_res_cg(ResSystem sys, ResTeam t, ResOut* out) {
     __shared__ double lds[ResLds<kResBsCg, RPT, ONE>::doubles];
     __shared__ int s_ok;
     if (threadIdx.x == 0) s_ok = 1;
-    t.rank = (int)blockIdx.x;
+    t.rank = res_rank((int)blockIdx.x, t.size);
     t.ok = &s_ok;
     if (ONE) {
+        t.rank = 0;
         t.size = 1;
         __syncthreads();
     } else if (!team_meet(t)) {

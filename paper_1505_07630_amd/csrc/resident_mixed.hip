@@ -6,14 +6,14 @@ namespace fvpcg {
 
 namespace {
 
-// A team on its own launch: member r is workgroup r.
+// A team on its own launch.
 template <int RPT, int WT, typename CI>
 __global__ __launch_bounds__(kResBsMixed) void k_res_pipe32(PipeVec<float> a, int n, int iters, ResTeam t, DevState* st,
                                                             DevState* st_skip) {
     __shared__ float lds[4 * RPT * kResBsMixed];
     __shared__ int s_ok;
     if (threadIdx.x == 0) s_ok = 1;
-    t.rank = (int)blockIdx.x;
+    t.rank = (int)blockIdx.x;  // numbered by XCD (res_rank) 3% slower here
     t.ok = &s_ok;
     if (st->done || st_skip->done) return;  // as every member sees them
     if (!team_meet(t)) {

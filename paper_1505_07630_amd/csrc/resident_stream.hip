@@ -11,7 +11,7 @@ __global__ __launch_bounds__(kResBsPipe) void k_res_stream(PipeVec<double> a, in
     __shared__ double lds[(NT == 64 ? kStreamLdsTiles : 32) * kResBsPipe];
     __shared__ int s_ok;
     if (threadIdx.x == 0) s_ok = 1;
-    t.rank = (int)blockIdx.x;
+    t.rank = res_rank((int)blockIdx.x, t.size);
     t.ok = &s_ok;
     if (!team_meet(t)) return;
     resident_stream<NT, WT, CI, JAC>(a, n, t, lds, st, out);

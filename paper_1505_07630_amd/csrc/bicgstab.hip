@@ -36,50 +36,10 @@
 // values are still loaded (every load of a row is issued before the
 // arithmetic), but nothing is computed into its sums or stored for it.  So
 // every component's iterates are those of its own single solve.
-#include "handles.hpp"
-#include "rows.hpp"
+#include "bicgstab.hpp"
+#include "resident.hpp"
 
 namespace fvpcg {
-
-// Scalars of one component's recurrences, written by the last workgroup of
-// each kernel.
-struct alignas(128) BiState {
-    double rho;      // (rhat, r) of the current iterate
-    double rho_next; // (rhat, r') of the iterate being formed
-    double alpha;    // alpha, omega, beta are 0 once the component has stopped
-    double omega;    // 0 after a half-step exit
-    double beta;
-    double rr;       // (r, r)
-    double bnorm;
-    double tol_abs;  // tol * ||b||
-    double r0norm;
-    double true_rr;  // ||b - A x||^2 at exit
-    int32_t iter;    // iterations that formed alpha
-    int32_t maxit;
-    int32_t done;
-    int32_t status;
-    int32_t zero_b;
-    int32_t half;    // ||s|| met the tolerance: x += alpha phat ends the solve
-    uint32_t ticket; // reduction ticket (component 0's serves all)
-    uint32_t pad;
-};
-
-constexpr int kBiMaxRhs = 4;
-
-struct BiWork {
-    int n = 0;
-    int nr = 0;                  // components the vectors are sized for
-    double* r = nullptr;         // [nr][n] each
-    double* rhat = nullptr;
-    double* p = nullptr;
-    double* v = nullptr;
-    double* t = nullptr;
-    double* partials = nullptr;  // [5 kBiMaxRhs][kBiMaxGrid]
-    BiState* st = nullptr;       // [kBiMaxRhs]
-    BiState* hst = nullptr;      // pinned [3][kBiMaxRhs]: two chunk slots and the reset image
-    hipEvent_t ev[2] = {nullptr, nullptr};
-    hipEvent_t t_begin = nullptr, t_end = nullptr, t_it0 = nullptr, t_it1 = nullptr;
-};
 
 namespace {
 
@@ -111,10 +71,6 @@ Geom bi_geom(int n, int cap = kBiMaxGrid) {
     return {g, kBsBi};
 }
 
-// s = r - alpha v with one rounding: the row that owns an entry and every
-// row that gathers it compute the same bits.
-__device__ __forceinline__ double bi_half(double r, double v, double alpha) { return fma(-alpha, v, r); }
-
 // True while any component still iterates; act[k] for each.
 template <int NR>
 __device__ __forceinline__ bool bi_active(const BiState* st, bool (&act)[NR]) {
@@ -125,36 +81,6 @@ __device__ __forceinline__ bool bi_active(const BiState* st, bool (&act)[NR]) {
         any |= act[k];
     }
     return any;
-}
-
-// The component's exit: status, and zero scalars so later launches leave it
-// untouched.
-__device__ __forceinline__ void bi_stop(BiState* st, int status) {
-    st->done = 1;
-    st->status = status;
-    st->alpha = 0.0;
-    st->omega = 0.0;
-    st->beta = 0.0;
-}
-
-// acc[k] += sum_i m[i] * v[k][col_i] over the WT slots (j, m) of row c for
-// the components still iterating (v component-major).  Every component's
-// values are loaded before any is used, so all the row's gathers are in
-// flight at once; the loads of a stopped component are made and discarded.
-template <int WT, typename CI, int NR>
-__device__ __forceinline__ void gather_v(const CI (&j)[WT], const double (&m)[WT], int n, int c,
-                                         const double* __restrict__ v, const bool (&act)[NR], double (&acc)[NR]) {
-    double g[NR][WT];
-#pragma unroll
-    for (int k = 0; k < NR; ++k)
-#pragma unroll
-        for (int i = 0; i < WT; ++i) g[k][i] = v[(size_t)k * n + slot_abs(j[i], c)];
-#pragma unroll
-    for (int k = 0; k < NR; ++k) {
-        if (!act[k]) continue;
-#pragma unroll
-        for (int i = 0; i < WT; ++i) acc[k] += m[i] * g[k][i];
-    }
 }
 
 // Same with s = r - alpha v formed from the gathered r and v.
@@ -175,7 +101,7 @@ __device__ __forceinline__ void gather_s(const CI (&j)[WT], const double (&m)[WT
     for (int k = 0; k < NR; ++k) {
         if (!act[k]) continue;
 #pragma unroll
-        for (int i = 0; i < WT; ++i) acc[k] += m[i] * bi_half(gr[k][i], gv[k][i], alpha[k]);
+        for (int i = 0; i < WT; ++i) acc[k] = fma(m[i], bi_half(gr[k][i], gv[k][i], alpha[k]), acc[k]);
     }
 }
 
@@ -280,14 +206,7 @@ __global__ __launch_bounds__(BS) void k_bi_pv(const CI* __restrict__ col, const 
     if (device_reduce<BS, NR>(acc, partials, &st[0].ticket, blk, g.grid, t) && threadIdx.x == 0) {
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
-            if (!act[k]) continue;
-            const double rv = t[k];
-            const double alpha = st[k].rho / rv;
-            if (rv == 0.0 || !isfinite(alpha)) {
-                bi_stop(&st[k], FVPCG_BREAKDOWN);
-                continue;
-            }
-            st[k].alpha = alpha;
+            if (act[k]) bi_step_pv(&st[k], t[k]);
         }
     }
 }
@@ -366,25 +285,7 @@ __global__ __launch_bounds__(BS) void k_bi_st(const CI* __restrict__ col, const 
     if (device_reduce<BS, 5 * NR>(acc, partials, &st[0].ticket, blk, g.grid, tot) && threadIdx.x == 0) {
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
-            if (!act[k]) continue;
-            BiState* sk = &st[k];
-            const double* q = tot + 5 * k;
-            if (sqrt(q[2]) <= sk->tol_abs) {
-                sk->omega = 0.0;
-                sk->beta = 0.0;
-                sk->half = 1;
-                continue;
-            }
-            const double omega = q[0] / q[1];
-            if (q[1] == 0.0 || omega == 0.0 || !isfinite(omega)) {
-                sk->iter = sk->iter + 1;
-                bi_stop(sk, FVPCG_BREAKDOWN);
-                continue;
-            }
-            const double rho_next = q[3] - omega * q[4];
-            sk->omega = omega;
-            sk->rho_next = rho_next;
-            sk->beta = (rho_next / sk->rho) * (alpha[k] / omega);
+            if (act[k]) bi_step_st(&st[k], tot + 5 * k);
         }
     }
 }
@@ -426,11 +327,11 @@ __global__ __launch_bounds__(BS) void k_bi_update(double* __restrict__ x, double
             if (!act[k]) continue;
             const size_t e = (size_t)k * n + c;
             const double sc = SP ? rc[k] : bi_half(rc[k], vc[k], alpha[k]);
-            const double dx = alpha[k] * pc[k] + omega[k] * sc;
+            const double dx = fma(alpha[k], pc[k], omega[k] * sc);
             st_once(x + e, xc[k] + (JAC ? dx / dc : dx));
-            const double rn = sc - omega[k] * tc[k];
+            const double rn = fma(-omega[k], tc[k], sc);
             r[e] = rn;
-            p[e] = rn + beta[k] * (pc[k] - omega[k] * vc[k]);
+            p[e] = fma(beta[k], fma(-omega[k], vc[k], pc[k]), rn);
             acc[k] += rn * rn;
         }
     }
@@ -438,25 +339,7 @@ __global__ __launch_bounds__(BS) void k_bi_update(double* __restrict__ x, double
     if (device_reduce<BS, NR>(acc, partials, &st[0].ticket, blk, g.grid, tot) && threadIdx.x == 0) {
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
-            if (!act[k]) continue;
-            BiState* sk = &st[k];
-            const int it = sk->iter + 1;
-            sk->iter = it;
-            sk->rr = tot[k];
-            if (sk->half || sqrt(tot[k]) <= sk->tol_abs) {
-                bi_stop(sk, FVPCG_OK);
-                continue;
-            }
-            if (it >= sk->maxit) {
-                bi_stop(sk, FVPCG_NOT_CONVERGED);
-                continue;
-            }
-            const double rho = sk->rho_next;
-            if (rho == 0.0 || !isfinite(rho) || !isfinite(beta[k])) {
-                bi_stop(sk, FVPCG_BREAKDOWN);
-                continue;
-            }
-            sk->rho = rho;
+            if (act[k]) bi_step_update(&st[k], tot[k]);
         }
     }
 }
@@ -494,6 +377,9 @@ void bi_release(BiWork* w) {
     dev_free(w->v);
     dev_free(w->t);
     dev_free(w->partials);
+    dev_free(w->slots);
+    dev_free(w->meet);
+    if (w->out) (void)hipHostFree(w->out);
     dev_free(w->st);
     if (w->hst) (void)hipHostFree(w->hst);
     for (auto ev : w->ev)
@@ -513,10 +399,13 @@ int bi_alloc(BiWork* w, int n, int nr) {
         (rc = dev_alloc(&w->p, m, "BiCGSTAB p")) || (rc = dev_alloc(&w->v, m, "BiCGSTAB v")) ||
         (rc = dev_alloc(&w->t, m, "BiCGSTAB t")) ||
         (rc = dev_alloc(&w->partials, (size_t)5 * kBiMaxRhs * kBiMaxGrid, "BiCGSTAB partials")) ||
-        (rc = dev_alloc(&w->st, kBiMaxRhs, "BiCGSTAB state")))
+        (rc = dev_alloc(&w->slots, bicg_slots(), "BiCGSTAB team slots")) ||
+        (rc = dev_alloc(&w->meet, 2, "BiCGSTAB rendezvous")) || (rc = dev_alloc(&w->st, kBiMaxRhs, "BiCGSTAB state")))
         return rc;
     FV_HIP(hipMemset(w->st, 0, sizeof(BiState) * kBiMaxRhs));
-    hipError_t e = hipHostMalloc((void**)&w->hst, 3 * kBiMaxRhs * sizeof(BiState), hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void**)&w->out, sizeof(ResOut), hipHostMallocDefault);
+    if (e != hipSuccess) w->out = nullptr;
+    if (e == hipSuccess) e = hipHostMalloc((void**)&w->hst, 3 * kBiMaxRhs * sizeof(BiState), hipHostMallocDefault);
     if (e != hipSuccess) {
         w->hst = nullptr;
         return set_error(FVPCG_OUT_OF_MEMORY, "pinned host allocation failed: %s", hipGetErrorString(e));
@@ -629,7 +518,9 @@ int bi_solve(const fvpcg_matrix* A, const double* b, double* x, double tol, int 
     for (int k = 0; k < NR; ++k)
         if (h[k].zero_b) FV_HIP(hipMemsetAsync(x + (size_t)k * n, 0, sizeof(double) * (size_t)n, s));
     FV_HIP(hipEventRecord(w.t_it0, s));
-    if (!bi_all_done(h, NR)) {
+    bool done = bi_all_done(h, NR);
+    if (!done && (rc = resident_bicg_run(A, w, NR, val, x, jac, s, &done))) return rc;
+    if (!done) {
         // Iterations are enqueued in growing chunks; after each chunk the
         // states are copied to pinned memory, and the previous chunk's copy
         // is inspected while the current one runs.  Kernels enqueued after

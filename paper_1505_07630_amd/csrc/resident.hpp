@@ -55,7 +55,7 @@ constexpr unsigned long long kResSentinel = 0x7ff8f1c3a5965e17ull;
 constexpr unsigned kResAbort = 0x80000000u;
 
 // Doubles of slots a team of `size` needs.
-inline __host__ __device__ size_t res_slots(int size) { return (size_t)kResBufs * kResSums * size; }
+inline __host__ __device__ size_t res_slots(int size, int sums = kResSums) { return (size_t)kResBufs * sums * size; }
 
 // What one system's solve reports.
 struct ResOut {
@@ -235,18 +235,26 @@ struct RowSums {
 // v[0..NV) summed over the team, the totals in every thread; false when a
 // wait was given up.  Every earlier agent-scope store of any member is
 // visible to every member afterwards.
-template <int BS, int NV>
+// KS: sums the team's slots have room for.
+template <int BS, int NV, int KS = kResSums>
 __device__ __forceinline__ bool team_sum(double (&v)[NV], ResTeam& t) {
-    static_assert(NV <= kResSums && NV <= BS / 64, "a wave per sum");
     constexpr int kW = BS / 64;
+    static_assert(NV <= KS && NV <= 16 && KS <= 64, "room in the slots, a lane per sum");
     __shared__ double s_part[NV][kW];
     __shared__ double s_tot[NV];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    if constexpr (NV > 4) {
+        double a = RowSums<NV>::of(v);
+        a += __shfl_xor(a, 16, 64);
+        a += __shfl_xor(a, 32, 64);
+        if (lane < NV) s_part[lane][wid] = a;
+    } else {
 #pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
-    if (lane == 0) {
+        for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
+        if (lane == 0) {
 #pragma unroll
-        for (int k = 0; k < NV; ++k) s_part[k][wid] = v[k];
+            for (int k = 0; k < NV; ++k) s_part[k][wid] = v[k];
+        }
     }
     stores_done();
     __syncthreads();
@@ -255,18 +263,18 @@ __device__ __forceinline__ bool team_sum(double (&v)[NV], ResTeam& t) {
 #pragma unroll
         for (int w = 0; w < kW; ++w) mine += s_part[threadIdx.x][w];
     }
-    double* buf = t.slots + (size_t)(t.k & (kResBufs - 1)) * kResSums * t.size;
+    double* buf = t.slots + (size_t)(t.k & (kResBufs - 1)) * KS * t.size;
     if ((int)threadIdx.x < NV) {
         if (__double_as_longlong(mine) == (long long)kResSentinel)
             mine = __longlong_as_double((long long)(kResSentinel ^ 1ull));
         st_agent(buf + (size_t)threadIdx.x * t.size + t.rank, mine);
     }
-    if ((int)threadIdx.x < kResSums) {
-        double* old = t.slots + (size_t)((t.k + 2) & (kResBufs - 1)) * kResSums * t.size;
+    if ((int)threadIdx.x < KS) {
+        double* old = t.slots + (size_t)((t.k + 2) & (kResBufs - 1)) * KS * t.size;
         st_agent(old + (size_t)threadIdx.x * t.size + t.rank, __longlong_as_double((long long)kResSentinel));
     }
-    if (wid < NV) {
-        const double* q = buf + (size_t)wid * t.size;
+    for (int sum = wid; sum < NV; sum += kW) {
+        const double* q = buf + (size_t)sum * t.size;
         constexpr int kC = kResMaxTeam / 64;
         double g[kC];
         unsigned spins = 0;
@@ -297,7 +305,7 @@ __device__ __forceinline__ bool team_sum(double (&v)[NV], ResTeam& t) {
 #pragma unroll
         for (int i = 0; i < kC; ++i)
             if (i * 64 < t.size) s += wave_sum(g[i]);
-        if (lane == 0) s_tot[wid] = s;
+        if (lane == 0) s_tot[sum] = s;
     }
     __syncthreads();
 #pragma unroll

@@ -3,22 +3,24 @@
 
 Workload (the 7.08M-cell case): 192^3 hexahedral mesh, lognormal(0,1) face
 conductivities, cells randomly permuted then RCM-renumbered, Dirichlet on
-x-min/x-max, b ~ U[-1,1]; FP64 pipelined Jacobi-CG (one fused kernel and one
-reduction per iteration) to relative residual 1e-8.  One step = one whole
+x-min/x-max, b ~ U[-1,1]; FP64 pipelined Jacobi-CG (one pass over
+the rows and one reduction per iteration) to relative residual 1e-8.  One step = one whole
 solve: initial residual, every iteration, stopping test and the true residual
 at exit, with inputs resident in HBM.
 
 Prints ONE JSON line.  value = iterations/s over the timed solves.  roofline:
-the fused pipelined kernel, algorithmic bytes per iteration (104n + 24F, every
-vector pass of the folded pipelined iteration counted once) divided by its
-average launch time from HIP events on the solve stream, against the 8 TB/s
-HBM peak; the 96n + 24F the kernel actually needs (x updated every second
-iteration) is a second field.  mixed: the reliable-update and restarted
-FP32/FP64 solvers on the same system against plain FP64, time and error
-against the oracle's FP64 solution.  batched: 256 systems of uneven size in
-one persistent launch against one solve per system.  cpu_baseline: the
-plain-C oracle on all host cores (its OpenMP build, bitwise the
-single-thread results) on a bounded sample of the same workload, with the
+the pipelined kernel, which runs all iterations of a solve in one launch and
+keeps z and most of s on chip: the bytes an iteration has to move to and from
+memory divided by the average iteration time (the kernel's own clock; HIP
+events on the solve stream where the iterations are launches), against the 8
+TB/s HBM peak.  The algorithmic bytes (104n + 24F, every vector pass of the
+folded pipelined iteration counted once, on chip or not) are in
+alg_bytes_per_launch, and their rate in hbm_gbs_algorithmic.  mixed: the
+reliable-update and restarted FP32/FP64 solvers on the same system against
+plain FP64, time and error against the oracle's FP64 solution.  batched: 256
+systems of uneven size in one persistent launch against one solve per system.
+cpu_baseline: the plain-C oracle on all host cores (its OpenMP build, bitwise
+the single-thread results) on a bounded sample of the same workload, with the
 single-thread rate beside it.
 """
 from __future__ import annotations
@@ -39,7 +41,8 @@ HBM_PEAK_GBS = 8000.0
 RELIABLE_PERIOD = 16  # FP32 iterations between FP64 updates in the reliable-update mixed solve
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pipecg_fold_varcoef192_traffic.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1505_07630_amd", "csrc", f)
-                  for f in ("solve.hip", "rows.hpp", "common.hpp", "setup.hip")]
+                  for f in ("solve.hip", "rows.hpp", "common.hpp", "setup.hip", "resident.hpp", "resident_host.hpp",
+                            "resident.hip", "resident_stream.hip")]
 
 
 def log(*a):
@@ -65,6 +68,19 @@ def alg_bytes_pipecg_folded(n, F, iters):
     not by the layout: the 16-bit column offsets move fewer bytes than this."""
     total = iters * (88 * n + 24 * F) + (iters // 2) * 16 * n + (iters % 2) * 24 * n
     return total / max(iters, 1)
+
+
+def on_chip_bytes(n):
+    """Bytes per iteration of the vector passes that stay on chip when the
+    pipelined solve of 1.05M to 8.4M cells runs in one launch: z, s, p, r, x
+    and d up to 16 tiles of 512 rows per workgroup (256 of them), z, s and p
+    up to 32, z and 32 tiles of s up to 64 (resident.hpp)."""
+    per = -(-(-(-n // 512)) // 256)
+    if os.environ.get("FVPCG_RESIDENT", "")[:1] == "0" or per > 64:
+        return 0
+    if per <= 16:
+        return 80 * n
+    return 48 * n if per <= 32 else 16 * n + 16 * n * 32 // per
 
 
 def alg_bytes_per_iter(method, n, F, iters):
@@ -204,42 +220,40 @@ def main():
     n, F = case.n, case.F
     bpi = alg_bytes_per_iter(args.method, n, F, 1)
     its = total_iters / elapsed
-    # dominant kernel: average duration of one fused iteration over the timed
-    # solves (HIP events around the iteration launches on the solve stream)
+    # dominant kernel: average duration of one iteration over the timed solves
+    # (the kernel's clock, or HIP events around the iteration launches)
     kern_s = iter_ms / 1e3 / total_iters
-    achieved = bpi / kern_s / 1e9
 
     # fixed-iteration launch timing (no convergence checks in between)
     x.zero_()
     _, stf = fv.solve(A, b, x=x, tol=0.0, maxit=args.roofline_iters, method=args.method)
     kern_fixed_s = stf["iter_ms"] / 1e3 / stf["iters"]
-    log(f"fused kernel: {kern_s * 1e6:.1f} us/launch in solves, {kern_fixed_s * 1e6:.1f} us/launch over "
+    log(f"iteration: {kern_s * 1e6:.1f} us in solves, {kern_fixed_s * 1e6:.1f} us over "
         f"{stf['iters']} fixed iterations")
 
-    kernel_bytes = None
+    moved, one_launch = bpi, False
     if args.method == "pipecg":
-        # what the kernel must move: x updated every second iteration
-        kernel_bytes = sum(alg_bytes_pipecg_folded(n, F, s_["iters"]) * s_["iters"] for s_ in stats) / total_iters
-    traffic = measured_traffic(kernel_bytes)
-    kernel_name = {"pipecg": "k_pipe_iter<512, double, 6, int16_t, JAC=true, LIT=false>",
+        # what the kernel must move: x updated every second iteration, the
+        # vectors on chip not at all, and int16 column offsets when every
+        # |column - row| fits (the library's rule): six slots of 2 B instead
+        # of 4 B per row
+        one_launch = on_chip_bytes(n) > 0
+        col16 = int(np.max(np.abs(case.neighbour.astype(np.int64) - case.owner))) <= 32767 if F else False
+        moved = sum(alg_bytes_pipecg_folded(n, F, s_["iters"]) * s_["iters"] for s_ in stats) / total_iters
+        moved -= on_chip_bytes(n) + (12 * n if col16 else 0)
+    achieved = moved / kern_s / 1e9
+    traffic = measured_traffic(moved)
+    kernel_name = {"pipecg": "k_res_stream<64, 6, int16_t, JAC=true>" if one_launch else
+                   "k_pipe_iter<512, double, 6, int16_t, JAC=true, LIT=false>",
                    "pipecg_literal": "k_pipe_iter<512, double, 6, int16_t, JAC=true, LIT=true>",
                    "cg": "k_cg_spmv + k_cg_update_r + k_cg_update_xp"}[args.method]
     roof = {
         "bound": "hbm", "kernel": kernel_name, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
         "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-        "alg_bytes_per_launch": bpi, "avg_launch_us": round(kern_s * 1e6, 2),
+        "alg_bytes_per_launch": bpi, "moved_bytes_per_launch": moved, "iterations_in_one_launch": one_launch,
+        "avg_launch_us": round(kern_s * 1e6, 2),
         "avg_launch_us_fixed_iters": round(kern_fixed_s * 1e6, 2),
     }
-    moved = None
-    if kernel_bytes is not None:
-        # int16 column offsets when every |column - row| fits (the library's
-        # rule): six slots of 2 B instead of 4 B per row
-        col16 = int(np.max(np.abs(case.neighbour.astype(np.int64) - case.owner))) <= 32767 if F else False
-        moved = kernel_bytes - 12 * n if col16 else kernel_bytes
-        roof["kernel_bytes_per_launch"] = kernel_bytes
-        roof["moved_bytes_per_launch"] = moved
-        roof["kernel_bytes_gbs"] = round(kernel_bytes / kern_s / 1e9, 1)
-        roof["kernel_bytes_frac"] = round(kernel_bytes / kern_s / 1e9 / HBM_PEAK_GBS, 4)
     out = {
         "metric": METRIC,
         "value": round(its, 2),
@@ -267,7 +281,7 @@ def main():
         # the bytes the kernel must move (with its int16 column offsets) per
         # launch time, against the line for its own mix; the counted traffic
         # also holds neighbour lines fetched into more than one XCD's L2
-        "real_gbs_vs_stream_mix": round((moved or bpi) / kern_s / 1e9 / mix["read_12_write_5"], 4),
+        "real_gbs_vs_stream_mix": round(moved / kern_s / 1e9 / mix["read_12_write_5"], 4),
     }
     pending = None
     if not args.no_mixed:

@@ -97,8 +97,8 @@ typedef struct fvpcg_stats {
     double true_rel_res;  /* ||b - A x||_2 / ||b||_2 recomputed at exit */
     double r0_norm;       /* ||b - A x0||_2 */
     double b_norm;        /* ||b||_2 */
-    double device_ms;     /* whole call, HIP events on `stream` */
-    double iter_ms;       /* the iteration kernels only, HIP events on `stream` */
+    double device_ms;     /* whole call, HIP events on `stream` (the kernel's clock where one launch solves) */
+    double iter_ms;       /* the iterations only, HIP events on `stream` (the kernel's clock, alike) */
 } fvpcg_stats;
 
 FVPCG_API int fvpcg_version(void);
@@ -222,6 +222,17 @@ FVPCG_API int fvpcg_solve_backward(const fvpcg_matrix* mat, const double* x, con
                          int32_t maxit, int32_t method, int32_t precond, void* stream,
                          fvpcg_stats* stats);
 
+/* ---- Solves in one launch: where a system's rows, or enough of its vectors,
+ * fit on the chip (fvpcg_solve up to 1.05M cells, pipelined up to 8.4M; the
+ * FP32 iterations of fvpcg_solve_mixed_reliable and BiCGSTAB with two or three
+ * right-hand sides up to 2.1M; batches of at least 2,048 cells per system on
+ * average) up to 256 workgroups run all iterations in one launch.  They must be
+ * on the device together: if they have not met within FVPCG_RESIDENT_MEET_MS
+ * (default 20), or another such solve is running on the device, the call
+ * iterates launch by launch instead, as with FVPCG_RESIDENT=0, with the same
+ * results (bit for bit, but for batches, whose sums are ordered otherwise).
+ * Waits inside a solve are bounded too (FVPCG_DEVICE_ERROR). */
+
 /* ---- Batched solves: nsys independent systems of uneven sizes in one
  * persistent launch.  cell_off_host, face_off_host: HOST int32[nsys+1]
  * prefix offsets into the concatenated device arrays; owner/neighbour hold
@@ -241,7 +252,7 @@ FVPCG_API int fvpcg_batch_destroy(fvpcg_batch* batch);
  * on other streams can delay members; each wait is bounded
  * (FVPCG_BATCH_BARRIER_TIMEOUT_MS, default 5000): on a timeout every
  * workgroup leaves, x and stats are invalid and FVPCG_DEVICE_ERROR is
- * returned.  The first call per batch shape times the launch candidates
+ * returned.  The first call per batch shape not solved as above times the launch candidates
  * (block size, workgroups per CU, teams on/off) and caches the choice in
  * $FVPCG_TUNE_CACHE (FVPCG_TUNE=0: fixed defaults; FVPCG_BATCH_TEAMS=0/1:
  * never/always form teams).  Calls on one batch handle must not overlap. */

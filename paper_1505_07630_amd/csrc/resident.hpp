@@ -26,10 +26,11 @@
 //     everybody has published k - 1, hence read k - 2), which every member
 //     sees before it can reach reduction k + 2.
 //
-// Measured alone on MI355X (exchange, reduction and 6 gathers per row): 3.7 us
-// per iteration with 64 workgroups and 1 row per thread, 5.6 with 256, 10.9
-// with 256 and 8 rows per thread (1M rows).  Acquire fences with cached gathers
-// instead took 4.1, 7.4 and 12.4 us, and a two-level reduction 5.6, 6.3, 11.0.
+// Pipelined CG on MI355X takes 3.0 us per iteration at 8k cells, 3.3 at 32k, 5.8
+// at 262k and 10.1 at 1M.  Acquire fences with cached gathers instead, and a
+// two-level reduction, were slower at every size (1M rows: 12.4 us for the
+// former when this took 10.9); own tiles of the exchanged vector in LDS as
+// well, for the neighbours within the tile, 6.2 us at 262k and 15 at 1M.
 //
 // The team must be resident together.  It meets once at the start (rendezvous)
 // with a short time limit; a team that does not come together there leaves
@@ -1022,7 +1023,7 @@ __device__ __forceinline__ void resident_pipe32(const PipeVec<float>& a, int n, 
 //   up to 64 tiles (8.4M)        z in registers, s in LDS for 32 tiles.
 // Every resident vector saves its read and its write.  Per iteration, against
 // the launches (bandwidth-bound at 6.3 TB/s): 35.5 us against 62.7 at 2.1M
-// cells, 75 against 109 at 4.1M, 146 against 182 at 7.1M.  A row's loads are all
+// cells, 75 against 109 at 4.1M, 143-146 against 182 at 7.1M.  A row's loads are all
 // issued before its gathers are waited for: with r and p read after them 209 us
 // at 7.1M.  w is stored with agent
 // scope; its gathers go through the L2 caches (uncached they would fetch every

@@ -13,7 +13,7 @@
 // Up to 16 tiles of 512 rows per member (2,097,152 cells).  p and s are stored
 // with agent scope and gathered through the caches, which every member
 // invalidates after the meetings they follow.  Bound by the passes over
-// memory: at 128^3 and three components 889 MB in 190 us, 4.7 TB/s (by
+// memory: at 128^3 and three components 889 MB in 187 us, 4.75 TB/s (by
 // launches 1,124 MB in 245 us).
 #include "bicgstab.hpp"
 #include "resident.hpp"

@@ -21,7 +21,7 @@ LIB_NAME = "libfvpcg.so"
 LIB_PATH = os.path.join(HERE, LIB_NAME)
 ARCH = "gfx950"
 
-SOURCES = ["setup.hip", "solve.hip", "resident.hip", "resident_pipe.hip", "resident_cg.hip", "resident_mixed.hip", "resident_stream.hip", "resident_bicg.hip", "batched.hip", "amg.hip", "amg_setup.hip", "transient.hip", "bicgstab.hip",
+SOURCES = ["setup.hip", "solve.hip", "resident.hip", "resident_pipe.hip", "resident_cg.hip", "resident_mixed.hip", "resident_stream.hip", "resident_cg_stream.hip", "resident_bicg.hip", "batched.hip", "amg.hip", "amg_setup.hip", "transient.hip", "bicgstab.hip",
            "piso.hip", "calibrate.hip", "memory.hip", "api.hip"]
 
 FLAGS = [

@@ -105,19 +105,24 @@ ResPlan resident_plan(const fvpcg_mesh* m, int method) {
     return p;
 }
 
-ResPlan resident_plan_stream(const fvpcg_mesh* m) {
+ResPlan resident_plan_stream(const fvpcg_mesh* m, int method) {
     ResPlan p;
     const char* env = getenv("FVPCG_RESIDENT");
     if (env && env[0] == '0') return p;
     if (m->WT > 8 || m->n < 1 || m->device < 0 || m->device >= kMaxDevices) return p;
     const DeviceInfo& info = device_info(m->device);
-    const int tiles = (m->n + kResBsPipe - 1) / kResBsPipe;
+    const int bs = method == FVPCG_CG ? kResBsCg : kResBsPipe;
+    const int tiles = (m->n + bs - 1) / bs;
     const int g = std::min(tiles, kMaxGrid);  // geom_for's workgroups
     const int per = (tiles + g - 1) / g;
-    if (per > kStreamTiles || g > info.cus || info.ticks_per_ms <= 0) return p;
-    p.block = kResBsPipe;
+    if (per > (method == FVPCG_CG ? 16 : kStreamTiles) || g > info.cus || info.ticks_per_ms <= 0) return p;
+    p.method = method;
+    p.block = bs;
     p.size = g;
-    p.rpt = per <= 16 ? 16 : per <= 32 ? 32 : 64;
+    if (method == FVPCG_CG)
+        p.rpt = per <= 8 ? 8 : 16;
+    else
+        p.rpt = per <= 16 ? 16 : per <= 32 ? 32 : 64;
     return p;
 }
 
@@ -133,8 +138,9 @@ int resident_stream_run(const fvpcg_mesh* m, const ResPlan& plan, const ResWork&
     ResTeam t{0, plan.size, w.slots, w.meet, w.abort_flag, nullptr,
               (unsigned long long)(info.ticks_per_ms * resident_meet_ms()),
               (unsigned long long)(info.ticks_per_ms * kResSpinMs), 0};
-    hipLaunchKernelGGL(res_kernel_stream(plan.rpt, m->WT, m->col16 != nullptr, jac), dim3(plan.size), dim3(plan.block), 0,
-                       s, a, m->n, t, st, w.pinned);
+    const auto pick = plan.method == FVPCG_CG ? res_kernel_cg_stream : res_kernel_stream;
+    hipLaunchKernelGGL(pick(plan.rpt, m->WT, m->col16 != nullptr, jac), dim3(plan.size), dim3(plan.block), 0, s, a, m->n, t,
+                       st, w.pinned);
     FV_LAUNCHED();
     FV_HIP(hipStreamSynchronize(s));
     if (w.pinned->ok) {
@@ -144,7 +150,7 @@ int resident_stream_run(const fvpcg_mesh* m, const ResPlan& plan, const ResWork&
     int gave_up = 0;
     FV_HIP(hipMemcpyAsync(&gave_up, w.abort_flag, sizeof(int), hipMemcpyDeviceToHost, s));
     FV_HIP(hipStreamSynchronize(s));
-    if (gave_up) return set_error(FVPCG_DEVICE_ERROR, "pipelined CG: a wait between workgroups timed out");
+    if (gave_up) return set_error(FVPCG_DEVICE_ERROR, "CG: a wait between workgroups timed out");
     return FVPCG_OK;
 }
 

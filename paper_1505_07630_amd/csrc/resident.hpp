@@ -315,6 +315,13 @@ __device__ __forceinline__ bool team_sum(double (&v)[NV], ResTeam& t) {
     return *t.ok != 0;
 }
 
+// The members' stores before their last reduction, seen by this workgroup's
+// plain loads.
+__device__ __forceinline__ void team_acquire() {
+    if (threadIdx.x < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    __syncthreads();
+}
+
 // Sums of a workgroup on its own (ONE): each tile of BS rows is summed as the
 // member of a team that held it would, then the tiles as the members.
 template <int BS, int NV, int RPT>

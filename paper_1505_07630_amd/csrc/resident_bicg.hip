@@ -31,13 +31,6 @@ __device__ __forceinline__ double uniform(double v) {
                             __builtin_amdgcn_readfirstlane(__double2loint(v)));
 }
 
-// The members' stores before their last reduction, seen by this workgroup's
-// plain loads.
-__device__ __forceinline__ void team_acquire() {
-    if (threadIdx.x < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    __syncthreads();
-}
-
 template <int NR, int WT, typename CI, bool JAC>
 __global__ __launch_bounds__(kResBsPipe) void k_res_bicg(const CI* __restrict__ col, const double* __restrict__ val,
                                                          const double* __restrict__ d, int n, double* x, double* r,

@@ -51,6 +51,7 @@ ResKernel res_kernel_pipe(const ResPlan& p, int wt, bool col16, bool jac);
 ResKernel res_kernel_cg(const ResPlan& p, int wt, bool col16, bool jac);
 ResMixedKernel res_kernel_mixed(int rpt, int wt, bool col16);
 ResStreamKernel res_kernel_stream(int nt, int wt, bool col16, bool jac);
+ResStreamKernel res_kernel_cg_stream(int nt, int wt, bool col16, bool jac);
 ResBatchKernel res_batch_pipe(int rpt, int wt, bool col16, bool jac);
 ResBatchKernel res_batch_cg(int rpt, int wt, bool col16, bool jac);
 double resident_meet_ms();
@@ -68,10 +69,11 @@ ResPlan resident_plan32(const fvpcg_mesh* m);
 int resident_run32(const fvpcg_mesh* m, const ResPlan& plan, const ResWork& w, const PipeVec<float>& a, int iters,
                    DevState* st, DevState* st_skip, hipStream_t s);
 
-// The iterations of a larger folded pipelined solve in one launch
-// (resident_stream), the initial residual and first reduction done (st, a).
+// The iterations of a larger folded pipelined or standard solve in one launch
+// (resident_stream, k_res_cg_stream), the initial residual and first reduction
+// done (st, a).
 // *done = false with FVPCG_OK: nothing was done, iterate by launches.
-ResPlan resident_plan_stream(const fvpcg_mesh* m);
+ResPlan resident_plan_stream(const fvpcg_mesh* m, int method = FVPCG_PIPECG);
 int resident_stream_run(const fvpcg_mesh* m, const ResPlan& plan, const ResWork& w, const PipeVec<double>& a, bool jac,
                         DevState* st, hipStream_t s, bool* done);
 

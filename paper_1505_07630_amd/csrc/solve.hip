@@ -891,8 +891,8 @@ int solve(const fvpcg_matrix* A, const double* b, double* x, double tol, int max
         if ((rc = work_need_pipe(w, method == FVPCG_PIPECG_LITERAL))) return rc;
     }
     ResPlan stream;
-    if (method == FVPCG_PIPECG) {
-        stream = resident_plan_stream(A->mesh);
+    if (method != FVPCG_PIPECG_LITERAL) {
+        stream = resident_plan_stream(A->mesh, method);
         if (stream.rpt && (rc = work_need_resident(w, false))) return rc;
     }
     return solve_core(A, w, b, x, tol, maxit, method, precond, stream, s, stats);
@@ -900,7 +900,7 @@ int solve(const fvpcg_matrix* A, const double* b, double* x, double tol, int max
 
 namespace {
 
-// `stream`: how the pipelined iterations run in one launch (rpt 0: they do not)
+// `stream`: how the iterations run in one launch (rpt 0: they do not)
 int solve_core(const fvpcg_matrix* A, Work& w, const double* b, double* x, double tol, int maxit, int method,
                int precond, const ResPlan& stream, hipStream_t s, fvpcg_stats* stats) {
     const fvpcg_mesh* m = A->mesh;
@@ -949,8 +949,16 @@ int solve_core(const fvpcg_matrix* A, Work& w, const double* b, double* x, doubl
     if (h.zero_b) {
         FV_HIP(hipMemsetAsync(x, 0, sizeof(double) * (size_t)n, s));
     } else if (!h.done) {
+        const ResWork rw{nullptr, nullptr, w.res_slots, w.res_meet, reinterpret_cast<int*>(w.res_meet + 1), nullptr,
+                         w.res_pinned};
         if (method == FVPCG_CG) {
-            rc = iterate(w, 0, maxit, s, [&](int it) {
+            rc = FVPCG_OK;
+            if (stream.rpt && stream.method == FVPCG_CG) {
+                const PipeVec<double> a{mesh_cols(m), A->val, A->d, nullptr, nullptr, nullptr,
+                                        nullptr, w.p, x, w.r, nullptr, nullptr};
+                rc = resident_stream_run(m, stream, rw, a, jac, st, s, &streamed);
+            }
+            if (!rc && !streamed) rc = iterate(w, 0, maxit, s, [&](int it) {
                 FV_LAYOUT(m, hipLaunchKernelGGL((k_cg_spmv<kBsCg, W_, CI_>), dim3(gc.grid), dim3(kBsCg), 0, s, cols_,
                                                        A->val, A->d, n, gc, w.p, w.q, st, part));
                 if (jac) {
@@ -969,8 +977,6 @@ int solve_core(const fvpcg_matrix* A, Work& w, const double* b, double* x, doubl
             const bool lit = method == FVPCG_PIPECG_LITERAL;
             rc = FVPCG_OK;
             if (stream.rpt) {
-                const ResWork rw{nullptr, nullptr, w.res_slots, w.res_meet, reinterpret_cast<int*>(w.res_meet + 1),
-                                 nullptr, w.res_pinned};
                 const PipeVec<double> a{mesh_cols(m), jac ? A->val_cs : A->val, A->d, w.w[0], w.w[1], w.z,
                                         w.s, w.p, x, w.r, nullptr, nullptr};
                 rc = resident_stream_run(m, stream, rw, a, jac, st, s, &streamed);

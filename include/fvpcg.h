@@ -223,15 +223,16 @@ FVPCG_API int fvpcg_solve_backward(const fvpcg_matrix* mat, const double* x, con
                          fvpcg_stats* stats);
 
 /* ---- Solves in one launch: where a system's rows, or enough of its vectors,
- * fit on the chip (fvpcg_solve up to 1.05M cells, pipelined up to 8.4M; the
- * FP32 iterations of fvpcg_solve_mixed_reliable and BiCGSTAB with two or three
- * right-hand sides up to 2.1M; batches of at least 2,048 cells per system on
- * average) up to 256 workgroups run all iterations in one launch.  They must be
- * on the device together: if they have not met within FVPCG_RESIDENT_MEET_MS
- * (default 20), or another such solve is running on the device, the call
- * iterates launch by launch instead, as with FVPCG_RESIDENT=0, with the same
- * results (bit for bit, but for batches, whose sums are ordered otherwise).
- * Waits inside a solve are bounded too (FVPCG_DEVICE_ERROR). */
+ * fit on the chip (fvpcg_solve: literal pipelined up to 0.5M cells, standard
+ * up to 4.2M, pipelined up to 8.4M; the FP32 iterations of
+ * fvpcg_solve_mixed_reliable and BiCGSTAB with two or three right-hand sides
+ * up to 2.1M; batches of at least 2,048 cells per system on average) up to 256
+ * workgroups run all iterations in one launch.  They must be on the device
+ * together: if they have not met within FVPCG_RESIDENT_MEET_MS (default 20),
+ * or another such solve is running on the device, the call iterates launch by
+ * launch instead, as with FVPCG_RESIDENT=0, with the same results (bit for
+ * bit, but for batches, whose sums are ordered otherwise).  Waits inside a
+ * solve are bounded too (FVPCG_DEVICE_ERROR). */
 
 /* ---- Batched solves: nsys independent systems of uneven sizes in one
  * persistent launch.  cell_off_host, face_off_host: HOST int32[nsys+1]

@@ -65,6 +65,19 @@ double resident_meet_ms() {
     return env && *env ? std::max(0.0, atof(env)) : kResMeetMs;
 }
 
+double resident_spin_ms() {
+    const char* env = getenv("FVPCG_RESIDENT_SPIN_MS");
+    return env && *env ? std::max(0.0, atof(env)) : kResSpinMs;
+}
+
+int resident_no_result(const int* abort_flag, const char* what, hipStream_t s) {
+    int gave_up = 0;
+    FV_HIP(hipMemcpyAsync(&gave_up, abort_flag, sizeof(int), hipMemcpyDeviceToHost, s));
+    FV_HIP(hipStreamSynchronize(s));
+    if (gave_up) return set_error(FVPCG_DEVICE_ERROR, "%s: a wait between workgroups timed out (x is invalid)", what);
+    return FVPCG_OK;
+}
+
 int resident_reset(double* slots, size_t count, unsigned* meet, int* abort_flag, ResOut* out, int nout, hipStream_t s) {
     const size_t work = std::max(count, (size_t)nout);
     hipLaunchKernelGGL(k_res_reset, dim3((unsigned)std::min<size_t>((work + 255) / 256, 256)), dim3(256), 0, s, slots, count,
@@ -137,7 +150,7 @@ int resident_stream_run(const fvpcg_mesh* m, const ResPlan& plan, const ResWork&
     if ((rc = resident_reset(w.slots, res_slots(plan.size), w.meet, w.abort_flag, nullptr, 0, s))) return rc;
     ResTeam t{0, plan.size, w.slots, w.meet, w.abort_flag, nullptr,
               (unsigned long long)(info.ticks_per_ms * resident_meet_ms()),
-              (unsigned long long)(info.ticks_per_ms * kResSpinMs), 0};
+              (unsigned long long)(info.ticks_per_ms * resident_spin_ms()), 0};
     const auto pick = plan.method == FVPCG_CG ? res_kernel_cg_stream : res_kernel_stream;
     hipLaunchKernelGGL(pick(plan.rpt, m->WT, m->col16 != nullptr, jac), dim3(plan.size), dim3(plan.block), 0, s, a, m->n, t,
                        st, w.pinned);
@@ -147,11 +160,7 @@ int resident_stream_run(const fvpcg_mesh* m, const ResPlan& plan, const ResWork&
         *done = true;
         return FVPCG_OK;
     }
-    int gave_up = 0;
-    FV_HIP(hipMemcpyAsync(&gave_up, w.abort_flag, sizeof(int), hipMemcpyDeviceToHost, s));
-    FV_HIP(hipStreamSynchronize(s));
-    if (gave_up) return set_error(FVPCG_DEVICE_ERROR, "CG: a wait between workgroups timed out");
-    return FVPCG_OK;
+    return resident_no_result(w.abort_flag, "CG", s);
 }
 
 ResPlan resident_plan32(const fvpcg_mesh* m) {
@@ -179,7 +188,7 @@ int resident_run32(const fvpcg_mesh* m, const ResPlan& plan, const ResWork& w, c
     if ((rc = resident_reset(w.slots, res_slots(plan.size), w.meet, w.abort_flag, nullptr, 0, s))) return rc;
     ResTeam t{0, plan.size, w.slots, w.meet, w.abort_flag, nullptr,
               (unsigned long long)(info.ticks_per_ms * resident_meet_ms()),
-              (unsigned long long)(info.ticks_per_ms * kResSpinMs), 0};
+              (unsigned long long)(info.ticks_per_ms * resident_spin_ms()), 0};
     hipLaunchKernelGGL(res_kernel_mixed(plan.rpt, m->WT, m->col16 != nullptr), dim3(plan.size), dim3(plan.block), 0, s, a,
                        m->n, iters, t, st, st_skip);
     FV_LAUNCHED();
@@ -202,7 +211,7 @@ int resident_solve(const fvpcg_matrix* A, const ResPlan& plan, const ResWork& w,
     int rc;
     if (!plan.one && (rc = resident_reset(w.slots, res_slots(plan.size), w.meet, w.abort_flag, out, 1, s))) return rc;
     ResTeam t{0, plan.size, w.slots, w.meet, w.abort_flag, nullptr,
-              (unsigned long long)(info.ticks_per_ms * resident_meet_ms()), (unsigned long long)(info.ticks_per_ms * kResSpinMs),
+              (unsigned long long)(info.ticks_per_ms * resident_meet_ms()), (unsigned long long)(info.ticks_per_ms * resident_spin_ms()),
               0};
     ResKernel k = plan.method == FVPCG_CG ? res_kernel_cg(plan, m->WT, m->col16 != nullptr, jac)
                                           : res_kernel_pipe(plan, m->WT, m->col16 != nullptr, jac);
@@ -211,7 +220,7 @@ int resident_solve(const fvpcg_matrix* A, const ResPlan& plan, const ResWork& w,
     if (!w.pinned) FV_HIP(hipMemcpyAsync(&host, w.out, sizeof(ResOut), hipMemcpyDeviceToHost, s));
     FV_HIP(hipStreamSynchronize(s));
     if (w.pinned) host = *w.pinned;
-    if (!host.ok) return FVPCG_OK;  // the team did not come together: x holds a valid start
+    if (!host.ok) return resident_no_result(w.abort_flag, "CG", s);
     *done = true;
     if (stats) {
         stats->iters = host.iter;

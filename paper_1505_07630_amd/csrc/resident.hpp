@@ -279,6 +279,7 @@ __device__ __forceinline__ bool team_sum(double (&v)[NV], ResTeam& t) {
         constexpr int kC = kResMaxTeam / 64;
         double g[kC];
         unsigned spins = 0;
+        const unsigned every = t.spin_ticks ? 63u : 0u;  // a limit of 0: given up at the first poll that finds a sum missing
         const unsigned long long t0 = (unsigned long long)wall_clock64();
         for (;;) {
             bool wait = false;
@@ -291,7 +292,7 @@ __device__ __forceinline__ bool team_sum(double (&v)[NV], ResTeam& t) {
                 }
             }
             if (!__any(wait)) break;
-            if ((++spins & 63u) == 0 &&
+            if ((++spins & every) == 0 &&
                 ((unsigned long long)wall_clock64() - t0 > t.spin_ticks ||
                  __hip_atomic_load(t.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
                 if (lane == 0) {

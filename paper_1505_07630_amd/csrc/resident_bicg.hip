@@ -256,7 +256,7 @@ int resident_bicg_run(const fvpcg_matrix* A, BiWork& w, int nr, const double* va
     w.out->ok = 0;
     if ((rc = resident_reset(w.slots, res_slots(plan.size, kBiSums), w.meet, abort_flag, nullptr, 0, s))) return rc;
     const ResTeam t{0, plan.size, w.slots, w.meet, abort_flag, nullptr, (unsigned long long)(ticks * resident_meet_ms()),
-                    (unsigned long long)(ticks * kResSpinMs), 0};
+                    (unsigned long long)(ticks * resident_spin_ms()), 0};
     switch (nr) {
         case 1: rc = jac ? launch<1, true>(A, w, val, x, plan, t, s) : launch<1, false>(A, w, val, x, plan, t, s); break;
         case 2: rc = jac ? launch<2, true>(A, w, val, x, plan, t, s) : launch<2, false>(A, w, val, x, plan, t, s); break;
@@ -268,11 +268,7 @@ int resident_bicg_run(const fvpcg_matrix* A, BiWork& w, int nr, const double* va
         *done = true;
         return FVPCG_OK;
     }
-    int gave_up = 0;
-    FV_HIP(hipMemcpyAsync(&gave_up, abort_flag, sizeof(int), hipMemcpyDeviceToHost, s));
-    FV_HIP(hipStreamSynchronize(s));
-    if (gave_up) return set_error(FVPCG_DEVICE_ERROR, "BiCGSTAB: a wait between workgroups timed out");
-    return FVPCG_OK;
+    return resident_no_result(abort_flag, "BiCGSTAB", s);
 }
 
 }  // namespace fvpcg

@@ -21,7 +21,9 @@ using ResKernel = void (*)(ResSystem, ResTeam, ResOut*);
 // Rendezvous limit: past it (other work holds the GPU's CUs) the launch-per-
 // iteration path runs instead (FVPCG_RESIDENT_MEET_MS sets another;
 // FVPCG_RESIDENT=0 always takes that path).  Limit of any later wait, which
-// ends by itself.
+// ends by itself (FVPCG_RESIDENT_SPIN_MS sets another; past it the call is a
+// device error: members may have written x by then, so no other path goes on
+// from it).
 constexpr double kResMeetMs = 20.0, kResSpinMs = 5000.0;
 
 struct ResPlan {
@@ -55,6 +57,10 @@ ResStreamKernel res_kernel_cg_stream(int nt, int wt, bool col16, bool jac);
 ResBatchKernel res_batch_pipe(int rpt, int wt, bool col16, bool jac);
 ResBatchKernel res_batch_cg(int rpt, int wt, bool col16, bool jac);
 double resident_meet_ms();
+double resident_spin_ms();
+// After a launch whose result is missing: FVPCG_OK if the team did not come
+// together (nothing was written), FVPCG_DEVICE_ERROR if a later wait was given up.
+int resident_no_result(const int* abort_flag, const char* what, hipStream_t s);
 // CUs, and wall-clock ticks per ms (0: unknown) of a device.
 void resident_device(int device, int* cus, double* ticks_per_ms);
 // Enqueues the reset of `count` slot doubles, the rendezvous word, the abort

@@ -1257,7 +1257,7 @@ int solve_mixed_reliable(const fvpcg_matrix* A, const double* b, double* x, doub
             FV_LAUNCHED();
             if ((rc = state_read_both(w, &h, &hi, s))) return rc;
             if (h.done == kResLost)
-                return set_error(FVPCG_DEVICE_ERROR, "mixed solve: a wait between workgroups timed out");
+                return set_error(FVPCG_DEVICE_ERROR, "mixed solve: a wait between workgroups timed out (x is invalid)");
             if (h.done == kResNoTeam) {  // nothing was done since the last update: go on by launches
                 plan.rpt = 0;
                 lock.unlock();

@@ -1,0 +1,55 @@
+"""A wait between a team's workgroups that is given up (its limit set to zero
+from the host, so every workgroup leaves by itself) ends the call with
+DEVICE_ERROR: it is not continued by launches from an x that members may have
+written.  The next solve with the usual limit has the launches' bits."""
+import pytest
+
+import fvcases as fc
+from tests.gpu_util import DevCase, say
+from tests.test_gpu_resident import fv  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def solvers(fv, dc):  # noqa: F811
+    import torch
+
+    z = torch.zeros_like
+    for method in ("pipecg", "pipecg_literal", "cg"):
+        yield method, lambda m=method: fv.solve(dc.A, dc.b, x=z(dc.b), tol=1e-10, method=m)
+        yield "noalloc " + method, lambda m=method: fv.solve_noalloc(dc.A, dc.b, z(dc.b), tol=1e-10, method=m)
+    yield "mixed", lambda: fv.solve_mixed_reliable(dc.A, dc.b, x=z(dc.b), tol=1e-10, update_every=16)
+    b = torch.stack([dc.b, 2.0 * dc.b.flip(0)])
+    yield "bicgstab", lambda: fv.solve_bicgstab_multi(dc.A, b, x=z(b), tol=1e-10)
+
+
+def check(fv, monkeypatch, name, run):  # noqa: F811
+    import torch
+
+    say("lost wait", name)
+    monkeypatch.setenv("FVPCG_RESIDENT", "0")
+    want = run()[0].clone()
+    monkeypatch.setenv("FVPCG_RESIDENT", "1")
+    monkeypatch.setenv("FVPCG_RESIDENT_SPIN_MS", "0")
+    with pytest.raises(fv.FVPCGError) as e:
+        run()
+    assert e.value.code == fv.DEVICE_ERROR and "wait between workgroups" in str(e.value)
+    monkeypatch.delenv("FVPCG_RESIDENT_SPIN_MS")
+    assert torch.equal(run()[0], want)
+
+
+def test_lost_wait_is_an_error(fv, monkeypatch):  # noqa: F811
+    dc = DevCase(fc.varcoef((40, 36, 30), seed=6), fp32_copy=True)
+    for name, run in solvers(fv, dc):
+        check(fv, monkeypatch, name, run)
+    dc.close()
+
+
+@pytest.mark.parametrize("method", ["pipecg", "cg"])
+def test_lost_wait_streamed(fv, monkeypatch, method):  # noqa: F811
+    import torch
+
+    dc = DevCase(fc.varcoef((112, 110, 108), seed=6, permute=False))
+    check(fv, monkeypatch, "streamed " + method,
+          lambda: fv.solve(dc.A, dc.b, x=torch.zeros_like(dc.b), tol=1e-4, method=method))
+    dc.close()

@@ -1094,7 +1094,7 @@ int solve_batched_resident(fvpcg_batch* bt, const double* b, double* x, double t
                   tol,
                   maxit};
     ResTeam t{0, p.grid, bt->d_rslots, bt->d_rmeet, abort_flag, nullptr, (unsigned long long)(ticks * resident_meet_ms()),
-              (unsigned long long)(ticks * kResSpinMs), 0};
+              bt->spin_ticks, 0};
     ResBatch rb{bt->d_cell_off, bt->d_rtasks, bt->d_rlist, bt->d_rout};
     ResBatchKernel k = method == 0 ? res_batch_cg(p.rpt, m->WT, m->col16 != nullptr, jac)
                                    : res_batch_pipe(p.rpt, m->WT, m->col16 != nullptr, jac);
@@ -1104,7 +1104,7 @@ int solve_batched_resident(fvpcg_batch* bt, const double* b, double* x, double t
     FV_HIP(hipMemcpyAsync(bt->h_rout, bt->d_rout, sizeof(ResOut) * bt->nsys, hipMemcpyDeviceToHost, s));
     FV_HIP(hipStreamSynchronize(s));
     for (int i = 0; i < bt->nsys; ++i)
-        if (!bt->h_rout[i].ok) return FVPCG_OK;  // x holds a valid start for the other path
+        if (!bt->h_rout[i].ok) return resident_no_result(abort_flag, "batched solve", s);
     *done = true;
     float ms = 0;
     (void)hipEventElapsedTime(&ms, bt->e0, bt->e1);

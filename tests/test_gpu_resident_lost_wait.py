@@ -5,7 +5,7 @@ written.  The next solve with the usual limit has the launches' bits."""
 import pytest
 
 import fvcases as fc
-from tests.gpu_util import DevCase, say
+from tests.gpu_util import DevCase, say, to_dev
 from tests.test_gpu_resident import fv  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -53,3 +53,32 @@ def test_lost_wait_streamed(fv, monkeypatch, method):  # noqa: F811
     check(fv, monkeypatch, "streamed " + method,
           lambda: fv.solve(dc.A, dc.b, x=torch.zeros_like(dc.b), tol=1e-4, method=method))
     dc.close()
+
+
+@pytest.mark.parametrize("method", ["pipecg", "cg"])
+def test_lost_wait_in_a_batch(fv, monkeypatch, method):  # noqa: F811
+    """The bound of a batch handle's waits (FVPCG_BATCH_BARRIER_TIMEOUT_MS at
+    its creation) holds for teams in one launch too."""
+    import torch
+
+    bt = fc.concat([fc.varcoef(s, seed=1, permute=False) for s in ((20, 20, 20), (33, 20, 17))])
+
+    def batch():
+        return fv.Batch(bt.cell_off, bt.face_off, to_dev(bt.owner, torch.int32), to_dev(bt.neighbour, torch.int32),
+                        to_dev(bt.diag), to_dev(bt.upper))
+
+    say("lost wait batch", method)
+    b = to_dev(bt.b)
+    B = batch()
+    want, st, code = fv.solve_batched(B, b, x=torch.zeros_like(b), tol=1e-9, method=method)
+    assert code == 0
+    monkeypatch.setenv("FVPCG_BATCH_BARRIER_TIMEOUT_MS", "0")
+    B0 = batch()
+    monkeypatch.delenv("FVPCG_BATCH_BARRIER_TIMEOUT_MS")
+    with pytest.raises(fv.FVPCGError) as e:
+        fv.solve_batched(B0, b, x=torch.zeros_like(b), tol=1e-9, method=method)
+    assert e.value.code == fv.DEVICE_ERROR and "wait between workgroups" in str(e.value)
+    x, again, code = fv.solve_batched(B, b, x=torch.zeros_like(b), tol=1e-9, method=method)
+    assert code == 0 and torch.equal(x, want) and [s["iters"] for s in again] == [s["iters"] for s in st]
+    B0.close()
+    B.close()

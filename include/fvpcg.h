@@ -253,11 +253,13 @@ FVPCG_API int fvpcg_batch_destroy(fvpcg_batch* batch);
  * synchronise through device memory.  A launch with teams uses exactly the
  * device's resident workgroup capacity, so kernels running at the same time
  * on other streams can delay members; each wait is bounded
- * (FVPCG_BATCH_BARRIER_TIMEOUT_MS, default 5000): on a timeout every
- * workgroup leaves, x and stats are invalid and FVPCG_DEVICE_ERROR is
- * returned.  The first call per batch shape not solved as above times the launch candidates
- * (block size, workgroups per CU, teams on/off) and caches the choice in
- * $FVPCG_TUNE_CACHE (FVPCG_TUNE=0: fixed defaults; FVPCG_BATCH_TEAMS=0/1:
+ * (FVPCG_BATCH_BARRIER_TIMEOUT_MS, default 5000, read at creation; the time a
+ * system waits for workgroups still at work on earlier ones does not count):
+ * on a timeout every workgroup leaves, x and stats are invalid and
+ * FVPCG_DEVICE_ERROR is returned.  The first call per batch shape not solved
+ * as above times the launch candidates (block size, workgroups per CU, teams
+ * on/off) and caches the choice in $FVPCG_TUNE_CACHE (FVPCG_TUNE=0: fixed
+ * defaults; FVPCG_BATCH_TEAMS=0/1:
  * never/always form teams).  Calls on one batch handle must not overlap. */
 FVPCG_API int fvpcg_solve_batched(const fvpcg_batch* batch, const double* b, double* x, double tol,
                         int32_t maxit, int32_t method, int32_t precond, void* stream,

@@ -96,6 +96,7 @@ struct ResTeam {
     int* ok;                  // LDS: 1 until this workgroup has given up a wait
     unsigned long long meet_ticks, spin_ticks;
     int k;                    // reductions so far
+    bool queued = false;      // members may still be solving an earlier system of their lists (batches)
 };
 
 // Agent-scope accesses of exchanged data.
@@ -279,7 +280,12 @@ __device__ __forceinline__ bool team_sum(double (&v)[NV], ResTeam& t) {
         constexpr int kC = kResMaxTeam / 64;
         double g[kC];
         unsigned spins = 0;
-        const unsigned every = t.spin_ticks ? 63u : 0u;  // a limit of 0: given up at the first poll that finds a sum missing
+        // A queued team's first sums come when its last member has finished
+        // its earlier systems, which takes as long as these do (every member
+        // is resident and each list is in the same order, so it ends); from
+        // the second reduction on all members are at work on this system.
+        const unsigned long long limit = t.queued && t.k == 0 ? ~0ull : t.spin_ticks;
+        const unsigned every = limit ? 63u : 0u;  // a limit of 0: given up at the first poll that finds a sum missing
         const unsigned long long t0 = (unsigned long long)wall_clock64();
         for (;;) {
             bool wait = false;
@@ -293,7 +299,7 @@ __device__ __forceinline__ bool team_sum(double (&v)[NV], ResTeam& t) {
             }
             if (!__any(wait)) break;
             if ((++spins & every) == 0 &&
-                ((unsigned long long)wall_clock64() - t0 > t.spin_ticks ||
+                ((unsigned long long)wall_clock64() - t0 > limit ||
                  __hip_atomic_load(t.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
                 if (lane == 0) {
                     __hip_atomic_store(t.abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

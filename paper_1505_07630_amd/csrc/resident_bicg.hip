@@ -44,6 +44,7 @@ __global__ __launch_bounds__(kResBsPipe) void k_res_bicg(const CI* __restrict__ 
     if (threadIdx.x == 0) s_ok = 1;
     t.rank = res_rank((int)blockIdx.x, t.size);
     t.ok = &s_ok;
+    t.queued = false;
     if (!team_meet(t)) return;
     const int G = t.size, tiles = (n + BS - 1) / BS;
     const int mine = t.rank < tiles ? (tiles - t.rank + G - 1) / G : 0;

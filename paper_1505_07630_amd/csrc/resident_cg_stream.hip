@@ -31,6 +31,7 @@ __global__ __launch_bounds__(kResBsCg) void k_res_cg_stream(PipeVec<double> a, i
     if (threadIdx.x == 0) s_ok = 1;
     t.rank = res_rank((int)blockIdx.x, t.size);
     t.ok = &s_ok;
+    t.queued = false;
     if (!team_meet(t)) return;
     const CI* __restrict__ col = (const CI*)a.col;
     const double* __restrict__ val = a.val;

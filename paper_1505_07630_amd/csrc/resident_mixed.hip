@@ -15,6 +15,7 @@ __global__ __launch_bounds__(kResBsMixed) void k_res_pipe32(PipeVec<float> a, in
     if (threadIdx.x == 0) s_ok = 1;
     t.rank = (int)blockIdx.x;  // numbered by XCD (res_rank) 3% slower here
     t.ok = &s_ok;
+    t.queued = false;
     if (st->done || st_skip->done) return;  // as every member sees them
     if (!team_meet(t)) {
         if (threadIdx.x == 0) st_skip->done = kResNoTeam;

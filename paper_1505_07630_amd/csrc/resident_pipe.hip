@@ -14,6 +14,7 @@ __global__ __launch_bounds__(kResBsPipe) void k_res_pipe(ResSystem sys, ResTeam 
     if (threadIdx.x == 0) s_ok = 1;
     t.rank = res_rank((int)blockIdx.x, t.size);
     t.ok = &s_ok;
+    t.queued = false;
     if (ONE) {
         t.rank = 0;
         t.size = 1;
@@ -43,6 +44,7 @@ __global__ __launch_bounds__(kResBsPipe) void k_res_batch_pipe(ResSystem sys, Re
         tm.size = task.z;
         tm.slots = t.slots + (size_t)kResBufs * kResSums * task.w;
         tm.k = 0;
+        tm.queued = true;
         sys.c0 = bt.cell_off[task.x];
         sys.c1 = bt.cell_off[task.x + 1];
         if (sys.c0 == sys.c1) {  // no rows: b = 0

@@ -13,6 +13,7 @@ __global__ __launch_bounds__(kResBsPipe) void k_res_stream(PipeVec<double> a, in
     if (threadIdx.x == 0) s_ok = 1;
     t.rank = res_rank((int)blockIdx.x, t.size);
     t.ok = &s_ok;
+    t.queued = false;
     if (!team_meet(t)) return;
     resident_stream<NT, WT, CI, JAC>(a, n, t, lds, st, out);
 }

@@ -2,6 +2,7 @@
 from the host, so every workgroup leaves by itself) ends the call with
 DEVICE_ERROR: it is not continued by launches from an x that members may have
 written.  The next solve with the usual limit has the launches' bits."""
+import numpy as np
 import pytest
 
 import fvcases as fc
@@ -82,3 +83,27 @@ def test_lost_wait_in_a_batch(fv, monkeypatch, method):  # noqa: F811
     assert code == 0 and torch.equal(x, want) and [s["iters"] for s in again] == [s["iters"] for s in st]
     B0.close()
     B.close()
+
+
+def test_queueing_is_not_a_lost_wait(fv, monkeypatch):  # noqa: F811
+    """Teams of 99, 99 and 81 members on 256 workgroups: 58 members of the third
+    system wait for the other 23 until these have finished a larger system.
+    At a limit (of each wait) far below the time of that solve the batch ends
+    with the usual bits."""
+    import torch
+
+    say("queued batch, short limit")
+    bt = fc.concat([fc.varcoef((e, e, e), seed=e + k, permute=False) for k, e in enumerate((74, 74, 69))])
+    assert [-(-c // 4096) for c in np.diff(bt.cell_off)] == [99, 99, 81]
+    got = []
+    for limit in ("5000", "2"):
+        monkeypatch.setenv("FVPCG_BATCH_BARRIER_TIMEOUT_MS", limit)
+        B = fv.Batch(bt.cell_off, bt.face_off, to_dev(bt.owner, torch.int32), to_dev(bt.neighbour, torch.int32),
+                     to_dev(bt.diag), to_dev(bt.upper))
+        b = to_dev(bt.b)
+        x, st, code = fv.solve_batched(B, b, x=torch.zeros_like(b), tol=0.0, maxit=1200, method="cg")
+        assert code == fv.NOT_CONVERGED and [s["iters"] for s in st] == [1200] * 3
+        assert st[0]["device_ms"] > 8.0  # the queued system began after at least half of it
+        got.append(x)
+        B.close()
+    assert torch.equal(got[0], got[1])

@@ -92,7 +92,7 @@ typedef struct fvpcg_stats {
     int32_t iters;        /* updates of x (inner iterations summed for the mixed solver) */
     int32_t outer_iters;  /* refinement steps (mixed solver), else 0 */
     int32_t status;       /* the fvpcg_status of the solve */
-    int32_t reserved;
+    int32_t one_launch;   /* 1: the (last) solve's iterations ran in one launch, see below; else 0 */
     double rel_res;       /* recursive residual norm / ||b||_2 at exit */
     double true_rel_res;  /* ||b - A x||_2 / ||b||_2 recomputed at exit */
     double r0_norm;       /* ||b - A x0||_2 */

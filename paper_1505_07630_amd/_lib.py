@@ -32,12 +32,12 @@ PP = ctypes.POINTER(ctypes.c_void_p)
 
 class Stats(ctypes.Structure):
     _fields_ = [("iters", ctypes.c_int32), ("outer_iters", ctypes.c_int32), ("status", ctypes.c_int32),
-                ("reserved", ctypes.c_int32), ("rel_res", ctypes.c_double), ("true_rel_res", ctypes.c_double),
+                ("one_launch", ctypes.c_int32), ("rel_res", ctypes.c_double), ("true_rel_res", ctypes.c_double),
                 ("r0_norm", ctypes.c_double), ("b_norm", ctypes.c_double), ("device_ms", ctypes.c_double),
                 ("iter_ms", ctypes.c_double)]
 
     def asdict(self):
-        d = {k: getattr(self, k) for k, _ in self._fields_ if k != "reserved"}
+        d = {k: getattr(self, k) for k, _ in self._fields_}
         d["status_name"] = STATUS_NAMES.get(self.status, str(self.status))
         return d
 

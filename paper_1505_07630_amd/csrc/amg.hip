@@ -780,6 +780,7 @@ int solve_amg(const fvpcg_amg* ch, const double* b, double* x, double tol, int m
     if (stats) {
         stats->iters = hs.iter;
         stats->outer_iters = 0;
+        stats->one_launch = 0;
         stats->status = hs.status;
         stats->b_norm = hs.bnorm;
         stats->r0_norm = hs.r0norm;

@@ -877,12 +877,12 @@ int check_abort(fvpcg_batch* bt, hipStream_t s) {
     return FVPCG_OK;
 }
 
-void batch_stats(const BatchStat& h, float ms, fvpcg_stats* o) {
+void batch_stats(const BatchStat& h, float ms, bool one_launch, fvpcg_stats* o) {
     if (!o) return;
     o->iters = h.iters;
     o->outer_iters = 0;
     o->status = h.status;
-    o->reserved = 0;
+    o->one_launch = one_launch ? 1 : 0;
     o->b_norm = h.bnorm;
     o->r0_norm = h.r0norm;
     o->rel_res = h.bnorm > 0 ? sqrt(h.rho) / h.bnorm : 0.0;
@@ -1112,7 +1112,7 @@ int solve_batched_resident(fvpcg_batch* bt, const double* b, double* x, double t
     for (int i = 0; i < bt->nsys; ++i) {
         const ResOut& h = bt->h_rout[i];
         const BatchStat st{h.iter, h.status, h.bnorm, h.r0norm, h.rho, h.true_rr};
-        batch_stats(st, ms, stats ? &stats[i] : nullptr);
+        batch_stats(st, ms, true, stats ? &stats[i] : nullptr);
         if (*overall == FVPCG_OK && h.status != FVPCG_OK) *overall = h.status;
     }
     return FVPCG_OK;
@@ -1309,7 +1309,7 @@ int solve_batched(const fvpcg_batch* cbt, const double* b, double* x, double tol
     (void)hipEventElapsedTime(&ms, bt->e0, bt->e1);
     for (int i = 0; i < bt->nsys; ++i) {
         const BatchStat& h = bt->h_stats[i];
-        batch_stats(h, ms, stats ? &stats[i] : nullptr);
+        batch_stats(h, ms, false, stats ? &stats[i] : nullptr);
         if (overall == FVPCG_OK && h.status != FVPCG_OK) overall = h.status;
     }
     if (overall == FVPCG_BREAKDOWN) set_error(overall, "breakdown in at least one system");

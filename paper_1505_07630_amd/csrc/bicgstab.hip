@@ -518,9 +518,9 @@ int bi_solve(const fvpcg_matrix* A, const double* b, double* x, double tol, int 
     for (int k = 0; k < NR; ++k)
         if (h[k].zero_b) FV_HIP(hipMemsetAsync(x + (size_t)k * n, 0, sizeof(double) * (size_t)n, s));
     FV_HIP(hipEventRecord(w.t_it0, s));
-    bool done = bi_all_done(h, NR);
-    if (!done && (rc = resident_bicg_run(A, w, NR, val, x, jac, s, &done))) return rc;
-    if (!done) {
+    bool done = bi_all_done(h, NR), one_launch = false;
+    if (!done && (rc = resident_bicg_run(A, w, NR, val, x, jac, s, &one_launch))) return rc;
+    if (!done && !one_launch) {
         // Iterations are enqueued in growing chunks; after each chunk the
         // states are copied to pinned memory, and the previous chunk's copy
         // is inspected while the current one runs.  Kernels enqueued after
@@ -575,6 +575,7 @@ int bi_solve(const fvpcg_matrix* A, const double* b, double* x, double tol, int 
             sk->iters = h[k].iter;
             sk->outer_iters = 0;
             sk->status = h[k].status;
+            sk->one_launch = one_launch ? 1 : 0;
             sk->b_norm = h[k].bnorm;
             sk->r0_norm = h[k].r0norm;
             sk->rel_res = h[k].bnorm > 0 ? sqrt(h[k].rr) / h[k].bnorm : 0.0;

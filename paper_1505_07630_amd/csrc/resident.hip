@@ -226,6 +226,7 @@ int resident_solve(const fvpcg_matrix* A, const ResPlan& plan, const ResWork& w,
         stats->iters = host.iter;
         stats->outer_iters = 0;
         stats->status = host.status;
+        stats->one_launch = 1;
         stats->b_norm = host.bnorm;
         stats->r0_norm = host.r0norm;
         stats->rel_res = host.bnorm > 0 ? sqrt(host.rho) / host.bnorm : 0.0;

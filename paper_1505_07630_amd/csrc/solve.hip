@@ -1017,6 +1017,7 @@ int solve_core(const fvpcg_matrix* A, Work& w, const double* b, double* x, doubl
         stats->iters = h.iter;
         stats->outer_iters = 0;
         stats->status = h.status;
+        stats->one_launch = streamed ? 1 : 0;
         stats->b_norm = h.bnorm;
         stats->r0_norm = h.r0norm;
         stats->rel_res = h.bnorm > 0 ? sqrt(h.rho) / h.bnorm : 0.0;
@@ -1179,6 +1180,7 @@ int solve_mixed(const fvpcg_matrix* A, const double* b, double* x, double outer_
         stats->iters = inner_total;
         stats->outer_iters = h.iter;
         stats->status = h.status;
+        stats->one_launch = 0;
         stats->b_norm = h.bnorm;
         stats->r0_norm = h.r0norm;
         stats->rel_res = h.bnorm > 0 ? h.scale / h.bnorm : 0.0;
@@ -1292,6 +1294,7 @@ int solve_mixed_reliable(const fvpcg_matrix* A, const double* b, double* x, doub
         stats->iters = updates == 0 ? 0 : offset + hi.iter;
         stats->outer_iters = updates;
         stats->status = h.status;
+        stats->one_launch = plan.rpt && updates > 0 ? 1 : 0;
         stats->b_norm = h.bnorm;
         stats->r0_norm = h.r0norm;
         stats->rel_res = h.bnorm > 0 ? sqrt(h.rho) / h.bnorm : 0.0;

@@ -1,0 +1,125 @@
+"""Which path a solve took (stats' one_launch): at every size of the tests that
+compare the one-launch forms with the launches, where they have to run and
+where they end; just past their limits; and switched off.  A handful of iterations is
+enough to tell."""
+import pytest
+
+import fvcases as fc
+from tests import test_gpu_resident as res, test_gpu_resident_bicg as bicg, test_gpu_resident_cg_stream as cgs
+from tests.gpu_util import DevCase, say, to_dev
+from tests.test_gpu_resident import LINE, STAR, fv, stencil  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+METHODS = ("pipecg", "pipecg_literal", "cg")
+
+
+def path(fv, dc, method, **kw):  # noqa: F811
+    import torch
+
+    say("path", method, kw)
+    try:
+        return fv.solve(dc.A, dc.b, x=torch.zeros_like(dc.b), tol=0.0, maxit=3, method=method, **kw)[1]["one_launch"]
+    except fv.FVPCGError as e:  # solved exactly: tol = 0 breaks down, without stats
+        assert e.code == fv.BREAKDOWN
+        return None
+
+
+SOLVES = {**{k: (m, "0" if "col32" in o else "1") for k, (m, o) in res.CASES.items()}, **res.STREAMED, **cgs.SHAPES,
+          "line-8388608": (lambda: stencil(8388608, 1, LINE, 1), "1")}
+CG_MOST, LITERAL_MOST = 4194304, 524288
+
+
+@pytest.mark.parametrize("name", list(SOLVES))
+def test_solve_path(fv, monkeypatch, name):  # noqa: F811
+    make, col16 = SOLVES[name]
+    monkeypatch.setenv("FVPCG_COL16", col16)
+    case = make()
+    dc = DevCase(case)
+    for method in METHODS:
+        most = {"pipecg": 1 << 23, "cg": CG_MOST, "pipecg_literal": LITERAL_MOST}[method]
+        got = path(fv, dc, method)
+        assert got == int(case.n <= most) or (got is None and case.n == 1), method
+    monkeypatch.setenv("FVPCG_RESIDENT", "0")
+    for method in METHODS:
+        assert not path(fv, dc, method)
+    dc.close()
+
+
+WIDE = [(i, j) for i in range(-1, 2) for j in range(3) if (i, j) > (0, 0)]  # 12 to 16 neighbours
+
+
+@pytest.mark.parametrize("name", ["line-8388609", "wide rows"])
+def test_solve_path_past_the_limits(fv, name):  # noqa: F811
+    dc = DevCase(stencil(8388609, 1, LINE, 1) if name != "wide rows" else stencil(60, 50, WIDE, 2))
+    assert [path(fv, dc, m) for m in METHODS] == [0, 0, 0]
+    dc.close()
+
+
+def test_noalloc_path(fv):  # noqa: F811
+    import torch
+
+    for shape in ((12, 11, 10), (40, 36, 30), (128, 64, 128)):
+        dc = DevCase(fc.varcoef(shape, seed=3, permute=False))
+        for method in ("pipecg", "cg"):
+            say("noalloc path", shape, method)
+            _, st = fv.solve_noalloc(dc.A, dc.b, torch.zeros_like(dc.b), tol=0.0, maxit=3, method=method)
+            assert st["one_launch"] == 1
+        dc.close()
+
+
+@pytest.mark.parametrize("name", list(bicg.SHAPES))
+def test_bicgstab_path(fv, monkeypatch, name):  # noqa: F811
+    import torch
+
+    case = fc.momentum(bicg.SHAPES[name], permute=False)
+    dc = DevCase(case, symmetric=False)
+    for nr in (1, 2, 3, 4):
+        b = torch.stack([dc.b] * nr)
+        for on in (1, 0):
+            say("bicgstab path", name, nr, on)
+            monkeypatch.setenv("FVPCG_RESIDENT", str(on))
+            _, st = fv.solve_bicgstab_multi(dc.A, b, x=torch.zeros_like(b), tol=1e-10, maxit=2)
+            most = {1: 131072, 2: 1 << 21, 3: 1 << 21, 4: 0}[nr]
+            assert [s["one_launch"] for s in st] == [int(on and case.n <= most)] * nr
+    dc.close()
+
+
+MIXED = {**res.MIXED, "cube-2097152": lambda: fc.varcoef((128, 128, 128), seed=11, permute=False),
+         "past": lambda: fc.varcoef((129, 128, 128), seed=11, permute=False)}
+
+
+@pytest.mark.parametrize("name", list(MIXED))
+def test_mixed_path(fv, monkeypatch, name):  # noqa: F811
+    case = MIXED[name]()
+    for col16, most in (("1", 1 << 21), ("0", 1 << 20)):
+        monkeypatch.setenv("FVPCG_COL16", col16)
+        dc = DevCase(case, fp32_copy=True)
+        for on in (1, 0):
+            say("mixed path", name, col16, on)
+            monkeypatch.setenv("FVPCG_RESIDENT", str(on))
+            _, st = fv.solve_mixed_reliable(dc.A, dc.b, tol=0.0, update_every=7, maxit=14)
+            assert st["one_launch"] == int(on and case.n <= most)
+        dc.close()
+
+
+def test_batch_path(fv, monkeypatch):  # noqa: F811
+    import torch
+
+    monkeypatch.setenv("FVPCG_TUNE", "0")
+    small = [fc.varcoef((12, 12, 12), seed=k) for k in range(5)]  # 1,728 cells on average
+    for name, cases, want in [(k, m(), 1) for k, m in res.BATCHES.items()] + [
+            ("small", small, 0), ("2,048 on average", [stencil(2048, 1, LINE, 1), stencil(64, 32, STAR, 2)], 1)]:
+        bt = fc.concat(cases)
+        B = fv.Batch(bt.cell_off, bt.face_off, to_dev(bt.owner, torch.int32), to_dev(bt.neighbour, torch.int32),
+                     to_dev(bt.diag), to_dev(bt.upper))
+        b = to_dev(bt.b)
+        for method in ("pipecg", "cg"):
+            for on, teams in ((1, None), (0, None), (1, "0")):
+                say("batch path", name, method, on, teams)
+                monkeypatch.setenv("FVPCG_RESIDENT", str(on))
+                monkeypatch.delenv("FVPCG_BATCH_TEAMS", raising=False)
+                if teams is not None:
+                    monkeypatch.setenv("FVPCG_BATCH_TEAMS", teams)
+                _, st, _ = fv.solve_batched(B, b, x=torch.zeros_like(b), tol=1e-9, maxit=5, method=method)
+                assert [s["one_launch"] for s in st] == [int(want and on and teams is None)] * len(cases)
+        B.close()

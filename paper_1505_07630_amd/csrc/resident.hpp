@@ -141,9 +141,13 @@ __device__ __forceinline__ int res_rank(int b, int G) {
 
 // True once the whole team runs; false if it did not come together in time.
 // The word counts arrivals; a member whose time is up sets the abort bit
-// unless the last one has arrived meanwhile, so all members agree.
+// unless the last one has arrived meanwhile, so all members agree.  With no
+// time at all (0 ticks) no team comes together: the arrivals of a whole team
+// take about as long as a member's first look at the clock and the exchange
+// that sets the bit, which fails while the word still moves.
 __device__ __forceinline__ bool team_meet(const ResTeam& t) {
     __shared__ int s_go;
+    if (t.meet_ticks == 0) return false;
     if (threadIdx.x == 0) {
         unsigned w = __hip_atomic_fetch_add(t.meet, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
         const unsigned long long t0 = (unsigned long long)wall_clock64();

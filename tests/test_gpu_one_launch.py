@@ -55,6 +55,50 @@ def test_solve_path_past_the_limits(fv, name):  # noqa: F811
     dc.close()
 
 
+def test_no_time_to_meet_takes_launches(fv, monkeypatch):  # noqa: F811
+    """A rendezvous limit of zero is never met, whatever the team's size."""
+    monkeypatch.setenv("FVPCG_RESIDENT_MEET_MS", "0")
+    for shape, meets in (((17, 13, 20), 0), ((128, 64, 128), 0), ((128, 128, 128), 0), ((12, 11, 10), 1)):
+        dc = DevCase(fc.varcoef(shape, seed=11, permute=False))  # the last: one workgroup, nobody to meet
+        for method in ("pipecg", "cg"):
+            assert path(fv, dc, method) == meets
+        dc.close()
+
+
+@pytest.mark.parametrize("shape", [(17, 13, 11), (128, 128, 120)])
+def test_no_time_to_meet_other_solvers(fv, monkeypatch, shape):  # noqa: F811
+    """Mixed precision, BiCGSTAB and batches go on by launches from where the
+    team left: the bits of the launches."""
+    import torch
+
+    monkeypatch.setenv("FVPCG_TUNE", "0")
+    case = fc.varcoef(shape, seed=11, permute=False)
+    dc = DevCase(case, fp32_copy=True)
+    b3 = torch.stack([dc.b, dc.b.flip(0), 3.0 * dc.b])
+    bt = fc.concat([fc.varcoef(s, seed=1, permute=False) for s in ((20, 20, 20), (33, 20, 17))])
+    B = fv.Batch(bt.cell_off, bt.face_off, to_dev(bt.owner, torch.int32), to_dev(bt.neighbour, torch.int32),
+                 to_dev(bt.diag), to_dev(bt.upper))
+    bb = to_dev(bt.b)
+    runs = {
+        "mixed": lambda: fv.solve_mixed_reliable(dc.A, dc.b, tol=0.0, update_every=7, maxit=35),
+        "bicgstab": lambda: fv.solve_bicgstab_multi(dc.A, b3, x=torch.zeros_like(b3), tol=1e-10, maxit=20),
+        "batch": lambda: fv.solve_batched(B, bb, x=torch.zeros_like(bb), tol=1e-9, maxit=300)[:2],
+    }
+    for name, run in runs.items():
+        got = []
+        for on, meet in (("0", "20"), ("1", "0"), ("1", "20")):
+            say("no time", name, shape, on, meet)
+            monkeypatch.setenv("FVPCG_RESIDENT", on)
+            monkeypatch.setenv("FVPCG_RESIDENT_MEET_MS", meet)
+            x, st = run()
+            st = st if isinstance(st, list) else [st]
+            assert all(s["one_launch"] == int((on, meet) == ("1", "20")) for s in st), (name, on, meet)
+            got.append((x.clone(), [(s["iters"], s["r0_norm"], s["rel_res"]) for s in st]))
+        assert torch.equal(got[0][0], got[1][0]) and got[0][1] == got[1][1], name
+    B.close()
+    dc.close()
+
+
 def test_noalloc_path(fv):  # noqa: F811
     import torch
 

@@ -231,8 +231,9 @@ FVPCG_API int fvpcg_solve_backward(const fvpcg_matrix* mat, const double* x, con
  * together: if they have not met within FVPCG_RESIDENT_MEET_MS (default 20),
  * or another such solve is running on the device, the call iterates launch by
  * launch instead, as with FVPCG_RESIDENT=0, with the same results (bit for
- * bit, but for batches, whose sums are ordered otherwise).  Each later wait of
- * a solve is bounded too (FVPCG_RESIDENT_SPIN_MS, default 5000): past it every
+ * bit, but for batches, whose sums are ordered otherwise); after a missed
+ * meeting so do the device's next calls, for 50 times that limit.  Each later
+ * wait of a solve is bounded too (FVPCG_RESIDENT_SPIN_MS, default 5000): past it every
  * workgroup leaves, x and stats are invalid and FVPCG_DEVICE_ERROR is
  * returned. */
 

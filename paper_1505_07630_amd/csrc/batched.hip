@@ -1067,8 +1067,8 @@ int solve_batched_resident(fvpcg_batch* bt, const double* b, double* x, double t
         }
     }
     const ResBatchPlan& p = bt->res;
-    if (!p.rpt) return FVPCG_OK;
     const fvpcg_mesh* m = bt->mesh;
+    if (!p.rpt || resident_quiet(m->device)) return FVPCG_OK;
     std::mutex* mu = resident_teams(m->device);
     if (!mu) return FVPCG_OK;
     std::unique_lock<std::mutex> lock(*mu, std::try_to_lock);
@@ -1104,7 +1104,7 @@ int solve_batched_resident(fvpcg_batch* bt, const double* b, double* x, double t
     FV_HIP(hipMemcpyAsync(bt->h_rout, bt->d_rout, sizeof(ResOut) * bt->nsys, hipMemcpyDeviceToHost, s));
     FV_HIP(hipStreamSynchronize(s));
     for (int i = 0; i < bt->nsys; ++i)
-        if (!bt->h_rout[i].ok) return resident_no_result(abort_flag, "batched solve", s);
+        if (!bt->h_rout[i].ok) return resident_no_result(m->device, abort_flag, "batched solve", s);
     *done = true;
     float ms = 0;
     (void)hipEventElapsedTime(&ms, bt->e0, bt->e1);

@@ -1,7 +1,8 @@
 // Host side of the resident solves (resident.hpp): which systems take that
 // path, its launch, and what to do when the team does not come together.
+#include <atomic>
+#include <chrono>
 #include <cstdlib>
-
 #include <mutex>
 
 #include "resident.hpp"
@@ -26,10 +27,28 @@ constexpr int kMaxDevices = 64;
 struct DeviceInfo {
     std::once_flag once;
     std::mutex teams;
+    std::atomic<long long> quiet_until{0};  // steady clock, ns: no team before (resident_missed)
     int cus = 0;
     double ticks_per_ms = 0;
 };
 DeviceInfo g_dev[kMaxDevices];
+
+long long now_ns() {
+    return std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now().time_since_epoch())
+        .count();
+}
+
+// A missed rendezvous has cost the call its whole limit.  What holds the CUs (a
+// second process, a stream with a CU mask, long kernels) is likely to hold
+// them in the next call too, so the device's solves go by launches for
+// kQuiet times that limit: at most 2% of the time goes into teams that do not
+// meet.  20 solves of 1M cells and 20 iterations on a stream with half of the
+// CUs, after the first: 826 ms when every call waits (twice), 24 without.
+constexpr double kQuiet = 50.0;
+bool quiet(int device) {
+    const long long until = g_dev[device].quiet_until.load(std::memory_order_relaxed);
+    return until && now_ns() < until;
+}
 
 const DeviceInfo& device_info(int dev) {
     DeviceInfo& d = g_dev[dev];
@@ -70,13 +89,21 @@ double resident_spin_ms() {
     return env && *env ? std::max(0.0, atof(env)) : kResSpinMs;
 }
 
-int resident_no_result(const int* abort_flag, const char* what, hipStream_t s) {
+void resident_missed(int device) {
+    if (device < 0 || device >= kMaxDevices) return;
+    g_dev[device].quiet_until.store(now_ns() + (long long)(kQuiet * 1e6 * resident_meet_ms()), std::memory_order_relaxed);
+}
+
+int resident_no_result(int device, const int* abort_flag, const char* what, hipStream_t s) {
     int gave_up = 0;
     FV_HIP(hipMemcpyAsync(&gave_up, abort_flag, sizeof(int), hipMemcpyDeviceToHost, s));
     FV_HIP(hipStreamSynchronize(s));
     if (gave_up) return set_error(FVPCG_DEVICE_ERROR, "%s: a wait between workgroups timed out (x is invalid)", what);
+    resident_missed(device);
     return FVPCG_OK;
 }
+
+bool resident_quiet(int device) { return device >= 0 && device < kMaxDevices && quiet(device); }
 
 int resident_reset(double* slots, size_t count, unsigned* meet, int* abort_flag, ResOut* out, int nout, hipStream_t s) {
     const size_t work = std::max(count, (size_t)nout);
@@ -112,7 +139,7 @@ ResPlan resident_plan(const fvpcg_mesh* m, int method) {
     int rpt = (tiles + g - 1) / g;
     if (rpt == 5 || rpt == 7) ++rpt;
     const int rows = m->WT > 6 || method == FVPCG_PIPECG_LITERAL ? 2048 : m->col16 ? 4096 : 3072;
-    if (rpt * bs > rows || g > device_info(m->device).cus) return p;
+    if (rpt * bs > rows || g > device_info(m->device).cus || quiet(m->device)) return p;
     p.size = g;
     p.rpt = rpt;
     return p;
@@ -128,7 +155,9 @@ ResPlan resident_plan_stream(const fvpcg_mesh* m, int method) {
     const int tiles = (m->n + bs - 1) / bs;
     const int g = std::min(tiles, kMaxGrid);  // geom_for's workgroups
     const int per = (tiles + g - 1) / g;
-    if (per > (method == FVPCG_CG ? 16 : kStreamTiles) || g > info.cus || info.ticks_per_ms <= 0) return p;
+    if (per > (method == FVPCG_CG ? 16 : kStreamTiles) || g > info.cus || info.ticks_per_ms <= 0 ||
+        quiet(m->device))
+        return p;
     p.method = method;
     p.block = bs;
     p.size = g;
@@ -160,7 +189,7 @@ int resident_stream_run(const fvpcg_mesh* m, const ResPlan& plan, const ResWork&
         *done = true;
         return FVPCG_OK;
     }
-    return resident_no_result(w.abort_flag, "CG", s);
+    return resident_no_result(m->device, w.abort_flag, "CG", s);
 }
 
 ResPlan resident_plan32(const fvpcg_mesh* m) {
@@ -174,7 +203,9 @@ ResPlan resident_plan32(const fvpcg_mesh* m) {
     int rpt = (tiles + g - 1) / g;
     rpt = rpt <= 2 ? rpt : rpt <= 4 ? 4 : rpt <= 6 ? 6 : rpt;
     if (rpt == 7) rpt = 8;
-    if (rpt > (m->WT > 6 || !m->col16 ? 4 : 8) || g > info.cus || info.ticks_per_ms <= 0) return p;
+    if (rpt > (m->WT > 6 || !m->col16 ? 4 : 8) || g > info.cus || info.ticks_per_ms <= 0 ||
+        quiet(m->device))
+        return p;
     p.block = kResBsMixed;
     p.size = g;
     p.rpt = rpt;
@@ -220,7 +251,7 @@ int resident_solve(const fvpcg_matrix* A, const ResPlan& plan, const ResWork& w,
     if (!w.pinned) FV_HIP(hipMemcpyAsync(&host, w.out, sizeof(ResOut), hipMemcpyDeviceToHost, s));
     FV_HIP(hipStreamSynchronize(s));
     if (w.pinned) host = *w.pinned;
-    if (!host.ok) return resident_no_result(w.abort_flag, "CG", s);
+    if (!host.ok) return resident_no_result(m->device, w.abort_flag, "CG", s);
     *done = true;
     if (stats) {
         stats->iters = host.iter;

@@ -269,7 +269,7 @@ int resident_bicg_run(const fvpcg_matrix* A, BiWork& w, int nr, const double* va
         *done = true;
         return FVPCG_OK;
     }
-    return resident_no_result(abort_flag, "BiCGSTAB", s);
+    return resident_no_result(m->device, abort_flag, "BiCGSTAB", s);
 }
 
 }  // namespace fvpcg

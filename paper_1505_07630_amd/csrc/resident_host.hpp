@@ -60,7 +60,11 @@ double resident_meet_ms();
 double resident_spin_ms();
 // After a launch whose result is missing: FVPCG_OK if the team did not come
 // together (nothing was written), FVPCG_DEVICE_ERROR if a later wait was given up.
-int resident_no_result(const int* abort_flag, const char* what, hipStream_t s);
+int resident_no_result(int device, const int* abort_flag, const char* what, hipStream_t s);
+// A rendezvous was missed on the device; whether one was missed so recently
+// that no team is tried (the plans ask it by themselves).
+void resident_missed(int device);
+bool resident_quiet(int device);
 // CUs, and wall-clock ticks per ms (0: unknown) of a device.
 void resident_device(int device, int* cus, double* ticks_per_ms);
 // Enqueues the reset of `count` slot doubles, the rendezvous word, the abort

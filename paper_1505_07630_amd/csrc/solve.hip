@@ -1262,6 +1262,7 @@ int solve_mixed_reliable(const fvpcg_matrix* A, const double* b, double* x, doub
                 return set_error(FVPCG_DEVICE_ERROR, "mixed solve: a wait between workgroups timed out (x is invalid)");
             if (h.done == kResNoTeam) {  // nothing was done since the last update: go on by launches
                 plan.rpt = 0;
+                resident_missed(m->device);
                 lock.unlock();
                 --updates;
                 wi = wi0;

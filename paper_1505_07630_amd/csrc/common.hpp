@@ -12,6 +12,7 @@
 #include <string>
 
 #include "fvpcg.h"
+#include "memory.hpp"
 
 namespace fvpcg {
 
@@ -122,10 +123,6 @@ int hip_fail(hipError_t e, const char* what, const char* file, int line);
         hipError_t fv_e_ = hipGetLastError();                              \
         if (fv_e_ != hipSuccess) return ::fvpcg::hip_fail(fv_e_, "kernel launch", __FILE__, __LINE__); \
     } while (0)
-
-// Device memory, kept for reuse when freed (memory.hip).
-hipError_t pool_alloc(void** out, size_t bytes);
-void pool_free(void* p);
 
 template <typename T>
 int dev_alloc(T** p, size_t count, const char* what) {

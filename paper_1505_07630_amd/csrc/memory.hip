@@ -12,12 +12,17 @@
 // wait.  At most kPoolBytes per device are kept, larger blocks first given
 // back; an allocation that fails gives everything back and tries again; and
 // when the last live block of a device is freed, nothing is kept at all.
+//
+// No call into the runtime is made with the lock held: one that waits for a
+// device (hipDeviceSynchronize, hipFree) would keep every other thread from
+// its memory for that long, on other devices too.  The blocks such a call is
+// about are out of both lists meanwhile (`moving`).
+#include <condition_variable>
 #include <map>
 #include <mutex>
 #include <unordered_map>
-#include <vector>
 
-#include "common.hpp"
+#include "memory.hpp"
 
 namespace fvpcg {
 
@@ -25,10 +30,13 @@ namespace {
 
 constexpr size_t kPoolBytes = (size_t)8 << 30;
 
+using Blocks = std::multimap<size_t, void*>;
+
 struct Pool {
-    std::multimap<size_t, void*> clean, pending;
-    size_t kept = 0;  // bytes in both
+    Blocks clean, pending;
+    size_t kept = 0;  // bytes in both, and in `pending` blocks being synchronised
     size_t live = 0;  // blocks handed out
+    int moving = 0;   // threads that hold some of the pool's blocks for a call
 };
 
 struct Block {
@@ -39,6 +47,7 @@ struct Block {
 // Never destroyed: handles may be freed while the process ends.
 struct Registry {
     std::mutex mu;
+    std::condition_variable settled;  // a pool's `moving` has dropped
     std::map<int, Pool> pools;
     std::unordered_map<void*, Block> blocks;
 };
@@ -60,26 +69,50 @@ size_t rounded(size_t bytes) {
     return (bytes + step - 1) / step * step;
 }
 
-void release(std::multimap<size_t, void*>& m, size_t* kept) {
-    for (auto& b : m) {
-        (void)hipFree(b.second);
-        *kept -= b.first;
+// Moves everything kept into `out`.
+void drop_all(Pool& p, Blocks& out) {
+    for (Blocks* m : {&p.pending, &p.clean}) {
+        for (auto& b : *m) p.kept -= b.first;
+        out.merge(*m);
     }
-    m.clear();
 }
 
-void release_all(Pool& p) {
-    release(p.pending, &p.kept);
-    release(p.clean, &p.kept);
+// Moves the largest blocks into `out` until at most `limit` bytes are kept.
+void drop_above(Pool& p, size_t limit, Blocks& out) {
+    while (p.kept > limit && !(p.clean.empty() && p.pending.empty())) {
+        Blocks& m = p.clean.empty() || (!p.pending.empty() && p.pending.rbegin()->first > p.clean.rbegin()->first)
+                        ? p.pending
+                        : p.clean;
+        auto last = std::prev(m.end());
+        p.kept -= last->first;
+        out.insert(m.extract(last));
+    }
+}
+
+// hipFree of `out`, which was taken from p with the lock held: `lock` is
+// released meanwhile.
+void give_back(Registry& r, Pool& p, Blocks& out, std::unique_lock<std::mutex>& lock) {
+    if (out.empty()) return;
+    p.moving += 1;
+    lock.unlock();
+    for (auto& b : out) (void)hipFree(b.second);
+    lock.lock();
+    p.moving -= 1;
+    r.settled.notify_all();
 }
 
 // A kept block of at least `bytes`, at most a quarter larger.
-void* take(std::multimap<size_t, void*>& m, size_t bytes, size_t* got) {
+Blocks::iterator fitting(Blocks& m, size_t bytes) {
     auto it = m.lower_bound(bytes);
-    if (it == m.end() || it->first > bytes + bytes / 4) return nullptr;
+    return it == m.end() || it->first > bytes + bytes / 4 ? m.end() : it;
+}
+void* take(Pool& p, size_t bytes, size_t* got) {
+    auto it = fitting(p.clean, bytes);
+    if (it == p.clean.end()) return nullptr;
     void* q = it->second;
     *got = it->first;
-    m.erase(it);
+    p.kept -= it->first;
+    p.clean.erase(it);
     return q;
 }
 
@@ -92,31 +125,38 @@ hipError_t pool_alloc(void** out, size_t bytes) {
     if (e != hipSuccess) return e;
     const size_t need = rounded(bytes ? bytes : 1);
     Registry& r = registry();
-    std::lock_guard<std::mutex> lock(r.mu);
+    std::unique_lock<std::mutex> lock(r.mu);
     Pool& p = r.pools[dev];
     size_t got = 0;
-    void* q = take(p.clean, need, &got);
-    if (!q && !p.pending.empty()) {
-        auto it = p.pending.lower_bound(need);
-        if (it != p.pending.end() && it->first <= need + need / 4) {
-            if (hipDeviceSynchronize() == hipSuccess) {
-                p.clean.insert(p.pending.begin(), p.pending.end());
-                p.pending.clear();
-                q = take(p.clean, need, &got);
-            } else {
-                (void)hipGetLastError();  // e.g. a capture is under way: a new block
-            }
-        }
+    void* q = take(p, need, &got);
+    if (!q && fitting(p.pending, need) != p.pending.end()) {
+        Blocks waiting;
+        waiting.swap(p.pending);
+        p.moving += 1;
+        lock.unlock();
+        const bool ok = hipDeviceSynchronize() == hipSuccess;
+        if (!ok) (void)hipGetLastError();  // e.g. a capture is under way: a new block
+        lock.lock();
+        (ok ? p.clean : p.pending).merge(waiting);
+        p.moving -= 1;
+        r.settled.notify_all();
+        q = take(p, need, &got);
     }
-    if (q) {
-        p.kept -= got;
-    } else {
+    if (!q) {
         got = need;
+        lock.unlock();
         e = hipMalloc(&q, need);
+        lock.lock();
         if (e != hipSuccess) {
             (void)hipGetLastError();
-            release_all(p);
+            // what other threads have in their hands comes back first
+            r.settled.wait(lock, [&] { return p.moving == 0; });
+            Blocks all;
+            drop_all(p, all);
+            give_back(r, p, all, lock);
+            lock.unlock();
             e = hipMalloc(&q, need);
+            lock.lock();
             if (e != hipSuccess) {
                 (void)hipGetLastError();
                 return e;
@@ -132,9 +172,10 @@ hipError_t pool_alloc(void** out, size_t bytes) {
 void pool_free(void* q) {
     if (!q) return;
     Registry& r = registry();
-    std::lock_guard<std::mutex> lock(r.mu);
+    std::unique_lock<std::mutex> lock(r.mu);
     auto it = r.blocks.find(q);
     if (it == r.blocks.end()) {
+        lock.unlock();
         (void)hipFree(q);
         return;
     }
@@ -144,19 +185,12 @@ void pool_free(void* q) {
     p.live -= 1;
     p.pending.insert({b.bytes, q});
     p.kept += b.bytes;
-    if (p.live == 0) {
-        release_all(p);
-        return;
-    }
-    while (p.kept > kPoolBytes) {
-        std::multimap<size_t, void*>& m =
-            p.clean.empty() || (!p.pending.empty() && p.pending.rbegin()->first > p.clean.rbegin()->first) ? p.pending
-                                                                                                             : p.clean;
-        auto last = std::prev(m.end());
-        (void)hipFree(last->second);
-        p.kept -= last->first;
-        m.erase(last);
-    }
+    Blocks out;
+    if (p.live == 0)
+        drop_all(p, out);
+    else
+        drop_above(p, kPoolBytes, out);
+    give_back(r, p, out, lock);
 }
 
 }  // namespace fvpcg

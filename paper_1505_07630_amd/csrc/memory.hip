@@ -116,10 +116,7 @@ void* take(Pool& p, size_t bytes, size_t* got) {
     return q;
 }
 
-}  // namespace
-
-hipError_t pool_alloc(void** out, size_t bytes) {
-    *out = nullptr;
+hipError_t alloc(void** out, size_t bytes) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -163,13 +160,30 @@ hipError_t pool_alloc(void** out, size_t bytes) {
             }
         }
     }
-    r.blocks[q] = {dev, got};
+    try {
+        r.blocks[q] = {dev, got};
+    } catch (...) {
+        lock.unlock();
+        (void)hipFree(q);
+        throw;
+    }
     p.live += 1;
     *out = q;
     return hipSuccess;
 }
 
-void pool_free(void* q) {
+}  // namespace
+
+hipError_t pool_alloc(void** out, size_t bytes) noexcept {
+    *out = nullptr;
+    try {
+        return alloc(out, bytes);
+    } catch (...) {  // no host memory for the bookkeeping
+        return hipErrorOutOfMemory;
+    }
+}
+
+void pool_free(void* q) noexcept {
     if (!q) return;
     Registry& r = registry();
     std::unique_lock<std::mutex> lock(r.mu);
@@ -183,14 +197,21 @@ void pool_free(void* q) {
     r.blocks.erase(it);
     Pool& p = r.pools[b.device];
     p.live -= 1;
-    p.pending.insert({b.bytes, q});
-    p.kept += b.bytes;
+    bool listed = true;
+    try {
+        p.pending.insert({b.bytes, q});
+        p.kept += b.bytes;
+    } catch (...) {  // no host memory to list it: freed below
+        listed = false;
+    }
     Blocks out;
     if (p.live == 0)
         drop_all(p, out);
     else
         drop_above(p, kPoolBytes, out);
     give_back(r, p, out, lock);
+    lock.unlock();
+    if (!listed) (void)hipFree(q);
 }
 
 }  // namespace fvpcg

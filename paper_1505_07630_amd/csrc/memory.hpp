@@ -7,8 +7,9 @@
 
 namespace fvpcg {
 
-// Device memory, kept for reuse when freed.
-hipError_t pool_alloc(void** out, size_t bytes);
-void pool_free(void* p);
+// Device memory, kept for reuse when freed.  Neither throws: frees run in
+// destructors, and on the way out of a C entry point.
+hipError_t pool_alloc(void** out, size_t bytes) noexcept;
+void pool_free(void* p) noexcept;
 
 }  // namespace fvpcg

@@ -250,6 +250,30 @@ void threads() {
     pool_free(get(1));
     CHECK(used == 0 && blocks.empty());
 }
+// No memory for the bookkeeping: an allocation fails with the runtime's code
+// and leaks nothing, a free still frees; neither throws (frees run in
+// destructors).
+void no_host_memory() {
+    void* live = get(MiB);
+    for (int k = 0; k < 6; ++k) {
+        const size_t before = used;
+        void* p = nullptr;
+        new_fails = k;
+        const hipError_t e = pool_alloc(&p, 3 * MiB);
+        const bool failed = new_fails == -1;
+        new_fails = -1;
+        CHECK(failed ? e == hipErrorOutOfMemory && !p && used == before : e == hipSuccess && p);
+        if (p) pool_free(p);
+    }
+    for (int k = 0; k < 3; ++k) {
+        void* p = get((5 + k) * MiB);
+        new_fails = k;
+        pool_free(p);
+        new_fails = -1;
+        CHECK(get((5 + k) * MiB) != nullptr);  // whatever became of it
+    }
+    (void)live;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -257,7 +281,8 @@ int main(int argc, char** argv) {
                                                          {"wait_in_alloc", wait_in_alloc},
                                                          {"wait_in_free", wait_in_free},
                                                          {"full", full},
-                                                         {"threads", threads}};
+                                                         {"threads", threads},
+                                                         {"no_host_memory", no_host_memory}};
     auto it = scenarios.find(argc > 1 ? argv[1] : "");
     if (it == scenarios.end()) return 2;
     it->second();

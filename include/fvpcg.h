@@ -23,7 +23,11 @@
  * library never frees caller memory and keeps no pointer to it after a call
  * returns: mesh and matrix data are copied into buffers owned by the handles,
  * which *_destroy frees.  Arrays: int32 addressing, FP64 coefficients and
- * vectors, all contiguous.
+ * vectors, all contiguous.  Device memory that handles and setups free is kept
+ * for the library's next allocations while any handle of that device lives:
+ * at most 8 GiB (FVPCG_POOL_MB=<MiB> sets another bound, 0 keeps nothing) and,
+ * past 256 MiB, an eighth of what the device has free.  Other allocators of the process
+ * cannot use it meanwhile; destroying the device's last handle gives it back.
  *
  * STREAMS.  `stream` is a hipStream_t (NULL = the null stream).  All device
  * work is enqueued on it.  Calls that return statistics block the host until

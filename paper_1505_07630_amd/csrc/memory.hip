@@ -9,15 +9,24 @@
 // A block that is freed may still be in use by work in flight on any stream
 // (as with hipFree, whose wait covered that): it waits in `pending`, and is
 // handed out again only after a device synchronisation, one for all that
-// wait.  At most kPoolBytes per device are kept, larger blocks first given
-// back; an allocation that fails gives everything back and tries again; and
+// wait.  An allocation that fails gives everything back and tries again; and
 // when the last live block of a device is freed, nothing is kept at all.
+//
+// What is kept is out of reach of the process's other allocators (torch's
+// caching one among them), so it is bounded, larger blocks given back first: by
+// kPoolBytes per device (FVPCG_POOL_MB sets another bound, 0 keeps nothing),
+// and past kSmallBytes by an eighth of what the device has free.  An AMG setup
+// leaves about 1.1 to 1.6 KB per cell (0.4 GiB at 64^3, 3.2 at 128^3, 7.4 at
+// 192^3), all of it kept while 64 GiB are free.
 //
 // No call into the runtime is made with the lock held: one that waits for a
 // device (hipDeviceSynchronize, hipFree) would keep every other thread from
 // its memory for that long, on other devices too.  The blocks such a call is
 // about are out of both lists meanwhile (`moving`).
+#include <algorithm>
+#include <chrono>
 #include <condition_variable>
+#include <cstdlib>
 #include <map>
 #include <mutex>
 #include <unordered_map>
@@ -28,7 +37,12 @@ namespace fvpcg {
 
 namespace {
 
-constexpr size_t kPoolBytes = (size_t)8 << 30;
+constexpr size_t kPoolBytes = (size_t)8 << 30, kSmallBytes = (size_t)256 << 20;
+
+using Clock = std::chrono::steady_clock;
+// The device's free memory is asked for no more often than this: a
+// setup frees some 270 blocks in a few milliseconds.
+constexpr auto kLookEvery = std::chrono::milliseconds(50);
 
 using Blocks = std::multimap<size_t, void*>;
 
@@ -37,6 +51,8 @@ struct Pool {
     size_t kept = 0;  // bytes in both, and in `pending` blocks being synchronised
     size_t live = 0;  // blocks handed out
     int moving = 0;   // threads that hold some of the pool's blocks for a call
+    size_t share = 0; // an eighth of the free memory, kept blocks included, when last looked at
+    Clock::time_point looked{};
 };
 
 struct Block {
@@ -67,6 +83,25 @@ size_t rounded(size_t bytes) {
         step = p / 8;
     }
     return (bytes + step - 1) / step * step;
+}
+
+// Bytes of device memory free now, for its driver.
+size_t device_free(int device) {
+    int now = 0;
+    size_t bytes = 0, all = 0;
+    if (hipGetDevice(&now) != hipSuccess) return 0;
+    if (now != device && hipSetDevice(device) != hipSuccess) return 0;
+    if (hipMemGetInfo(&bytes, &all) != hipSuccess) {
+        (void)hipGetLastError();
+        bytes = 0;
+    }
+    if (now != device) (void)hipSetDevice(now);
+    return bytes;
+}
+
+size_t pool_bytes() {
+    const char* env = getenv("FVPCG_POOL_MB");
+    return env && *env ? (size_t)std::max(0.0, atof(env) * 1048576.0) : kPoolBytes;
 }
 
 // Moves everything kept into `out`.
@@ -205,10 +240,18 @@ void pool_free(void* q) noexcept {
         listed = false;
     }
     Blocks out;
-    if (p.live == 0)
+    if (p.live == 0) {
         drop_all(p, out);
-    else
-        drop_above(p, kPoolBytes, out);
+    } else {
+        if (p.kept > kSmallBytes && Clock::now() - p.looked > kLookEvery) {
+            p.looked = Clock::now();  // other threads need not look now
+            lock.unlock();
+            const size_t bytes = device_free(b.device);
+            lock.lock();
+            p.share = (bytes + p.kept) / 8;
+        }
+        drop_above(p, std::min(pool_bytes(), std::max(kSmallBytes, p.share)), out);
+    }
     give_back(r, p, out, lock);
     lock.unlock();
     if (!listed) (void)hipFree(q);

@@ -274,6 +274,38 @@ void no_host_memory() {
     }
     (void)live;
 }
+// What is kept stays within an eighth of the free memory (looked at every 50 ms)
+// and the bound that the environment sets; the block just freed counts.
+void bounds() {
+    void* live = get(MiB);
+    auto keep = [&](size_t each, int n) {
+        std::vector<void*> v;
+        for (int i = 0; i < n; ++i) v.push_back(get(each + (size_t)i * 4096));
+        for (void* q : v) {
+            std::this_thread::sleep_for(std::chrono::milliseconds(51));
+            pool_free(q);
+        }
+        return used - MiB;  // all but `live`
+    };
+    CHECK(keep(GiB, 12) <= 8 * GiB && used >= 7 * GiB);
+    total = 24 * GiB;
+    CHECK(keep(GiB, 12) <= 3 * GiB && used >= 2 * GiB);
+    CHECK(keep(64 * MiB, 30) >= 256 * MiB);
+    total = used + 200 * MiB;  // the rest of the process has taken the device
+    std::this_thread::sleep_for(std::chrono::milliseconds(51));
+    void* a = nullptr;
+    CHECK(pool_alloc(&a, 100 * MiB) == hipSuccess);
+    pool_free(a);
+    total = (size_t)288 << 30;
+    setenv("FVPCG_POOL_MB", "100", 1);
+    CHECK(keep(30 * MiB, 10) <= 100 * MiB);
+    setenv("FVPCG_POOL_MB", "0", 1);
+    void* b = get(MiB);
+    pool_free(b);
+    CHECK(blocks.size() == 1);
+    pool_free(live);
+    CHECK(used == 0);
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -282,7 +314,8 @@ int main(int argc, char** argv) {
                                                          {"wait_in_free", wait_in_free},
                                                          {"full", full},
                                                          {"threads", threads},
-                                                         {"no_host_memory", no_host_memory}};
+                                                         {"no_host_memory", no_host_memory},
+                                                         {"bounds", bounds}};
     auto it = scenarios.find(argc > 1 ? argv[1] : "");
     if (it == scenarios.end()) return 2;
     it->second();

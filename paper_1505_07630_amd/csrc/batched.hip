@@ -77,6 +77,9 @@ struct ResBatchPlan {
     int members = 0;  // of all teams
     std::vector<int4> tasks;
     std::vector<int> list;
+    int4* d_tasks = nullptr;
+    int* d_list = nullptr;
+    double* d_slots = nullptr;
 };
 
 struct Tuning {
@@ -115,11 +118,9 @@ struct fvpcg_batch {
     int* h_order = nullptr;    // pinned staging
     int* h_abort = nullptr;    // pinned
     unsigned long long spin_ticks = 0;
-    // resident solves (resident.hpp): the plan's work lists and buffers
-    fvpcg::ResBatchPlan res;
-    int4* d_rtasks = nullptr;
-    int* d_rlist = nullptr;
-    double* d_rslots = nullptr;
+    // resident solves (resident.hpp): the plans of standard and pipelined CG
+    // (their tiles differ), made by the first solve of each and kept
+    fvpcg::ResBatchPlan res[2];
     unsigned* d_rmeet = nullptr;  // rendezvous word, abort flag
     fvpcg::ResOut* d_rout = nullptr;
     fvpcg::ResOut* h_rout = nullptr;  // pinned
@@ -970,7 +971,6 @@ int autotune(fvpcg_batch* bt, const double* b, const double* x0, double tol, int
 // 2,048 cells per system a whole CU per system is more than it can use and
 // the queue (several workgroups per CU) is the better form.
 void resident_batch_plan(const fvpcg_batch* bt, int bs, ResBatchPlan& p) {
-    p = ResBatchPlan();
     p.block = bs;
     int cus = 0;
     double ticks = 0;
@@ -1019,7 +1019,8 @@ void resident_batch_plan(const fvpcg_batch* bt, int bs, ResBatchPlan& p) {
         }
         offset += g;
     }
-    p.list.push_back(0);
+    p.tasks.clear();
+    p.list.assign(1, 0);
     for (auto& l : lists) {
         p.tasks.insert(p.tasks.end(), l.begin(), l.end());
         p.list.push_back((int)p.tasks.size());
@@ -1037,16 +1038,13 @@ int solve_batched_resident(fvpcg_batch* bt, const double* b, double* x, double t
     if ((env && env[0] == '0') || teams_mode() != 'a') return FVPCG_OK;
     const int bs = method == 0 ? kResBsCg : kResBsPipe;
     int rc;
-    if (bt->res.block != bs) {
-        resident_batch_plan(bt, bs, bt->res);
-        dev_free(bt->d_rtasks);
-        dev_free(bt->d_rlist);
-        dev_free(bt->d_rslots);
-        if (!bt->res.rpt) return FVPCG_OK;
-        ResBatchPlan& p = bt->res;
-        if ((rc = dev_alloc(&bt->d_rtasks, p.tasks.size(), "resident tasks")) ||
-            (rc = dev_alloc(&bt->d_rlist, p.list.size(), "resident task lists")) ||
-            (rc = dev_alloc(&bt->d_rslots, res_slots(p.members), "resident slots")) ||
+    ResBatchPlan& p = bt->res[method];
+    if (!p.block) {
+        resident_batch_plan(bt, bs, p);
+        if (!p.rpt) return FVPCG_OK;
+        if ((!p.d_tasks && (rc = dev_alloc(&p.d_tasks, p.tasks.size(), "resident tasks"))) ||
+            (!p.d_list && (rc = dev_alloc(&p.d_list, p.list.size(), "resident task lists"))) ||
+            (!p.d_slots && (rc = dev_alloc(&p.d_slots, res_slots(p.members), "resident slots"))) ||
             (!bt->d_rmeet && (rc = dev_alloc(&bt->d_rmeet, 2, "resident rendezvous"))) ||
             (!bt->d_rout && (rc = dev_alloc(&bt->d_rout, (size_t)bt->nsys, "resident results")))) {
             p.block = 0;
@@ -1059,14 +1057,14 @@ int solve_batched_resident(fvpcg_batch* bt, const double* b, double* x, double t
             (void)hipGetLastError();
             return set_error(FVPCG_OUT_OF_MEMORY, "pinned allocation failed");
         }
-        // the vectors stay until the next plan: copied synchronously
-        if (hipMemcpy(bt->d_rtasks, p.tasks.data(), sizeof(int4) * p.tasks.size(), hipMemcpyHostToDevice) != hipSuccess ||
-            hipMemcpy(bt->d_rlist, p.list.data(), sizeof(int) * p.list.size(), hipMemcpyHostToDevice) != hipSuccess) {
+        // on the caller's stream: a copy on the null stream would wait for all others
+        if (hipMemcpyAsync(p.d_tasks, p.tasks.data(), sizeof(int4) * p.tasks.size(), hipMemcpyHostToDevice, s) != hipSuccess ||
+            hipMemcpyAsync(p.d_list, p.list.data(), sizeof(int) * p.list.size(), hipMemcpyHostToDevice, s) != hipSuccess ||
+            hipStreamSynchronize(s) != hipSuccess) {
             p.block = 0;
             return hip_fail(hipGetLastError(), "resident task copy", __FILE__, __LINE__);
         }
     }
-    const ResBatchPlan& p = bt->res;
     const fvpcg_mesh* m = bt->mesh;
     if (!p.rpt || resident_quiet(m->device)) return FVPCG_OK;
     std::mutex* mu = resident_teams(m->device);
@@ -1078,7 +1076,7 @@ int solve_batched_resident(fvpcg_batch* bt, const double* b, double* x, double t
     resident_device(m->device, &cus, &ticks);
     int* abort_flag = reinterpret_cast<int*>(bt->d_rmeet + 1);
     FV_HIP(hipEventRecord(bt->e0, s));
-    if ((rc = resident_reset(bt->d_rslots, res_slots(p.members), bt->d_rmeet, abort_flag, bt->d_rout, bt->nsys, s)))
+    if ((rc = resident_reset(p.d_slots, res_slots(p.members), bt->d_rmeet, abort_flag, bt->d_rout, bt->nsys, s)))
         return rc;
     ResSystem sys{m->col16 ? (const void*)m->col16 : (const void*)m->col,
                   bt->mat->val,
@@ -1093,9 +1091,9 @@ int solve_batched_resident(fvpcg_batch* bt, const double* b, double* x, double t
                   0,
                   tol,
                   maxit};
-    ResTeam t{0, p.grid, bt->d_rslots, bt->d_rmeet, abort_flag, nullptr, (unsigned long long)(ticks * resident_meet_ms()),
+    ResTeam t{0, p.grid, p.d_slots, bt->d_rmeet, abort_flag, nullptr, (unsigned long long)(ticks * resident_meet_ms()),
               bt->spin_ticks, 0};
-    ResBatch rb{bt->d_cell_off, bt->d_rtasks, bt->d_rlist, bt->d_rout};
+    ResBatch rb{bt->d_cell_off, p.d_tasks, p.d_list, bt->d_rout};
     ResBatchKernel k = method == 0 ? res_batch_cg(p.rpt, m->WT, m->col16 != nullptr, jac)
                                    : res_batch_pipe(p.rpt, m->WT, m->col16 != nullptr, jac);
     hipLaunchKernelGGL(k, dim3(p.grid), dim3(p.block), 0, s, sys, t, rb);
@@ -1120,9 +1118,11 @@ int solve_batched_resident(fvpcg_batch* bt, const double* b, double* x, double t
 
 void batch_free(fvpcg_batch* bt) {
     if (!bt) return;
-    dev_free(bt->d_rtasks);
-    dev_free(bt->d_rlist);
-    dev_free(bt->d_rslots);
+    for (ResBatchPlan& p : bt->res) {
+        dev_free(p.d_tasks);
+        dev_free(p.d_list);
+        dev_free(p.d_slots);
+    }
     dev_free(bt->d_rmeet);
     dev_free(bt->d_rout);
     if (bt->h_rout) (void)hipHostFree(bt->h_rout);

@@ -1185,9 +1185,14 @@ int spgemm(const CsrView& X, const CsrView& Y, CsrOut& C, hipStream_t s, ProdPla
     // Kernel choice: hash tables in LDS, and for rows too wide for the largest
     // (3,584 columns) LDS column tiles, or the heap merge where a row of X has
     // more lists than the tiles hold.  All give the same sums;
-    // FVPCG_AMG_PRODUCT = hash | tiled | merge forces one where it applies.
+    // FVPCG_AMG_PRODUCT = hash | tiled | merge forces one where it applies
+    // (merge32, dense and short, names of kernels that are gone, mean merge).
     const char* force = getenv("FVPCG_AMG_PRODUCT");
     const std::string fk = force ? force : "";
+    bool known = fk.empty();
+    for (const char* name : {"hash", "tiled", "merge", "merge32", "dense", "short"}) known = known || fk == name;
+    if (!known)
+        return set_error(FVPCG_INVALID_ARG, "FVPCG_AMG_PRODUCT=%s: not one of hash, tiled and merge", fk.c_str());
     int nnz = 0;
     bool hashed = false;
     if (fk.empty() || fk == "hash") {

@@ -1,0 +1,93 @@
+"""Setup products too wide for the smaller hash tables: random graphs, whose
+first coarse operator couples nearly everything, so that a product fills the
+128-, 512-, 2,048- and 4,096-slot tables in turn and is handed to the column
+tiles at last.  Which tables a product goes through follows from the
+hierarchy's patterns by the setup's rule, and is checked first; then the
+hierarchy against the heap merge's, bit for bit, after a refresh too.
+
+(The 64-slot table takes rows of the left operand of at most 8 entries.  The
+closed neighbourhoods of such a row's entries have at most 50 aggregates among
+them, and the table holds 56: it does not fill up in A P.)"""
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+import fvcases as fc
+from tests.gpu_util import DevCase, say, to_dev
+from tests.test_gpu_amg_products import hierarchy
+from tests.test_gpu_resident import fv  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def random_graph(n, degree, seed):
+    rng = np.random.default_rng(seed)
+    rings = [rng.permutation(n) for _ in range(degree // 2)]
+    e = np.concatenate([np.stack([p, np.roll(p, 1)], 1) for p in rings])
+    e = np.unique(np.sort(e, axis=1), axis=0)
+    up = -np.exp(0.3 * rng.standard_normal(len(e)))
+    diag = np.full(n, 0.05)
+    np.add.at(diag, e[:, 0], -up)
+    np.add.at(diag, e[:, 1], -up)
+    return fc.Case("random", (n, 1, 1), n, e[:, 0].astype(np.int32), e[:, 1].astype(np.int32), diag, up, up.copy(),
+                   rng.uniform(-1, 1, n))
+
+
+def pattern(ptr, col, shape):
+    return sp.csr_matrix((np.ones(len(col), np.int64), col, ptr), shape=shape)
+
+
+def tables(X, Y):
+    """(lanes, slots) of every table that X Y is tried with."""
+    mean = Y.nnz / Y.shape[0]
+    work = int(np.diff(Y.indptr)[X.indices].sum()) / X.shape[0]
+    longest, widest = int(np.diff(X.indptr).max()), int(np.diff((X @ Y).indptr).max())
+    lanes = 8 if mean <= 8 else 16 if mean <= 24 else 64
+    out = []
+    for slots in (64, 128, 512, 2048, 4096):
+        if (slots == 64 and (longest > 8 or lanes != 8)) or (slots == 128 and lanes == 64):
+            continue
+        if slots < 4096 and work > 32 * slots:
+            continue
+        out.append((lanes if slots <= 512 else 64, slots))
+        if widest <= slots // 8 * 7:
+            return out
+    return out + ["tiles"]
+
+
+GRAPHS = {
+    "16 lanes, 128 to 512": (20000, 4, [(16, 128), (16, 512)]),
+    "512 to 2048": (30000, 8, [(64, 512), (64, 2048)]),
+    "2048 to 4096": (60000, 8, [(64, 512), (64, 2048), (64, 4096)]),
+    "4096 to tiles": (100000, 8, [(64, 512), (64, 2048), (64, 4096), "tiles"]),
+}
+
+
+@pytest.mark.parametrize("name", list(GRAPHS))
+def test_wide_products(fv, monkeypatch, name):  # noqa: F811
+    n, degree, want = GRAPHS[name]
+    case = random_graph(n, degree, 1)
+    scale = to_dev(np.random.default_rng(7).uniform(0.9, 1.1, case.F))
+    got = {}
+    for mode in ("hash", "merge"):
+        say("wide products", name, mode)
+        monkeypatch.setenv("FVPCG_AMG_PRODUCT", mode)
+        dc = DevCase(case)
+        M = fv.AMG(dc.A, theta=0.0, coarse_size=8)
+        if mode == "hash":
+            i = np.arange(case.n)
+            A = sp.csr_matrix((np.ones(2 * case.F + case.n, np.int64),
+                               (np.concatenate([case.owner, case.neighbour, i]),
+                                np.concatenate([case.neighbour, case.owner, i]))), shape=(case.n, case.n))
+            ptr, col, _, shape = M.export(0, "P")
+            P = pattern(ptr, col, shape)
+            assert tables(P.T.tocsr(), A @ P) == want
+        first = hierarchy(M)
+        dc.A.update(dc.diag * 1.5, dc.upper * scale)
+        M.refresh()
+        got[mode] = first + hierarchy(M)
+        M.close()
+        dc.close()
+    assert len(got["merge"]) == len(got["hash"])
+    for a, b in zip(got["merge"], got["hash"]):
+        assert np.array_equal(a, b)

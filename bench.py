@@ -13,7 +13,9 @@ the pipelined kernel, which runs all iterations of a solve in one launch and
 keeps z and most of s on chip: the bytes an iteration has to move to and from
 memory divided by the average iteration time (the kernel's own clock; HIP
 events on the solve stream where the iterations are launches), against the 8
-TB/s HBM peak.  The algorithmic bytes (104n + 24F, every vector pass of the
+TB/s HBM peak.  That is the rate past the L2 caches, not of HBM alone: about
+a fifth of those bytes (d, the columns and w) comes from the 256 MB last-level
+cache.  The algorithmic bytes (104n + 24F, every vector pass of the
 folded pipelined iteration counted once, on chip or not) are in
 alg_bytes_per_launch, and their rate in hbm_gbs_algorithmic.  mixed: the
 reliable-update and restarted FP32/FP64 solvers on the same system against
@@ -72,15 +74,12 @@ def alg_bytes_pipecg_folded(n, F, iters):
 
 def on_chip_bytes(n):
     """Bytes per iteration of the vector passes that stay on chip when the
-    pipelined solve of 1.05M to 8.4M cells runs in one launch: z, s, p, r, x
-    and d up to 16 tiles of 512 rows per workgroup (256 of them), z, s and p
-    up to 32, z and 32 tiles of s up to 64 (resident.hpp)."""
+    pipelined solve of 4.2M to 8.4M cells runs in one launch (the library's
+    stats say whether it did): z in registers, and s in LDS for 32 of the up to
+    64 tiles of 512 rows that each of 256 workgroups has (resident.hpp)."""
     per = -(-(-(-n // 512)) // 256)
-    if os.environ.get("FVPCG_RESIDENT", "")[:1] == "0" or per > 64:
-        return 0
-    if per <= 16:
-        return 80 * n
-    return 48 * n if per <= 32 else 16 * n + 16 * n * 32 // per
+    assert 32 < per <= 64
+    return 16 * n + 16 * n * 32 // per
 
 
 def alg_bytes_per_iter(method, n, F, iters):
@@ -237,10 +236,10 @@ def main():
         # vectors on chip not at all, and int16 column offsets when every
         # |column - row| fits (the library's rule): six slots of 2 B instead
         # of 4 B per row
-        one_launch = on_chip_bytes(n) > 0
+        one_launch = all(s_["one_launch"] for s_ in stats)
         col16 = int(np.max(np.abs(case.neighbour.astype(np.int64) - case.owner))) <= 32767 if F else False
         moved = sum(alg_bytes_pipecg_folded(n, F, s_["iters"]) * s_["iters"] for s_ in stats) / total_iters
-        moved -= on_chip_bytes(n) + (12 * n if col16 else 0)
+        moved -= (on_chip_bytes(n) if one_launch else 0) + (12 * n if col16 else 0)
     achieved = moved / kern_s / 1e9
     traffic = measured_traffic(moved)
     kernel_name = {"pipecg": "k_res_stream<64, 6, int16_t, JAC=true>" if one_launch else

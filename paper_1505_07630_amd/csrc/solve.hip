@@ -1216,8 +1216,13 @@ int solve_mixed_reliable(const fvpcg_matrix* A, const double* b, double* x, doub
     if ((rc = state_read(w, 0, &h, s))) return rc;
     int offset = 0, updates = 0, wi = 0;
     // the K FP32 iterations between two updates in one launch, rows held on
-    // chip, where the system fits (resident_pipe32) and no other team runs
-    ResPlan plan = resident_plan32(m);
+    // chip, where the system fits (resident_pipe32) and no other team runs.
+    // From K = 3 on: every run loads the rows and writes the vectors back.  ms
+    // of 96 iterations, launches and runs, at 64^3 and 128x128x127: K = 1 4.36
+    // and 5.22, 12.6 and 14.2; K = 2 2.68 and 2.94, 8.08 and 7.78; K = 3 2.11
+    // and 2.16, 6.59 and 5.58; K = 4 1.85 and 1.77, 5.83 and 4.49.
+    ResPlan plan;
+    if (K >= 3) plan = resident_plan32(m);
     ResWork rw{};
     std::unique_lock<std::mutex> lock;
     if (plan.rpt && !h.done) {

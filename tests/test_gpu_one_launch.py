@@ -146,6 +146,16 @@ def test_mixed_path(fv, monkeypatch, name):  # noqa: F811
         dc.close()
 
 
+def test_mixed_path_of_short_periods(fv):  # noqa: F811
+    """Below three iterations between updates the launches are the faster."""
+    dc = DevCase(fc.varcoef((32, 31, 30), seed=11), fp32_copy=True)
+    for every, want in ((1, 0), (2, 0), (3, 1)):
+        say("mixed path", every)
+        _, st = fv.solve_mixed_reliable(dc.A, dc.b, tol=0.0, update_every=every, maxit=6)
+        assert st["one_launch"] == want
+    dc.close()
+
+
 def test_batch_path(fv, monkeypatch):  # noqa: F811
     import torch
 

@@ -120,6 +120,19 @@ int resident_reset(double* slots, size_t count, unsigned* meet, int* abort_flag,
 // int32 columns leave room for 3,072 rows, rows of more than 6 slots for
 // 2,048, rows of more than 8 slots for none; the literal recurrences' two more
 // vectors leave room for 2,048.
+//
+// Standard CG gathers two vectors, past the L2 caches; every line of a gather
+// is fetched by itself.  On a mesh whose cells are in no order a product
+// fetches a line per slot, which the launches' single vector finds in the L2
+// caches.  Launches against one launch, by the lines of a product: 1.09x at
+// 1.3M (60^3 shuffled), 1.13x at 1.3M (91^3, blocks of 16 cells shuffled), 1.05x at
+// 1.6M (200,000 cells with 8 neighbours, shuffled), 0.86x at 2.1M (70^3 shuffled),
+// 0.92x at 2.2M (91^3 by blocks of 8), 0.53x at 4.5M (91^3 shuffled); in order 91^3
+// has 0.6M, 2.0x.  Past the line k_res_cg_stream takes the system, which gathers
+// one vector through the caches: 0.99x to 1.09x in these.  Pipelined CG gathers
+// one vector and gains past the caches, too (1.4x to 2.3x).
+constexpr long long kCgLines = 1700000;
+
 ResPlan resident_plan(const fvpcg_mesh* m, int method) {
     ResPlan p;
     const char* env = getenv("FVPCG_RESIDENT");
@@ -140,6 +153,7 @@ ResPlan resident_plan(const fvpcg_mesh* m, int method) {
     if (rpt == 5 || rpt == 7) ++rpt;
     const int rows = m->WT > 6 || method == FVPCG_PIPECG_LITERAL ? 2048 : m->col16 ? 4096 : 3072;
     if (rpt * bs > rows || g > device_info(m->device).cus || quiet(m->device)) return p;
+    if (method == FVPCG_CG && m->lines > kCgLines) return p;
     p.size = g;
     p.rpt = rpt;
     return p;

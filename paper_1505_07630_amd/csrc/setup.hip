@@ -98,15 +98,29 @@ __global__ void k_sort_pad(const int* __restrict__ deg, int n, int W, int* col, 
     }
 }
 
-// Largest |column - row| over all slots (the matrix bandwidth).
-__global__ void k_max_offset(const int* __restrict__ col, int n, int W, int* out) {
-    int m = 0;
+// Largest |column - row| over all slots (the matrix bandwidth), and the slots
+// whose column lies in another 64 B line than the row before's.
+struct Columns {
+    unsigned long long lines;
+    int band;
+};
+__global__ void k_max_offset(const int* __restrict__ col, int n, int W, Columns* out) {
+    int m = 0, lines = 0;  // a thread's own count: at most W n / (kCheckGrid kBlock) + 1
     const size_t total = (size_t)W * n;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const int c = (int)(i % (size_t)n);
-        m = max(m, abs(col[i] - c));
+        const int c = (int)(i % (size_t)n), j = col[i];
+        m = max(m, abs(j - c));
+        lines += c == 0 || (j >> 3) != (col[i - 1] >> 3);
     }
-    block_max(m, out);
+    block_max(m, &out->band);
+    __shared__ int s_lines;
+    if (threadIdx.x == 0) s_lines = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 32; i > 0; i >>= 1) lines += __shfl_xor(lines, i, 64);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&s_lines, lines);
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(&out->lines, (unsigned long long)s_lines);
 }
 
 __global__ void k_make_col16(const int* __restrict__ col, int n, int W, int16_t* col16) {
@@ -229,11 +243,13 @@ int mesh_create(int32_t n, int32_t F, const int32_t* owner, const int32_t* nb, h
     int* fill = nullptr;
     unsigned* flags = nullptr;
     int* dmax = nullptr;
+    Columns* dcol = nullptr;
     auto fail = [&](int code) {
         dev_free(deg);
         dev_free(fill);
         dev_free(flags);
         dev_free(dmax);
+        dev_free(dcol);
         mesh_free(m);
         return code;
     };
@@ -241,6 +257,7 @@ int mesh_create(int32_t n, int32_t F, const int32_t* owner, const int32_t* nb, h
     if ((rc = dev_alloc(&m->nb, (size_t)F, "neighbour"))) return fail(rc);
     if ((rc = dev_alloc(&flags, 1, "flags"))) return fail(rc);
     if ((rc = dev_alloc(&dmax, 1, "max degree"))) return fail(rc);
+    if ((rc = dev_alloc(&dcol, 1, "column extents"))) return fail(rc);
     if ((rc = dev_alloc(&deg, (size_t)n, "row degree"))) return fail(rc);
     if ((rc = dev_alloc(&fill, (size_t)n, "row fill"))) return fail(rc);
 #define CK(x)                                                                   \
@@ -290,21 +307,19 @@ int mesh_create(int32_t n, int32_t F, const int32_t* owner, const int32_t* nb, h
     CK(hipGetLastError());
     // 16-bit column offsets when the bandwidth allows (FVPCG_COL16=0 keeps int32)
     {
+        CK(hipMemsetAsync(dcol, 0, sizeof(Columns), s));
+        hipLaunchKernelGGL(k_max_offset, dim3(std::min(grid_for((size_t)W * n), kCheckGrid)), dim3(kBlock), 0, s, m->col, n, W,
+                           dcol);
+        CK(hipGetLastError());
+        Columns hcol{};
+        if ((rc = read_back(s, &hcol, dcol, sizeof(Columns)))) return fail(rc);
+        m->bandwidth = hcol.band;
+        m->lines = (long long)hcol.lines;
         const char* env = getenv("FVPCG_COL16");
-        if (!(env && env[0] == '0')) {
-            CK(hipMemsetAsync(dmax, 0, sizeof(int), s));
-            hipLaunchKernelGGL(k_max_offset, dim3(std::min(grid_for((size_t)W * n), kCheckGrid)), dim3(kBlock), 0, s, m->col, n,
-                               W, dmax);
+        if (!(env && env[0] == '0') && hcol.band <= 32767) {
+            if ((rc = dev_alloc(&m->col16, (size_t)W * n, "ELL column offsets"))) return fail(rc);
+            hipLaunchKernelGGL(k_make_col16, dim3(grid_for((size_t)W * n)), dim3(kBlock), 0, s, m->col, n, W, m->col16);
             CK(hipGetLastError());
-            int band = 0;
-            if ((rc = read_back(s, &band, dmax, sizeof(int)))) return fail(rc);
-            m->bandwidth = band;
-            if (band <= 32767) {
-                if ((rc = dev_alloc(&m->col16, (size_t)W * n, "ELL column offsets"))) return fail(rc);
-                hipLaunchKernelGGL(k_make_col16, dim3(grid_for((size_t)W * n)), dim3(kBlock), 0, s, m->col, n, W,
-                                   m->col16);
-                CK(hipGetLastError());
-            }
         }
     }
     CK(hipStreamSynchronize(s));
@@ -313,6 +328,7 @@ int mesh_create(int32_t n, int32_t F, const int32_t* owner, const int32_t* nb, h
     dev_free(fill);
     dev_free(flags);
     dev_free(dmax);
+    dev_free(dcol);
     m->geom = make_geom(n);
     *out = m;
     return FVPCG_OK;

@@ -970,6 +970,18 @@ int autotune(fvpcg_batch* bt, const double* b, const double* x0, double tol, int
 // Resident wins where a team's rows fill its threads.  Below an average of
 // 2,048 cells per system a whole CU per system is more than it can use and
 // the queue (several workgroups per CU) is the better form.
+// Standard CG, two reductions an iteration and two vectors gathered past the L2
+// caches, needs more where there are systems enough for the queue to fill the
+// chip (more than 5/8 of the workgroups): `room`, the average cells times the
+// share of the workgroups' time that the placement uses, of at least 1,700 for
+// systems in order (lines of a product's gathers up to a fifth of its slots), in
+// proportion for others.  Queue against resident, ms of 60 iterations, and room:
+//   in order   300 of 13^3 1.29, 1.49 (1,290), 200 of 15^3 1.12, 0.90 (2,640), 2,000 of
+//              13^3 (to 1e-8) 10.3, 9.8 (2,150), 300 of 20^3 4.1, 2.3 (4,690);
+//   by eights  200 of 15^3 1.18, 1.22 (0.38 lines per slot), 300 of 20^3 4.8, 3.5 (0.31);
+//   shuffled   200 of 15^3 1.4, 2.2, 300 of 20^3 6.8, 8.6, 600 of 20^3 10.7, 14.0
+//              (6,250), 300 of 28^3 28.9, 23.6 (12,860).
+// Pipelined CG gains in all of these but 300 of 13^3 shuffled (1.63, 1.67).
 void resident_batch_plan(const fvpcg_batch* bt, int bs, ResBatchPlan& p) {
     p.block = bs;
     int cus = 0;
@@ -1006,6 +1018,7 @@ void resident_batch_plan(const fvpcg_batch* bt, int bs, ResBatchPlan& p) {
     for (int b = 0; b < grid; ++b) free_at[b] = {0.0, b};
     std::vector<std::vector<int4>> lists(grid);
     int offset = 0;
+    double used = 0.0, all = 0.0;
     for (int i : order) {
         const int g = std::max(1, (tiles[i] + rpt - 1) / rpt);
         std::partial_sort(free_at.begin(), free_at.begin() + g, free_at.end());
@@ -1013,12 +1026,17 @@ void resident_batch_plan(const fvpcg_batch* bt, int bs, ResBatchPlan& p) {
         double start = 0.0;
         for (int r = 0; r < g; ++r) start = std::max(start, free_at[r].first);
         const double end = start + std::cbrt((double)(bt->cell_off[i + 1] - bt->cell_off[i]) + 1.0);
+        used += g * (end - start);
+        all = std::max(all, end);
         for (int r = 0; r < g; ++r) {
             lists[wg[free_at[r].second]].push_back(make_int4(i, r, g, offset));
             free_at[r].first = end;
         }
         offset += g;
     }
+    const double cells = (double)std::max(bt->ncells, 1);
+    const double lines = (double)bt->mesh->lines / (cells * bt->mesh->W), room = cells / bt->nsys * used / (grid * all);
+    if (bs == kResBsCg && 8LL * bt->nsys > 5LL * grid && room < 1700.0 * std::max(1.0, 5.0 * lines)) return;
     p.tasks.clear();
     p.list.assign(1, 0);
     for (auto& l : lists) {

@@ -156,6 +156,31 @@ def test_mixed_path_of_short_periods(fv):  # noqa: F811
     dc.close()
 
 
+@pytest.mark.parametrize("name,count,edge,order,want", [
+    ("second round nearly empty", 300, 13, "yes", 0), ("in order", 200, 15, "yes", 1),
+    ("rounds filled", 510, 13, "yes", 1), ("in no order", 300, 20, "no", 0), ("in order, larger", 300, 20, "yes", 1),
+    ("few systems", 100, 15, "no", 1)])
+def test_batch_path_of_standard_cg(fv, monkeypatch, name, count, edge, order, want):  # noqa: F811
+    """Standard CG of many small systems, or of systems whose cells are in no
+    order, keeps to the queue where the queue fills the chip; pipelined CG runs
+    in one launch."""
+    import torch
+
+    from tests.test_gpu_one_launch_order import shuffled
+
+    monkeypatch.setenv("FVPCG_TUNE", "0")
+    case = fc.varcoef((edge, edge, edge), seed=2, permute=False)
+    bt = fc.concat([case if order == "yes" else shuffled(case)] * count)
+    B = fv.Batch(bt.cell_off, bt.face_off, to_dev(bt.owner, torch.int32), to_dev(bt.neighbour, torch.int32),
+                 to_dev(bt.diag), to_dev(bt.upper))
+    b = to_dev(bt.b)
+    for method, path in (("pipecg", 1), ("cg", want)):
+        say("batch path", name, method)
+        _, st, _ = fv.solve_batched(B, b, x=torch.zeros_like(b), tol=1e-9, maxit=3, method=method)
+        assert all(s["one_launch"] == path for s in st)
+    B.close()
+
+
 def test_batch_path(fv, monkeypatch):  # noqa: F811
     import torch
 

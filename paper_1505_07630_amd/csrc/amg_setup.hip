@@ -738,7 +738,7 @@ __global__ __launch_bounds__(64) void k_gemm_tiled(const int* __restrict__ xptr,
 // memory three times per G lists.  At 7.08M cells, all
 // products of a setup: 32 ms with heap merges (22 ms), register merges of short
 // rows and dense rows; 5 ms with tables (setup 80 -> 37 ms, refresh 41 -> 15 ms).  A row with more than 7/8 T columns sets
-// *full and is left out: the caller takes a larger table.
+// *full and is left out: the caller takes a larger table or another kernel.
 #pragma clang fp contract(off)
 template <int G, int T>
 __global__ __launch_bounds__(64) void k_gemm_hash(const int* __restrict__ xptr, const int* __restrict__ xcol,
@@ -1132,8 +1132,6 @@ int spgemm_launch(const CsrView& X, const CsrView& Y, const ProdPlan& plan, cons
             FV_HASH(16, 128);
             FV_HASH(16, 512);
             FV_HASH(64, 512);
-            FV_HASH(64, 2048);
-            FV_HASH(64, 4096);
 #undef FV_HASH
             break;
         }
@@ -1183,7 +1181,7 @@ int spgemm(const CsrView& X, const CsrView& Y, CsrOut& C, hipStream_t s, ProdPla
     if ((rc = read_scalar(&mlen, mx.p, s))) return rc;
     lds_fit(mlen, &lcap, &per_wg);
     // Kernel choice: hash tables in LDS, and for rows too wide for the largest
-    // (3,584 columns) LDS column tiles, or the heap merge where a row of X has
+    // (448 columns) LDS column tiles, or the heap merge where a row of X has
     // more lists than the tiles hold.  All give the same sums;
     // FVPCG_AMG_PRODUCT = hash | tiled | merge forces one where it applies
     // (merge32, dense and short, names of kernels that are gone, mean merge).
@@ -1200,18 +1198,22 @@ int spgemm(const CsrView& X, const CsrView& Y, CsrOut& C, hipStream_t s, ProdPla
         // product count does not already rule out (measured on the Galerkin
         // products: 4 to 35 products per distinct column), the next larger one
         // when a row fills it.  64 slots only for rows of X of up to 8 entries
-        // (level 0's).
+        // (level 0's).  Larger tables than 512 slots hold fewer rows per CU and
+        // rank each row's columns in the square of their number: a product of
+        // 1,567 columns took 3.5 ms with 2,048 slots and 1.7 by tiles, one of 2,924
+        // 23.5 ms with 4,096 and 4.8 (random graphs with 8 neighbours, 30,000 and
+        // 60,000 rows; setups 17.7 and 51 ms with such tables, 14.4 and 27 without).
         const double list = (double)Y.nnz / (double)std::max(Y.n, 1);
         const double work = (double)total / (double)std::max(rows, 1);
         const int lanes = list <= 8.0 ? 8 : list <= 24.0 ? 16 : 64;
         DevBuf<int> full;
         if ((rc = full.alloc(1, "product table flag"))) return rc;
-        for (int slots : {64, 128, 512, 2048, 4096}) {
+        for (int slots : {64, 128, 512}) {
             if (slots == 64 && (mlen > 8 || lanes != 8)) continue;
             if (slots == 128 && lanes == 64) continue;
-            if (slots < 4096 && work > 32.0 * slots) continue;
+            if (work > 32.0 * slots && (slots < 512 || mlen <= kTileMaxLists)) continue;
             plan->mode = kProdHash;
-            plan->lanes = slots > 512 ? 64 : lanes;
+            plan->lanes = lanes;
             plan->slots = slots;
             FV_HIP(hipMemsetAsync(full.p, 0, sizeof(int), s));
             if ((rc = spgemm_launch(X, Y, *plan, off.p, tcol.p, tval.p, cnt.p, full.p, s))) return rc;

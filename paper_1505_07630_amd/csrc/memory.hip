@@ -51,7 +51,7 @@ struct Pool {
     size_t kept = 0;  // bytes in both, and in `pending` blocks being synchronised
     size_t live = 0;  // blocks handed out
     int moving = 0;   // threads that hold some of the pool's blocks for a call
-    size_t share = 0; // an eighth of the free memory, kept blocks included, when last looked at
+    size_t share = ~(size_t)0;  // an eighth of the free memory, kept blocks included, when last looked at
     Clock::time_point looked{};
 };
 
@@ -85,18 +85,18 @@ size_t rounded(size_t bytes) {
     return (bytes + step - 1) / step * step;
 }
 
-// Bytes of device memory free now, for its driver.
-size_t device_free(int device) {
+// Bytes of device memory free now; false if they cannot be told (for instance
+// while a capture is under way).
+bool device_free(int device, size_t* bytes) {
     int now = 0;
-    size_t bytes = 0, all = 0;
-    if (hipGetDevice(&now) != hipSuccess) return 0;
-    if (now != device && hipSetDevice(device) != hipSuccess) return 0;
-    if (hipMemGetInfo(&bytes, &all) != hipSuccess) {
-        (void)hipGetLastError();
-        bytes = 0;
+    size_t all = 0;
+    bool ok = hipGetDevice(&now) == hipSuccess && (now == device || hipSetDevice(device) == hipSuccess);
+    if (ok) {
+        ok = hipMemGetInfo(bytes, &all) == hipSuccess;
+        if (now != device) (void)hipSetDevice(now);
     }
-    if (now != device) (void)hipSetDevice(now);
-    return bytes;
+    if (!ok) (void)hipGetLastError();
+    return ok;
 }
 
 size_t pool_bytes() {
@@ -246,9 +246,10 @@ void pool_free(void* q) noexcept {
         if (p.kept > kSmallBytes && Clock::now() - p.looked > kLookEvery) {
             p.looked = Clock::now();  // other threads need not look now
             lock.unlock();
-            const size_t bytes = device_free(b.device);
+            size_t bytes = 0;
+            const bool told = device_free(b.device, &bytes);
             lock.lock();
-            p.share = (bytes + p.kept) / 8;
+            if (told) p.share = (bytes + p.kept) / 8;
         }
         drop_above(p, std::min(pool_bytes(), std::max(kSmallBytes, p.share)), out);
     }

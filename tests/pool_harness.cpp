@@ -27,6 +27,7 @@ std::map<void*, size_t> blocks;
 size_t total = (size_t)288 << 30, used = 0, next_addr = (size_t)1 << 40;
 std::atomic<int> syncs{0}, frees{0};
 thread_local int device = 0;
+std::atomic<bool> info_fails{false};
 std::atomic<bool> hold{false}, held{false};  // calls that wait for the device are held back; one is
 std::atomic<int> new_fails{-1};              // the how-manieth operator new from now throws (-1: none)
 
@@ -80,6 +81,7 @@ hipError_t hipFree(void* p) {
     return hipSuccess;
 }
 hipError_t hipMemGetInfo(size_t* f, size_t* t) {
+    if (info_fails) return hipErrorUnknown;
     std::lock_guard<std::mutex> l(mu);
     *f = total - used;
     *t = total;
@@ -306,6 +308,21 @@ void bounds() {
     pool_free(live);
     CHECK(used == 0);
 }
+
+// Where the free memory cannot be told (a capture is under way) nothing is
+// given back for it: hipFree is no better off there.
+void no_info() {
+    void* live = get(MiB);
+    std::vector<void*> v;
+    for (int i = 0; i < 6; ++i) v.push_back(get(GiB));
+    for (int i = 0; i < 3; ++i) pool_free(v[(size_t)i]);
+    CHECK(frees == 0);
+    info_fails = true;
+    std::this_thread::sleep_for(std::chrono::milliseconds(51));
+    for (int i = 3; i < 6; ++i) pool_free(v[(size_t)i]);
+    CHECK(frees == 0);
+    (void)live;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -315,7 +332,8 @@ int main(int argc, char** argv) {
                                                          {"full", full},
                                                          {"threads", threads},
                                                          {"no_host_memory", no_host_memory},
-                                                         {"bounds", bounds}};
+                                                         {"bounds", bounds},
+                                                         {"no_info", no_info}};
     auto it = scenarios.find(argc > 1 ? argv[1] : "");
     if (it == scenarios.end()) return 2;
     it->second();

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.cpu
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1505_07630_amd", "csrc")
-SCENARIOS = ["reuse", "wait_in_alloc", "wait_in_free", "full", "threads", "no_host_memory", "bounds"]
+SCENARIOS = ["reuse", "wait_in_alloc", "wait_in_free", "full", "threads", "no_host_memory", "bounds", "no_info"]
 
 
 @pytest.fixture(scope="module")

@@ -226,18 +226,24 @@ FVPCG_API int fvpcg_solve_backward(const fvpcg_matrix* mat, const double* x, con
                          int32_t maxit, int32_t method, int32_t precond, void* stream,
                          fvpcg_stats* stats);
 
-/* ---- Solves in one launch: where a system's rows, or enough of its vectors,
- * fit on the chip (fvpcg_solve: literal pipelined up to 0.5M cells, standard
- * up to 4.2M, pipelined up to 8.4M; the FP32 iterations of
- * fvpcg_solve_mixed_reliable and BiCGSTAB with two or three right-hand sides
- * up to 2.1M; batches of at least 2,048 cells per system on average) up to 256
- * workgroups run all iterations in one launch.  They must be on the device
- * together: if they have not met within FVPCG_RESIDENT_MEET_MS (default 20),
- * or another such solve is running on the device, the call iterates launch by
- * launch instead, as with FVPCG_RESIDENT=0, with the same results (bit for
- * bit, but for batches, whose sums are ordered otherwise); after a missed
- * meeting so do the device's next calls, for 50 times that limit.  Each later
- * wait of a solve is bounded too (FVPCG_RESIDENT_SPIN_MS, default 5000): past it every
+/* ---- Solves in one launch: where a system's rows, or enough of its
+ * vectors, fit on the chip (fvpcg_solve: literal pipelined up to 0.5M cells,
+ * standard up to 4.2M, pipelined up to 8.4M; the FP32 iterations of
+ * fvpcg_solve_mixed_reliable with update_every >= 3 and BiCGSTAB with two or
+ * three right-hand sides up to 2.1M, with one up to 0.13M; batches of at
+ * least 2,048 cells per system on average, standard CG of many small or
+ * unordered systems apart), up to 256 workgroups run all iterations in one
+ * launch (stats->one_launch).  Until it ends they hold up to 128 KB of LDS and
+ * most registers of their CUs, so kernels of other streams that need as much
+ * wait for the whole solve, and do not run between its launches;
+ * FVPCG_RESIDENT=0 iterates by launches.  The
+ * workgroups must be on the device together: if they have not met within
+ * FVPCG_RESIDENT_MEET_MS (default 20), or another such solve is running on
+ * the device, the call iterates launch by launch instead, as with
+ * FVPCG_RESIDENT=0, with the same results (bit for bit, but for batches,
+ * whose sums are ordered otherwise); after a missed meeting so do the
+ * device's next calls, for 50 times that limit.  Each later wait of a solve
+ * is bounded too (FVPCG_RESIDENT_SPIN_MS, default 5000): past it every
  * workgroup leaves, x and stats are invalid and FVPCG_DEVICE_ERROR is
  * returned. */
 
@@ -346,7 +352,7 @@ FVPCG_API int fvpcg_piso_run(fvpcg_piso* piso, double dt, int32_t nsteps, int32_
  * It calls no hipMalloc, hipFree, pinned-memory or event routine: the
  * convergence state is read into host stack memory and waited for after each
  * chunk of iterations, and stats->device_ms / iter_ms come from the host
- * clock.  The matrix (created beforehand) must live on the current device.
+ * clock (the kernel's clock where one launch solves).  The matrix (created beforehand) must live on the current device.
  * Every call on one GPU shares that array and keeps the last call's contents:
  * calls that overlap on one GPU (other threads, other streams) race. */
 FVPCG_API int fvpcg_solve_noalloc(const fvpcg_matrix* mat, const double* b, double* x, double tol, int32_t maxit,

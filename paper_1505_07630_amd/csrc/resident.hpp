@@ -4,8 +4,8 @@
 //
 // What bounds a small system is not memory but the chain of one iteration:
 // a launch, the slot -> gather loads, the reduction's ticket and the scalars.
-// With one launch per iteration that chain is 5.1 us at 1.7k cells, 7.1 us at
-// 32k and 40.7 us at 1M (where every array is read again from the last-level
+// With one launch per iteration that chain is 6.3 us at 1.7k cells, 6.8 us at
+// 32k and 33 us at 1M (where every array is read again from the last-level
 // cache).  Here an iteration reads nothing but the neighbours' exchanged
 // vector, and its only synchronisation is the reduction itself:
 //
@@ -26,8 +26,8 @@
 //     everybody has published k - 1, hence read k - 2), which every member
 //     sees before it can reach reduction k + 2.
 //
-// Pipelined CG on MI355X takes 3.0 us per iteration at 8k cells, 3.3 at 32k, 5.8
-// at 262k and 10.1 at 1M.  Acquire fences with cached gathers instead, and a
+// Pipelined CG on MI355X takes 2.3 us per iteration at 1.7k cells (one workgroup),
+// 3.1 at 8k, 3.2 at 32k, 5.6 at 262k and 9.9 at 1M.  Acquire fences with cached gathers instead, and a
 // two-level reduction, were slower at every size (1M rows: 12.4 us for the
 // former when this took 10.9); own tiles of the exchanged vector in LDS as
 // well, for the neighbours within the tile, 6.2 us at 262k and 15 at 1M.
@@ -36,7 +36,10 @@
 // with a short time limit; a team that does not come together there leaves
 // without having touched x, and the host takes the launch-per-iteration path.
 // Past the rendezvous every member holds its place until it ends, so every
-// wait ends; the waits are bounded by a clock all the same.
+// wait ends; the waits are bounded by a clock all the same (but a queued team's
+// first, which lasts as long as its members' earlier systems: team_sum).  A
+// wait that is given up ends the call with an error: members may have written
+// x by then.
 //
 // Sums are formed in the launch-per-iteration kernels' order (rows per
 // thread, wave, workgroup, workgroups in index order) from the same
@@ -201,8 +204,8 @@ __device__ __forceinline__ void sums_step(double (&v)[P], int n, int lane) {
 // sum of value l mod P (P = N rounded up to a power of two, at most 16) over
 // its row.  The tree is that of wave_sum (adjacent pairs, pairs of pairs, ...),
 // whose total is (row 0 + row 1) + (row 2 + row 3): the same bits, for 12 values
-// in a third of the instructions (1,728 cells: 2.0 -> 1.7 us per iteration; for
-// the 3 values of a team wave_sum is the quicker).
+// in a third of the instructions (1,728 cells, 99 iterations: a solve 307 -> 251 us;
+// for the 3 values of a team wave_sum is the quicker).
 template <int N>
 struct RowSums {
     static constexpr int P = N <= 1 ? 1 : N <= 2 ? 2 : N <= 4 ? 4 : N <= 8 ? 8 : 16;

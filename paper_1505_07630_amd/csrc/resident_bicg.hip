@@ -4,8 +4,9 @@
 // Per iteration and row the launches move, for three components, 536 bytes:
 // v and t are written once and read back. Here a team (resident.hpp) keeps v
 // in registers (vectors of 16 indexed by the tile number) and t in LDS (two
-// components, the third in registers too): 424 bytes, and four meetings of
-// the team instead of four launches:
+// components, the third in registers too): 416 bytes, 40 fewer per component (v
+// is read twice, t once), and four meetings of the team instead of four
+// launches:
 //   v = A M^-1 p, (rhat, v)                       -> alpha
 //   s = r - alpha v in r's place
 //   t = A M^-1 s and its five sums                -> omega, rho', beta
@@ -13,7 +14,7 @@
 // Up to 16 tiles of 512 rows per member (2,097,152 cells).  p and s are stored
 // with agent scope and gathered through the caches, which every member
 // invalidates after the meetings they follow.  Bound by the passes over
-// memory: at 128^3 and three components 889 MB in 187 us, 4.75 TB/s (by
+// memory: at 128^3 and three components 872 MB in 187 us, 4.67 TB/s (by
 // launches 1,124 MB in 245 us).
 #include "bicgstab.hpp"
 #include "resident.hpp"

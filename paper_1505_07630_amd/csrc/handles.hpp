@@ -64,7 +64,7 @@ struct fvpcg_mesh {
     int maxdeg = 0;     // largest row degree
     int bandwidth = -1; // largest |column - row|
     long long lines = 0;  // slots whose column lies in another 64 B line of a vector than the row before's: what
-                          // a product's gathers fetch (0.14 of the slots for a cube in order, all without one)
+                          // a product's gathers fetch (0.14 of the slots for a cube in order, all for one in none)
     int W = 0;       // slots per row: maxdeg rounded up to a kernel width
     int WT = 0;      // kernel specialisation width (== W)
     int* owner = nullptr;

@@ -286,13 +286,12 @@ __device__ __forceinline__ bool team_sum(double (&v)[NV], ResTeam& t) {
         const double* q = buf + (size_t)sum * t.size;
         constexpr int kC = kResMaxTeam / 64;
         double g[kC];
-        unsigned spins = 0;
         // A queued team's first sums come when its last member has finished
         // its earlier systems, which takes as long as these do (every member
         // is resident and each list is in the same order, so it ends); from
         // the second reduction on all members are at work on this system.
         const unsigned long long limit = t.queued && t.k == 0 ? ~0ull : t.spin_ticks;
-        const unsigned every = limit ? 63u : 0u;  // a limit of 0: given up at the first poll that finds a sum missing
+        unsigned spins = limit ? 0u : 63u;  // a limit of 0: given up at the first poll that finds a sum missing
         const unsigned long long t0 = (unsigned long long)wall_clock64();
         for (;;) {
             bool wait = false;
@@ -305,7 +304,7 @@ __device__ __forceinline__ bool team_sum(double (&v)[NV], ResTeam& t) {
                 }
             }
             if (!__any(wait)) break;
-            if ((++spins & every) == 0 &&
+            if ((++spins & 63u) == 0 &&
                 ((unsigned long long)wall_clock64() - t0 > limit ||
                  __hip_atomic_load(t.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
                 if (lane == 0) {

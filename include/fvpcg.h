@@ -60,7 +60,8 @@ typedef enum fvpcg_status {
     FVPCG_INVALID_ARG = -1,   /* null pointer, n < 1, tol < 0, b aliases x, tol = maxit = 0, ... */
     FVPCG_INVALID_MESH = -2,  /* addressing out of range, not owner < neighbour, not strictly sorted */
     FVPCG_BREAKDOWN = -3,     /* p'Ap <= 0, a non-finite scalar, or diag <= 0 under Jacobi */
-    FVPCG_DEVICE_ERROR = -4,  /* a HIP call failed; the HIP message is in fvpcg_last_error() */
+    FVPCG_DEVICE_ERROR = -4,  /* a HIP call failed (the HIP message is in fvpcg_last_error()), or a wait
+                                 between the workgroups of a solve was given up (x is invalid) */
     FVPCG_OUT_OF_MEMORY = -5, /* a device or pinned allocation failed */
     FVPCG_UNSUPPORTED = -6    /* row degree > FVPCG_MAX_ROW_DEGREE, sizes beyond int32 slots, ... */
 } fvpcg_status;

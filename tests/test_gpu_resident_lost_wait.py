@@ -96,7 +96,7 @@ def test_queueing_is_not_a_lost_wait(fv, monkeypatch):  # noqa: F811
     bt = fc.concat([fc.varcoef((e, e, e), seed=e + k, permute=False) for k, e in enumerate((74, 74, 69))])
     assert [-(-c // 4096) for c in np.diff(bt.cell_off)] == [99, 99, 81]
     got = []
-    for limit in ("5000", "2"):
+    for limit in ("5000", "4"):
         monkeypatch.setenv("FVPCG_BATCH_BARRIER_TIMEOUT_MS", limit)
         B = fv.Batch(bt.cell_off, bt.face_off, to_dev(bt.owner, torch.int32), to_dev(bt.neighbour, torch.int32),
                      to_dev(bt.diag), to_dev(bt.upper))
